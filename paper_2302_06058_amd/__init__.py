@@ -76,22 +76,49 @@ def _check(fn: str, status: int) -> None:
 
 
 # -- tensor helpers (device memory and streams only) ---------------------------------
+_DTYPE_CODES: dict = {}
+
+
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype == torch.float32:
-        return F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    if not _DTYPE_CODES:
+        import torch
+        _DTYPE_CODES.update({torch.bfloat16: BF16, torch.float32: F32})
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _stream() -> int:
+def _nbytes(t) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+# The step of a small layer is bound by the host: five calls with a launch or two of 3.3 us each.  What a wrapper adds to its
+# launches counts as much: torch.cuda.current_stream() builds a Stream object (2.8 us), the handle behind it costs 0.1 us.
+# With that and new_empty (1.4 us against 1.7) a wrapper went from 5.0-7.2 us beyond its launches to 2-3.
+_raw_stream = _device_index = None
+
+
+def _bind_stream() -> None:
+    """Where to ask for the current stream's handle (torch is imported at the first call, not with this module)."""
+    global _raw_stream, _device_index
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()                          # initialises the runtime
+    try:
+        from torch._C import _cuda_getCurrentRawStream as raw, _cuda_getDevice as index
+    except ImportError:                                  # a torch without them: the public, slower way
+        raw, index = (lambda _: torch.cuda.current_stream().cuda_stream), (lambda: 0)
+    _device_index, _raw_stream = index, raw
+
+
+def _stream() -> int:
+    if _raw_stream is None:
+        _bind_stream()
+    return _raw_stream(_device_index())
 
 
 def _need_cuda(*ts):
@@ -115,8 +142,12 @@ def workspace_bytes(kind: int, I: int, J: int, T: int, K: int, dtype: int, N: in
 
 
 def _empty(shape, dtype, like):
+    return like.new_empty(shape, dtype=dtype)
+
+
+def _empty_i32(shape, like):
     import torch
-    return torch.empty(shape, dtype=dtype, device=like.device)
+    return _empty(shape, torch.int32, like)
 
 
 def operand_elems(rows: int, cols: int, N: int, M: int) -> int:
@@ -168,16 +199,15 @@ def bimask_forward_mask(W, N: int, M: int, B_bits=None):
 
 
 def bimask_forward_mask_compress(W, N: int, M: int, B_bits=None, values=None, index=None):
-    import torch
     _need_cuda(W, B_bits, values, index)
     I, J = W.shape
     ldw = _rowmajor(W)
     if B_bits is None:
-        B_bits = _empty((I, mask_words(J)), torch.int32, W)
+        B_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = _empty(_values_shape(I, J, N, M), W.dtype, W)
+        values = W.new_empty(_values_shape(I, J, N, M))
     if index is None and N <= 2:
-        index = _empty(_index_shape(I, J, N, M), torch.int32, W)
+        index = _empty_i32(_index_shape(I, J, N, M), W)
     _check("bimask_forward_mask_compress",
            lib().bimask_forward_mask_compress(_ptr(W), I, J, ldw, _dtype_code(W), N, M, _ptr(B_bits),
                                               _ptr(values), _ptr(index), _stream()))
@@ -197,12 +227,12 @@ def bimask_perm_search(B_bits, I: int, J: int, N: int, M: int, perms, scores=Non
         best = _empty((1,), torch.int32, perms)
     if best_perm is None and want_best_perm:
         best_perm = _empty((I,), torch.int32, perms)
-    need = workspace_bytes(WS_PERM_SEARCH, I, J, 0, K, BF16, N, M)
     if workspace is None:
+        need = workspace_bytes(WS_PERM_SEARCH, I, J, 0, K, BF16, N, M)
         workspace = _empty((max(need, 16),), torch.uint8, perms)
     _check("bimask_perm_search",
            lib().bimask_perm_search(_ptr(B_bits), I, J, N, M, _ptr(perms), K, _ptr(scores), _ptr(best),
-                                    _ptr(best_perm), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                    _ptr(best_perm), _ptr(workspace), _nbytes(workspace),
                                     _stream()))
     return scores, best, best_perm
 
@@ -266,16 +296,15 @@ def bimask_backward_mask(W, N: int, M: int, B_bits, perm=None, Bbar_bits=None):
 
 
 def bimask_backward_mask_compress(W, N: int, M: int, B_bits, perm=None, Bbar_bits=None, values=None, index=None):
-    import torch
     _need_cuda(W, B_bits, perm, Bbar_bits, values, index)
     I, J = W.shape
     ldw = _rowmajor(W)
     if Bbar_bits is None:
-        Bbar_bits = _empty((I, mask_words(J)), torch.int32, W)
+        Bbar_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = _empty(_values_shape(J, I, N, M), W.dtype, W)
+        values = W.new_empty(_values_shape(J, I, N, M))
     if index is None and N <= 2:
-        index = _empty(_index_shape(J, I, N, M), torch.int32, W)
+        index = _empty_i32(_index_shape(J, I, N, M), W)
     _check("bimask_backward_mask_compress",
            lib().bimask_backward_mask_compress(_ptr(W), I, J, ldw, _dtype_code(W), N, M, _ptr(B_bits), _ptr(perm),
                                                _ptr(Bbar_bits), _ptr(values), _ptr(index), _stream()))
@@ -303,9 +332,9 @@ def bimask_sparse_gemm_fwd(X, Wf_values, Wf_index, I: int, J: int, N: int, M: in
     T = X.shape[0]
     ldx = _rowmajor(X)
     if Y is None:
-        Y = _empty((T, I), X.dtype, X)
+        Y = X.new_empty((T, I))
     ldy = _rowmajor(Y)
-    wsb = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    wsb = _nbytes(workspace)
     _check("bimask_sparse_gemm_fwd",
            lib().bimask_sparse_gemm_fwd(_ptr(X), T, ldx, _ptr(Wf_values), _ptr(Wf_index), I, J, _dtype_code(X),
                                         N, M, _ptr(Y), ldy, _ptr(workspace), wsb, _stream()))
@@ -313,17 +342,17 @@ def bimask_sparse_gemm_fwd(X, Wf_values, Wf_index, I: int, J: int, N: int, M: in
 
 
 def bimask_sparse_gemm_bwd(dY, perm, Wb_values, Wb_index, I: int, J: int, N: int, M: int, dX=None, workspace=None):
-    import torch
     _need_cuda(dY, perm, Wb_values, Wb_index, dX, workspace)
     T = dY.shape[0]
     lddy = _rowmajor(dY)
     if dX is None:
-        dX = _empty((T, J), dY.dtype, dY)
+        dX = dY.new_empty((T, J))
     lddx = _rowmajor(dX)
     if workspace is None and perm is not None:
+        import torch
         need = workspace_bytes(WS_GEMM_BWD, I, J, T, 0, _dtype_code(dY), N, M)
         workspace = _empty((max(need, 16),), torch.uint8, dY)
-    wsb = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    wsb = _nbytes(workspace)
     _check("bimask_sparse_gemm_bwd",
            lib().bimask_sparse_gemm_bwd(_ptr(dY), T, lddy, _ptr(perm), _ptr(Wb_values), _ptr(Wb_index), I, J,
                                         _dtype_code(dY), N, M, _ptr(dX), lddx, _ptr(workspace), wsb, _stream()))
@@ -355,7 +384,7 @@ def group_layers(entries):
         g.n_swaps = 0 if e.get("swaps") is None else e["swaps"].shape[0]
         ws = e.get("workspace")
         g.workspace = _ptr(ws)
-        g.workspace_bytes = 0 if ws is None else ws.numel() * ws.element_size()
+        g.workspace_bytes = _nbytes(ws)
     return arr
 
 
