@@ -236,6 +236,8 @@ int bimask_sparse_gemm_bwd(const void* dY, int64_t T, int64_t lddy, const int32_
         const size_t need = bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, I, J, T, 0, dtype, N, M);
         if (!workspace || workspace_bytes < need) return BIMASK_ERR_WORKSPACE;
         if (!aligned16(workspace)) return BIMASK_ERR_ALIGN;
+        if (dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
+            return launch_gemm_f32(Wb_values, Wb_index, J, I, sp, dY, T, lddy, perm, dX, lddx, as_stream(stream));
         if (int rc = launch_gather_cols(dY, T, lddy, perm, I, dtype, workspace, as_stream(stream))) return rc;
         act = workspace;
         ldact = I;

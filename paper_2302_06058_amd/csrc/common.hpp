@@ -159,6 +159,11 @@ int launch_gather_cols(const void* dY, int64_t T, int64_t ld, const int32_t* per
 int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int64_t K, bool sparse24,
                 const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc, int dtype, hipStream_t s);
 
+// fp32 (either operand format), with the column gather of Eq. (10) in the token loads when perm is given
+int launch_gemm_f32(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, bool sparse24, const void* Bm, int64_t T,
+                    int64_t ldb, const int32_t* perm, void* C, int64_t ldc, hipStream_t s);
+bool gemm_f32_fuses_gather(int64_t T, int64_t Adim, int64_t K);
+
 // workgroup tile (weight rows x tokens) of the streaming 2:4 kernel
 enum class Sp24Tile { k256x64, k128x64, k256x128, k64x64 };
 int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bm, int64_t T,

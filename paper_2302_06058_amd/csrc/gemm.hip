@@ -9,7 +9,7 @@
 //
 // bf16, 2:4  : v_smfmac_f32_32x32x32_bf16 on the fragment-major compressed operand (gemm_sp24.hip)
 // bf16, other: v_mfma_f32_32x32x16_bf16 on the dense masked weights (this file)
-// fp32       : plain fp32 FMA kernel, small problems only (this file)
+// fp32       : v_mfma_f32_16x16x4_f32, contraction split over the wavefronts (gemm_f32.hip)
 #include "common.hpp"
 
 namespace bimask {
@@ -192,66 +192,6 @@ k_gemm_dense_bf16(const uint16_t* __restrict__ A, int64_t Adim, int64_t K, const
                 if (a + e < Adim) dst[e] = static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)));
         }
     }
-}
-
-// ---------------------------------------------------------------------------------
-// fp32: 64 x 64 tile, 16 x 16 threads, 4 x 4 outputs per thread, plain FMA.
-// ---------------------------------------------------------------------------------
-template <bool SPARSE>
-__global__ void __launch_bounds__(kThreads)
-k_gemm_f32(const float* __restrict__ A, const uint32_t* __restrict__ Ameta, int64_t Adim, int64_t K,
-           const float* __restrict__ Bm, int64_t T, int64_t ldb, float* __restrict__ C, int64_t ldc) {
-    constexpr int TS = 64, KS = 32;
-    __shared__ float sA[TS][KS + 1];
-    __shared__ float sB[TS][KS + 1];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t a0 = static_cast<int64_t>(blockIdx.x) * TS, t0 = static_cast<int64_t>(blockIdx.y) * TS;
-    const int64_t ks = ceil_div(K, 128);                 // stages of the fragment-major operand
-    float acc[4][4] = {};
-    for (int64_t k0 = 0; k0 < K; k0 += KS) {
-        for (int idx = threadIdx.x; idx < TS * KS; idx += kThreads) {
-            const int r = idx / KS, k = idx % KS;
-            const int64_t gk = k0 + k;
-            float va = 0.f, vb = 0.f;
-            if (gk < K) {
-                const int64_t a = a0 + r, t = t0 + r;
-                if (t < T) vb = Bm[t * ldb + gk];
-                if (a < Adim) {
-                    if constexpr (SPARSE) {
-                        const int64_t g = gk >> 2;
-                        const int pos = static_cast<int>(gk & 3);
-                        const uint32_t nib = (Ameta[tiled_idx_word(a, g, ks)] >> (4 * (g & 7))) & 15u;
-                        const int p0 = nib & 3, p1 = nib >> 2;
-                        if (pos == p0) va = A[tiled_val_off(a, 2 * g, ks)];
-                        else if (pos == p1) va = A[tiled_val_off(a, 2 * g + 1, ks)];
-                    } else {
-                        va = A[tiled_dense_off(a, gk, ks)];
-                    }
-                }
-            }
-            sA[r][k] = va;
-            sB[r][k] = vb;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int k = 0; k < KS; ++k) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { av[u] = sA[tx * 4 + u][k]; bv[u] = sB[ty * 4 + u][k]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(bv[u], av[v], acc[u][v]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t t = t0 + ty * 4 + u, a = a0 + tx * 4 + v;
-            if (t < T && a < Adim) C[t * ldc + a] = acc[u][v];
-        }
 }
 
 // out[t][r] = in[t][perm[r]]   (the column permutation of g(Y) in Eq. 10)
@@ -594,16 +534,7 @@ bool gemm_bwd_needs_gather(int64_t I, int64_t J, int dtype, int N, int M) {
 
 int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int64_t K, bool sparse24,
                 const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc, int dtype, hipStream_t s) {
-    if (dtype == BIMASK_F32) {
-        dim3 grid(static_cast<unsigned>(ceil_div(Adim, 64)), static_cast<unsigned>(ceil_div(T, 64)));
-        if (sparse24)
-            hipLaunchKernelGGL(k_gemm_f32<true>, grid, dim3(kThreads), 0, s, static_cast<const float*>(A_values),
-                               A_index, Adim, K, static_cast<const float*>(Bm), T, ldb, static_cast<float*>(C), ldc);
-        else
-            hipLaunchKernelGGL(k_gemm_f32<false>, grid, dim3(kThreads), 0, s, static_cast<const float*>(A_values),
-                               A_index, Adim, K, static_cast<const float*>(Bm), T, ldb, static_cast<float*>(C), ldc);
-        return check_launch();
-    }
+    if (dtype == BIMASK_F32) return launch_gemm_f32(A_values, A_index, Adim, K, sparse24, Bm, T, ldb, nullptr, C, ldc, s);
     if (sparse24) {
         if (K <= 512) {
             // narrow weights: wavefront-private tiles; short contractions (below 256, or below 384 with more

@@ -127,6 +127,14 @@ def test_fp32_gemms_are_exact(N, M):
     exact_layer(136, 264, 300, N, M, synth.F32, 7500 + M)
 
 
+# 16 x 16 tiles; 4 / 8 / 16 wavefronts by contraction length and tile count; gather in the token loads or as a pass
+@pytest.mark.parametrize("I,J,T", [(8, 8, 5), (16, 136, 37), (40, 264, 70), (520, 24, 131), (264, 520, 1040), (24, 136, 16400)])
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
+@pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
+def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
+    exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
+
+
 def test_large_shapes_with_padded_leading_dimensions():
     """The 512 x 128 forward kernel and the row-interleaved gather of the backward pass on activations whose rows
     are longer than the matrices (ldx > J, lddy > I, ldy > I, lddx > J): the outputs must equal those of the
