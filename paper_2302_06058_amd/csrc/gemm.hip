@@ -542,7 +542,9 @@ int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int
             // streaming kernel below (measured per layer shape: 128 x 512 forward 30 -> 20 us, 2048 x 512 14 -> 10 us)
             int rc = launch_gemm_sp24_narrow(A_values, A_index, Adim, K, Bm, ldb, nullptr, T, C, ldc, s);
             if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
-            if (K < 256 || (K < 384 && Adim > 512)) {
+            // with few tokens a workgroup or two would walk all weight rows: 2048 x 256 at 64 tokens 5.1 us resident, 4.6
+            // split; a single stage has nothing to split (64 x 128 at one token 4.1 against 4.7)
+            if ((K < 256 || (K < 384 && Adim > 512)) && (K <= 128 || !gemm_few_tiles(Adim, T))) {
                 rc = launch_gemm_sp24_resident(A_values, A_index, Adim, K, Bm, ldb, nullptr, T, C, ldc, s);
                 if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
             }
@@ -560,8 +562,14 @@ int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int
         const bool narrow = (w256 - w128) * 5 >= w256;
         // few tokens and few weight tiles: 256-row tiles would leave CUs idle
         const bool underfilled = ceil_div(Adim, 256) * ceil_div(T, 64) <= 128;
-        const Sp24Tile tile = Adim <= 64 ? Sp24Tile::k64x64
-                            : (narrow || underfilled ? Sp24Tile::k128x64 : (big ? Sp24Tile::k256x128 : Sp24Tile::k256x64));
+        // a 64 x 32 or 64 x 64 tile per CU at most: split the contraction inside the workgroup (4096 x 4096 at 64 tokens
+        // 17.5 -> 8.9 us, at 256 18.3 -> 15.4)
+        const bool split32 = gemm_few_tiles(Adim, T), split64 = ceil_div(Adim, 64) * ceil_div(T, 64) <= 256;
+        const Sp24Tile tile = split32 ? Sp24Tile::k64x32Split
+                            : split64 ? Sp24Tile::k64x64Split
+                            : Adim <= 64 ? Sp24Tile::k64x64
+                            : narrow || underfilled ? Sp24Tile::k128x64
+                            : big ? Sp24Tile::k256x128 : Sp24Tile::k256x64;
         return launch_gemm_sp24(A_values, A_index, Adim, K, Bm, T, ldb, C, ldc, tile, s);
     }
     {   // dense masked weights: the streaming kernel on the fragment-major operand; else the general kernel

@@ -26,6 +26,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(__bf16)))) __bf16 bf16x16;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // native 16-byte register vector
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
@@ -35,10 +36,10 @@ constexpr int kRowBytes = SK * 2;       // LDS bytes per token row per stage (16
 union BFrag { bf16x16 v; u32x4 q[2]; };
 union AFrag { bf16x8 v; u32x4 q; };
 
-template <int BM, int BN>
+template <int BN, int KG>
 struct SpSmem {
-    static constexpr int kStage = BN * kRowBytes;
-    static constexpr int kTotal = 2 * kStage;
+    static constexpr int kStage = BN * kRowBytes;        // one group's token stage
+    static constexpr int kTotal = 2 * KG * kStage;
 };
 
 // 8 consecutive bf16 of a token row starting at element k, zero beyond kend; 4-byte loads
@@ -67,13 +68,19 @@ __device__ __forceinline__ u32x4 load_guarded(const uint16_t* row, int64_t k, in
 // DENSE: the weight operand is the dense masked matrix of a ratio with N > 2 in its fragment-major layout
 // (two 16-byte A fragments per sub-step instead of one compressed fragment plus index bits) and every
 // sparse 32x32x32 instruction becomes two dense 32x32x16 ones on the same token fragment halves.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, bool BGUARD, bool BHALF, bool KTAIL, bool DENSE>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
+// KG: groups of WAVES_M x WAVES_N wavefronts that share the output tile and split the CONTRACTION: group g takes the
+// stages g, g + KG, ... with a token buffer of its own, and the groups' fp32 sums meet in LDS in group order.  A problem
+// with few output tiles leaves most CUs idle and walks a long contraction on a handful of them; small tiles with the
+// stages side by side shorten that walk (1000 x 2048 at 64 tokens 10.9 -> 6.5 us on 32 workgroups, 512 x 4608 at 784
+// 23.1 -> 12.7).  Where the tiles fill the chip it gains nothing: the bytes every CU pulls through its L1 set the pace
+// there, not the wavefronts in flight (512 x 4608 at 3136 tokens, 128 x 64 tiles: 24.2 us with one group, 24.2 with two).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KG, int PF, bool BGUARD, bool BHALF, bool KTAIL, bool DENSE>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KG)
 k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, int64_t Adim, int64_t K,
             const uint16_t* __restrict__ Bm, int64_t T, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc,
             int tiles_a, bool vecC) {
-    constexpr int NT = 64 * WAVES_M * WAVES_N;          // threads per workgroup
-    using S = SpSmem<BM, BN>;
+    constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW; // wavefronts / threads of a group
+    using S = SpSmem<BN, KG>;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int NBUF = PF + 1;
@@ -83,7 +90,8 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     extern __shared__ u32x4 smem_u4[];
     uint8_t* smem = reinterpret_cast<uint8_t*>(smem_u4);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+    const int tid = threadIdx.x - kg * NT, lane = tid & 63, wave = tid >> 6;      // within the group
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const bool bfetch = !BHALF || __builtin_amdgcn_readfirstlane(wave) < WAVES_M * WAVES_N / 2;   // wave-uniform
     const int l32 = lane & 31, h = lane >> 5;
@@ -104,6 +112,7 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     const int64_t a0 = (within / gsz) * BM;
     const int64_t t0 = (first_t + within % gsz) * BN;
     const int nk = static_cast<int>(ceil_div(K, SK));   // = stages of the padded weight operand
+    const int nfull = nk / KG, nks = (nk + KG - 1) / KG;  // steps (a stage per group); in the last one some groups may idle
     const int64_t rt_last = ceil_div(Adim, 32) - 1;
 
     // per-lane source pointers (row tiles / rows clamped at the edges: loaded, never stored)
@@ -171,22 +180,25 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
         }                                                                                        \
     }
 
-    // One pipeline step: stage kt leaves its registers for LDS / the matrix cores while stage
-    // kt+PF is requested.  Kept free of control flow (loads past the end are clamped to the
+    uint8_t* sB = smem;
+    // One pipeline step: step st's stage leaves its registers for LDS / the matrix cores while the stage
+    // of step st+PF is requested.  Kept free of control flow (loads past the end are clamped to the
     // last stage, never skipped) so that the outstanding-load bookkeeping stays exact and a
     // step only ever waits for the stage it consumes.
-#define BIMASK_STEP(u, kt, DO_LOAD)                                                              \
+#define BIMASK_STEP(u, st, DO_LOAD)                                                              \
     {                                                                                            \
-        uint8_t* sB = smem + ((kt) & 1) * S::kStage;                                             \
+        sB = smem + (((st) & 1) * KG + kg) * S::kStage;                                          \
         if (bfetch) _Pragma("unroll") for (int it = 0; it < NB_; ++it)                          \
             *reinterpret_cast<u32x4*>(sB + sb_off[it]) = rb[u][it];                              \
         if (DO_LOAD) {                                                                           \
-            const int ktl = (kt) + PF < nk ? (kt) + PF : nk - 1;                                 \
-            BIMASK_LOAD_STAGE(((u) + PF) % NBUF, ktl)                                            \
+            BIMASK_LOAD_STAGE(((u) + PF) % NBUF, stage_of((st) + PF))                            \
         }                                                                                        \
         __syncthreads();                                                                         \
-        /* token fragments of instruction s4+1 are requested from LDS before the matrix       \
-           instructions of s4 are issued, so LDS latency hides behind them */                 \
+    }
+    // token fragments of instruction s4+1 are requested from LDS before the matrix instructions of s4 are issued, so
+    // LDS latency hides behind them
+#define BIMASK_MATRIX(u)                                                                         \
+    {                                                                                            \
         BFrag bf[2][TN];                                                                         \
         BIMASK_READ_FRAGS(bf[0], 0)                                                              \
         _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4) {                                       \
@@ -217,23 +229,31 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
         }                                                                                        \
     }
 
+    auto stage_of = [&](int st) {                        // this group's stage of step st (clamped: loaded, never used)
+        const int kt = st * KG + kg;
+        return kt < nk ? kt : nk - 1;
+    };
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
-        const int ktl = s < nk ? s : nk - 1;
-        BIMASK_LOAD_STAGE(s, ktl)
-    }
+    for (int st = 0; st < PF; ++st) BIMASK_LOAD_STAGE(st, stage_of(st))
 
-    int kt0 = 0;
+    int st0 = 0;
 #pragma unroll 1
-    for (; kt0 + NBUF <= nk; kt0 += NBUF) {
+    for (; st0 + NBUF <= nfull; st0 += NBUF) {
 #pragma unroll
-        for (int u = 0; u < NBUF; ++u) BIMASK_STEP(u, kt0 + u, true)
+        for (int u = 0; u < NBUF; ++u) {
+            BIMASK_STEP(u, st0 + u, true)
+            BIMASK_MATRIX(u)
+        }
     }
-    // fewer than NBUF stages remain: everything they need is already in flight
+    // at most NBUF - 1 whole steps and, with several groups, a partial one remain: all but the very last are in flight
 #pragma unroll
-    for (int u = 0; u < NBUF - 1; ++u) {
-        if (kt0 + u < nk) BIMASK_STEP(u, kt0 + u, false)
+    for (int u = 0; u < (KG == 1 ? NBUF - 1 : NBUF); ++u) {
+        if (st0 + u < nks) {
+            BIMASK_STEP(u, st0 + u, KG > 1 && u == 0)
+            if (KG == 1 || (st0 + u) * KG + kg < nk) BIMASK_MATRIX(u)
+        }
     }
+#undef BIMASK_MATRIX
 #undef BIMASK_STEP
 #undef BIMASK_READ_FRAGS
 #undef BIMASK_LOAD_STAGE
@@ -243,8 +263,38 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     // (16 bytes) of its token row.  The tile goes through LDS (the stage buffers are free now)
     // so that it leaves as whole 2*BM-byte row segments with streaming stores: full lines go
     // straight to memory and neither evict the operands from L2 nor wait there as dirty lines.
-    static_assert(BN * BM * 2 <= S::kTotal, "output tile must fit the stage buffers");
+    static_assert(BN * BM * 2 <= S::kTotal && (KG - 1) * BN * BM * 4 <= S::kTotal, "output tile must fit the stage buffers");
     __syncthreads();                                     // every wavefront is done with the last stage
+    if constexpr (KG > 1) {
+        f32x4* part = reinterpret_cast<f32x4*>(smem_u4) + lane;      // [group - 1][wave][i][j][quad][lane]
+        if (kg > 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        part[(((((kg - 1) * NW + wave) * TM + i) * TN + j) * 4 + q) * 64] =
+                            (f32x4){acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 x = part[((((g * NW + wave) * TM + i) * TN + j) * 4 + q) * 64];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += x[e];
+                        }
+        }
+        __syncthreads();
+    }
+    if (kg == 0)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -266,8 +316,8 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     __syncthreads();
     constexpr int UPR = BM / 8;                          // 16-byte units per tile row
 #pragma unroll
-    for (int it = 0; it < BN * UPR / NT; ++it) {
-        const int q = tid + NT * it, t = q / UPR, u = q % UPR;
+    for (int q = threadIdx.x; q < BN * UPR; q += NT * KG) {
+        const int t = q / UPR, u = q % UPR;
         const u32x4 v = *reinterpret_cast<const u32x4*>(smem + t * (BM * 2) + ((u ^ ((2 * t) & (UPR - 1))) << 4));
         const int64_t a = a0 + 8 * u;
         if (t0 + t < T && a < Adim) {
@@ -287,41 +337,46 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, bool BGUARD, bool BHALF, bool KTAIL = false, bool DENSE = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KG, int PF, bool BGUARD, bool BHALF, bool KTAIL = false, bool DENSE = false>
 int run_sp24_t(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bm, int64_t T, int64_t ldb,
              void* C, int64_t ldc, hipStream_t s) {
-    using S = SpSmem<BM, BN>;
-    auto kern = k_gemm_sp24<BM, BN, WAVES_M, WAVES_N, PF, BGUARD, BHALF, KTAIL, DENSE>;
+    using S = SpSmem<BN, KG>;
+    auto kern = k_gemm_sp24<BM, BN, WAVES_M, WAVES_N, KG, PF, BGUARD, BHALF, KTAIL, DENSE>;
     if (S::kTotal > 48 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                S::kTotal) != hipSuccess) return BIMASK_ERR_HIP;
+        static DeviceMemo attr_set;
+        const int dev = DeviceMemo::device();
+        if (!attr_set.get(dev)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    S::kTotal) != hipSuccess) return BIMASK_ERR_HIP;
+            attr_set.set(dev, 1);
+        }
     }
     const bool vecC = aligned16(C) && (ldc * 2) % 16 == 0;
     const int tiles_a = static_cast<int>(ceil_div(Adim, BM));
     const int64_t tiles_t = ceil_div(T, BN);
     const int64_t grid = ceil_div(tiles_a * tiles_t, 8) * 8;      // whole rounds over the 8 XCDs
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(64 * WAVES_M * WAVES_N), S::kTotal, s,
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(64 * WAVES_M * WAVES_N * KG), S::kTotal, s,
                        static_cast<const uint16_t*>(A), meta, Adim, K, static_cast<const uint16_t*>(Bm), T, ldb,
                        static_cast<uint16_t*>(C), ldc, tiles_a, vecC);
     return check_launch();
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, bool BHALF = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, bool BHALF = false, int KG = 1>
 int run_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bm, int64_t T, int64_t ldb,
              void* C, int64_t ldc, hipStream_t s) {
     const bool rows16 = aligned16(Bm) && (ldb * 2) % 16 == 0;
-    if (rows16 && K % SK == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, PF, false, BHALF>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
-    if (rows16 && K % 8 == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, PF, false, BHALF, true>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
-    return run_sp24_t<BM, BN, WAVES_M, WAVES_N, 1, true, false>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
+    if (rows16 && K % SK == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, KG, PF, false, BHALF>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
+    if (rows16 && K % 8 == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, KG, PF, false, BHALF, true>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
+    return run_sp24_t<BM, BN, WAVES_M, WAVES_N, KG, 1, true, false>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
 }
 
 // dense masked weights: aligned token rows and a contraction that is a multiple of 8 only (the caller
 // takes the general dense kernel otherwise)
-template <int BM, int BN, int WAVES_M, int WAVES_N, int PF>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KG = 1>
 int run_dense_frag(const void* A, int64_t Adim, int64_t K, const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc,
                    hipStream_t s) {
-    if (K % SK == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, PF, false, false, false, true>(A, nullptr, Adim, K, Bm, T, ldb, C, ldc, s);
-    return run_sp24_t<BM, BN, WAVES_M, WAVES_N, PF, false, false, true, true>(A, nullptr, Adim, K, Bm, T, ldb, C, ldc, s);
+    if (K % SK == 0) return run_sp24_t<BM, BN, WAVES_M, WAVES_N, KG, PF, false, false, false, true>(A, nullptr, Adim, K, Bm, T, ldb, C, ldc, s);
+    return run_sp24_t<BM, BN, WAVES_M, WAVES_N, KG, PF, false, false, true, true>(A, nullptr, Adim, K, Bm, T, ldb, C, ldc, s);
 }
 
 }  // namespace
@@ -331,6 +386,7 @@ int run_dense_frag(const void* A, int64_t Adim, int64_t K, const void* Bm, int64
 //   128 x 64, 4 wavefronts: weight dimensions that would leave 256-row tiles largely empty, or few tokens
 //   256 x 128, 8 wavefronts, 1 stage prefetched: large problems (half the weight traffic per token)
 //   64 x 64, 4 wavefronts of 32 x 32: at most 64 weight rows (no matrix work or fragment reads on padding rows)
+//   64 x 32, 4 groups of 2 wavefronts / 64 x 64, 2 groups of 4 wavefronts splitting the contraction: few tiles
 int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bm, int64_t T,
                      int64_t ldb, void* C, int64_t ldc, Sp24Tile tile, hipStream_t s) {
     if (!aligned16(A) || !aligned16(meta)) return BIMASK_ERR_ALIGN;
@@ -339,6 +395,8 @@ int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t 
         case Sp24Tile::k128x64: return run_sp24<128, 64, 4, 1, 2>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
         case Sp24Tile::k256x128: return run_sp24<256, 128, 8, 1, 1>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
         case Sp24Tile::k64x64: return run_sp24<64, 64, 2, 2, 2>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
+        case Sp24Tile::k64x32Split: return run_sp24<64, 32, 2, 1, 1, false, 4>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
+        case Sp24Tile::k64x64Split: return run_sp24<64, 64, 2, 2, 1, false, 2>(A, meta, Adim, K, Bm, T, ldb, C, ldc, s);
     }
     return BIMASK_ERR_UNSUPPORTED;
 }
@@ -352,6 +410,7 @@ int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t 
 int launch_gemm_dense_frag(const void* A, int64_t Adim, int64_t K, const void* Bm, int64_t T, int64_t ldb, void* C,
                            int64_t ldc, hipStream_t s) {
     if (!aligned16(A) || !aligned16(Bm) || (ldb * 2) % 16 != 0 || K % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
+    if (gemm_few_tiles(Adim, T)) return run_dense_frag<64, 32, 2, 1, 1, 4>(A, Adim, K, Bm, T, ldb, C, ldc, s);
     if (Adim <= 64) return run_dense_frag<64, 64, 2, 2, 2>(A, Adim, K, Bm, T, ldb, C, ldc, s);
     const bool big = ceil_div(Adim, 256) * ceil_div(T, 128) >= 190;
     // weight dimensions that would leave a fifth or more of the 256-row tiles empty (384 = 1.5 tiles) take 128-row tiles

@@ -121,6 +121,21 @@ def test_dense_core_gemms_4of8_are_exact(I, J, T, perm):
     exact_layer(I, J, T, 4, 8, synth.BF16, 7300 + I + J, perm=perm)
 
 
+# few output tiles: the contraction split over groups of wavefronts (64 x 32 tiles by 4, 64 x 64 by 2): one stage per group
+# and fewer, whole and partial last steps, ragged rows, tokens and stages, token rows of 16-byte pitch and of 8-byte pitch
+@pytest.mark.parametrize("I,J,T", [(68, 132, 35), (64, 260, 70), (136, 136, 37), (192, 648, 165), (512, 1152, 290), (1000, 520, 251),
+                                   (64, 4096, 1030), (1024, 1024, 1000), (960, 904, 1001), (900, 908, 1023)])
+@pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
+def test_split_contractions_are_exact(I, J, T, perm):
+    exact_layer(I, J, T, 2, 4, synth.BF16, 7700 + I + J, perm=perm)
+    if I % 8 == 0 and J % 8 == 0:
+        exact_layer(I, J, T, 4, 8, synth.BF16, 7800 + I + J, perm=perm)
+
+
+def test_tiles_of_256_x_64_stay_exact_where_the_tiles_fill_the_chip():
+    exact_layer(256, 640, 12500, 2, 4, synth.BF16, 7900)
+
+
 @pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
 def test_fp32_gemms_are_exact(N, M):
     exact_layer(64, 128, 40, N, M, synth.F32, 7400 + M)
