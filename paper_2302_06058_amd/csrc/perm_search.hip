@@ -10,8 +10,9 @@
 // eligible columns pop-counted.  Workgroups are numbered so that each XCD works on one slice
 // at a time: the slice then stays in that XCD's L2 for all K candidates and the mask is read
 // from HBM about once.  Partial scores per (slice, row range, candidate) go to scratch; a
-// second one-workgroup kernel sums them, takes the arg-max and copies the winning
-// permutation.  Integer only, no atomics: the result is bit-reproducible.
+// second small kernel sums them, takes the arg-max and copies the winning
+// permutation.  Large searches on unaligned masks and groups of many layers score from LDS instead (below).
+// Integers only: the result is bit-reproducible.
 #include <atomic>
 
 #include "common.hpp"
@@ -168,13 +169,15 @@ k_perm_score_group(const ScoreGroup g, int K, int N) {
 }
 
 // Sums the per-tile partial scores, takes the first arg-max and copies the winner.
-// One workgroup of 1024 threads: 128 candidates x 8 tile groups at a time, so every
+// `piece` of `pieces` workgroups: all of them find the winner (the partial sums are a few KB), each copies its share of
+// the permutation, the first one writes the scores.
+// A workgroup has 1024 threads: 128 candidates x 8 tile groups at a time, so every
 // thread issues its few independent loads at once instead of walking all tiles serially.
 constexpr int kFinalThreads = 1024;
 __device__ __forceinline__ void
 perm_final_body(const int32_t* __restrict__ partial, int ntiles, int K, int64_t I,
                 const int32_t* __restrict__ perms, int32_t* __restrict__ scores,
-                int32_t* __restrict__ best, int32_t* __restrict__ best_perm) {
+                int32_t* __restrict__ best, int32_t* __restrict__ best_perm, int64_t piece, int64_t pieces) {
     __shared__ int psum[8][128];
     __shared__ long long red[128];
     const int cl = threadIdx.x & 127, part = threadIdx.x >> 7;
@@ -198,7 +201,7 @@ perm_final_body(const int32_t* __restrict__ partial, int ntiles, int K, int64_t 
             int tot = 0;
 #pragma unroll
             for (int p = 0; p < 8; ++p) tot += psum[p][cl];
-            scores[c] = tot;
+            if (piece == 0) scores[c] = tot;
             // larger score first, then the smaller candidate index
             const long long key = (static_cast<long long>(tot) << 32) | static_cast<uint32_t>(0x7FFFFFFF - c);
             mine = key > mine ? key : mine;
@@ -215,10 +218,10 @@ perm_final_body(const int32_t* __restrict__ partial, int ntiles, int K, int64_t 
         __syncthreads();
     }
     const int bc = 0x7FFFFFFF - static_cast<int>(red[0] & 0xFFFFFFFFll);
-    if (threadIdx.x == 0) *best = bc;
+    if (piece == 0 && threadIdx.x == 0) *best = bc;
     if (best_perm) {
         const int32_t* P = perms + static_cast<int64_t>(bc) * I;
-        for (int64_t i = threadIdx.x; i < I; i += kFinalThreads) best_perm[i] = P[i];
+        for (int64_t i = piece * kFinalThreads + threadIdx.x; i < I; i += pieces * kFinalThreads) best_perm[i] = P[i];
     }
 }
 
@@ -226,7 +229,7 @@ __global__ void __launch_bounds__(kFinalThreads)
 k_perm_final(const int32_t* __restrict__ partial, int ntiles, int K, int64_t I,
              const int32_t* __restrict__ perms, int32_t* __restrict__ scores,
              int32_t* __restrict__ best, int32_t* __restrict__ best_perm) {
-    perm_final_body(partial, ntiles, K, I, perms, scores, best, best_perm);
+    perm_final_body(partial, ntiles, K, I, perms, scores, best, best_perm, blockIdx.x, gridDim.x);
 }
 
 struct FinalGroupP {
@@ -245,13 +248,285 @@ struct FinalGroup {
 __global__ void __launch_bounds__(kFinalThreads)
 k_perm_final_group(const FinalGroup g, int K) {
     const FinalGroupP& p = g.p[blockIdx.x];
-    perm_final_body(p.partial, p.ntiles, K, p.I, p.perms, p.scores, p.best, p.best_perm);
+    perm_final_body(p.partial, p.ntiles, K, p.I, p.perms, p.scores, p.best, p.best_perm, 0, 1);
+}
+
+// ---- scoring from LDS -------------------------------------------------------------------------------------------
+// With K candidates every mask row is read K times, and from L2 that is what the kernel above lives on: 564 MB for
+// 4096 x 11008 at K = 100, at 15 TB/s (the rate of its 16-byte gathers) 37 us.  Here a workgroup copies one column slice
+// of the mask -- ALL rows, 16 .. 128 bytes of each -- into LDS once and scores a range of candidates on it; L2 only
+// delivers the candidates themselves, once per slice.  The widest slice that fits is taken: neighbouring lanes then read
+// neighbouring chunks of a row (fewer bank conflicts between random rows), whole cache lines are copied, and the
+// candidates are read fewer times.  The slice is zero beyond column J, so that a column outside the matrix never counts
+// as "more than N": eligible columns = all columns of the slice - those.  The wavefronts share the (candidate, row-block
+// group) pairs of the workgroup evenly; sums meet in LDS (integers: any order).
+constexpr int kLdsThreads = 1024;
+constexpr int kLdsScoreBytes = 156 * 1024;               // slice; the candidates' sums (kLdsCands) follow
+constexpr int kLdsCands = 256;                           // candidates per workgroup at most
+
+// full adder; one three-input bit operation each
+__device__ __forceinline__ uint32_t add3(uint32_t a, uint32_t b, uint32_t c) { return a ^ b ^ c; }
+__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) { return (a & b) | (c & (a | b)); }
+
+// bit planes of the number of ones among 8 words
+__device__ __forceinline__ void planes8(const uint32_t* x, uint32_t (&p)[4]) {
+    const uint32_t s0 = add3(x[0], x[1], x[2]), c0 = maj3(x[0], x[1], x[2]);
+    const uint32_t s1 = add3(x[3], x[4], x[5]), c1 = maj3(x[3], x[4], x[5]);
+    const uint32_t s2 = add3(s0, s1, x[6]), c2 = maj3(s0, s1, x[6]);
+    const uint32_t c3 = s2 & x[7];
+    const uint32_t t = add3(c0, c1, c2), d = maj3(c0, c1, c2);
+    p[0] = s2 ^ x[7];
+    p[1] = t ^ c3;
+    p[2] = d ^ (t & c3);
+    p[3] = d & t & c3;
+}
+
+// columns (bits) whose M rows hold more than N ones
+template <int M, bool N2OF4>
+__device__ __forceinline__ uint32_t more_than_n(const uint32_t (&x)[M], int N) {
+    if constexpr (N2OF4) return (maj3(x[0], x[1], x[2]) & x[3]) | (x[0] & x[1] & x[2]);
+    uint32_t sp[Planes<M>::L];
+    if constexpr (M == 4) {
+        const uint32_t s0 = add3(x[0], x[1], x[2]), c0 = maj3(x[0], x[1], x[2]), c1 = s0 & x[3];
+        sp[0] = s0 ^ x[3]; sp[1] = c0 ^ c1; sp[2] = c0 & c1;
+    } else if constexpr (M == 8) {
+        planes8(x, sp);
+    } else {
+        uint32_t a[4], b[4];
+        planes8(x, a);
+        planes8(x + 8, b);
+        uint32_t carry = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) { sp[p] = add3(a[p], b[p], carry); carry = maj3(a[p], b[p], carry); }
+        sp[4] = carry;
+    }
+    uint32_t eq = 0xFFFFFFFFu, gt = 0;
+#pragma unroll
+    for (int p = Planes<M>::L - 1; p >= 0; --p) {
+        if ((N >> p) & 1) { eq &= sp[p]; }
+        else { gt |= eq & sp[p]; eq &= ~sp[p]; }
+    }
+    return gt;
+}
+
+// One layer's share: `block` = slice * groups + group; the group takes the candidates [group * cpg, ...).
+// sh: log2 of the 16-byte chunks per row of the slice.
+struct ScoreLdsP {
+    const uint32_t* B_bits;
+    const int32_t* perms;
+    int32_t* partial;
+    int64_t J;
+    int I, wpr32, sh, groups, cpg;
+};
+template <int M, bool N2OF4>
+__device__ __forceinline__ void perm_score_lds_body(const ScoreLdsP& p, int K, int N, int block) {
+    extern __shared__ u32x4 slice_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sh = p.sh, chl = 1 << sh, I = p.I;
+    const int slice = block / p.groups, c0 = (block - slice * p.groups) * p.cpg;
+    const int nc = p.cpg < K - c0 ? p.cpg : K - c0;
+    if (nc <= 0) return;                                 // whole workgroup
+    int* sum = reinterpret_cast<int*>(slice_lds + (static_cast<int64_t>(I) << sh));
+    const int wslice = slice * 4 * chl;                  // first mask word of the slice
+    const int64_t cols_left = p.J - static_cast<int64_t>(wslice) * 32;
+    const int ncols = static_cast<int>(cols_left < 128 * chl ? cols_left : 128 * chl);
+
+    // copy the slice: whole chunks of aligned rows as 16-byte loads, eight in flight per thread
+    const bool vec = p.wpr32 % 4 == 0 && (reinterpret_cast<uintptr_t>(p.B_bits) & 15u) == 0;
+    const int total = I << sh;
+    for (int q0 = tid; q0 < total; q0 += 8 * kLdsThreads) {
+        u32x4 v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int q = q0 + e * kLdsThreads;
+            v[e] = (u32x4){0u, 0u, 0u, 0u};
+            if (q < total) {
+                const int w0 = wslice + 4 * (q & (chl - 1));
+                const uint32_t* src = p.B_bits + static_cast<int64_t>(q >> sh) * p.wpr32 + w0;
+                if (vec) {
+                    if (w0 < p.wpr32) v[e] = *reinterpret_cast<const u32x4*>(src);
+                } else {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        if (w0 + w < p.wpr32) v[e][w] = src[w];
+                }
+                const int left = ncols - 128 * (q & (chl - 1));          // columns of this chunk that exist
+                if (left < 128) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const int n = left - 32 * w;
+                        v[e][w] &= n >= 32 ? 0xFFFFFFFFu : (n <= 0 ? 0u : (1u << n) - 1u);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (q0 + e * kLdsThreads < total) slice_lds[q0 + e * kLdsThreads] = v[e];
+    }
+    for (int c = tid; c < nc; c += kLdsThreads) sum[c] = 0;
+    __syncthreads();
+
+    // A wavefront walks over groups of D steps of one candidate each (64 >> sh row blocks a step); the candidate's entries
+    // for the next group are requested before this group is counted.
+    constexpr int D = M == 16 ? 2 : 4;
+    const int nblk = I / M, bps = 64 >> sh, groups = (nblk + D * bps - 1) / (D * bps);
+    const int all = nc * groups, per = (all + kLdsThreads / 64 - 1) / (kLdsThreads / 64);
+    int it = wave * per;
+    const int end = it + per < all ? it + per : all;
+    if (it < end) {
+        const int bl = lane >> sh;
+        const char* mine = reinterpret_cast<const char*>(slice_lds + (lane & (chl - 1)));
+        int c = it / groups, g = it - c * groups;
+        auto fetch = [&](int4 (&pe)[D][M / 4], int cc, int gg) {
+            const char* src = reinterpret_cast<const char*>(p.perms + static_cast<int64_t>(c0 + cc) * I);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                int b = (gg * D + d) * bps + bl;
+                b = b < nblk ? b : nblk - 1;             // clamped: read, counted as nothing
+#pragma unroll
+                for (int v = 0; v < M / 4; ++v) pe[d][v] = *reinterpret_cast<const int4*>(src + static_cast<uint32_t>(b) * (4 * M) + 16 * v);
+            }
+        };
+        int4 pe[D][M / 4];
+        fetch(pe, c, g);
+        int acc = 0;
+        for (; it < end; ++it) {
+            int4 cur[D][M / 4];
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+#pragma unroll
+                for (int v = 0; v < M / 4; ++v) cur[d][v] = pe[d][v];
+            const bool last = g + 1 == groups;           // of this candidate
+            const int cn = last ? (c + 1 < nc ? c + 1 : c) : c, gn = last ? 0 : g + 1;
+            fetch(pe, cn, gn);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                u32x4 x[M];
+#pragma unroll
+                for (int v = 0; v < M / 4; ++v) {
+                    x[4 * v + 0] = *reinterpret_cast<const u32x4*>(mine + (static_cast<uint32_t>(cur[d][v].x) << (sh + 4)));
+                    x[4 * v + 1] = *reinterpret_cast<const u32x4*>(mine + (static_cast<uint32_t>(cur[d][v].y) << (sh + 4)));
+                    x[4 * v + 2] = *reinterpret_cast<const u32x4*>(mine + (static_cast<uint32_t>(cur[d][v].z) << (sh + 4)));
+                    x[4 * v + 3] = *reinterpret_cast<const u32x4*>(mine + (static_cast<uint32_t>(cur[d][v].w) << (sh + 4)));
+                }
+                int cnt = 0;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t xw[M];
+#pragma unroll
+                    for (int m = 0; m < M; ++m) xw[m] = x[m][w];
+                    cnt += __popc(more_than_n<M, N2OF4>(xw, N));
+                }
+                acc += (g * D + d) * bps + bl < nblk ? cnt : 0;
+            }
+            if (last || it + 1 == end) {                 // wave-uniform: this candidate's sum leaves the registers
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+                if (lane == 0) atomicAdd(&sum[c], acc);
+                acc = 0;
+            }
+            c = last ? c + 1 : c;
+            g = gn;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < nc; i += kLdsThreads)
+        p.partial[static_cast<int64_t>(slice) * K + c0 + i] = ncols * nblk - sum[i];
+}
+
+template <int M, bool N2OF4>
+__global__ void __launch_bounds__(kLdsThreads)
+k_perm_score_lds(const ScoreLdsP p, int K, int N) { perm_score_lds_body<M, N2OF4>(p, K, N, static_cast<int>(blockIdx.x)); }
+
+constexpr int kLdsGroupCap = group_capacity(sizeof(ScoreLdsP));
+struct ScoreLdsGroup {
+    int n;
+    unsigned first[kLdsGroupCap + 1];
+    ScoreLdsP p[kLdsGroupCap];
+};
+template <int M, bool N2OF4>
+__global__ void __launch_bounds__(kLdsThreads)
+k_perm_score_lds_group(const ScoreLdsGroup g, int K, int N) {
+    int l = 0;
+    while (l + 1 < g.n && blockIdx.x >= g.first[l + 1]) ++l;
+    perm_score_lds_body<M, N2OF4>(g.p[l], K, N, static_cast<int>(blockIdx.x - g.first[l]));
+}
+
+struct LdsPlan {
+    int sh, nslices, steps;                              // steps of one candidate on one slice
+    size_t lds;
+};
+// A slice takes up to `slice_bytes`.  false: the search takes the L2 kernel (few candidates, which do not pay for the copy;
+// more rows than LDS holds at 16 bytes each; or more slices than the scratch has room for).
+bool plan_lds(int64_t I, int64_t J, int K, int M, size_t ws_bytes, int64_t slice_bytes, LdsPlan& pl) {
+    if (K < 16 || I * 16 > kLdsScoreBytes) return false;
+    int sh = 3;
+    while (sh > 0 && ((I << sh) * 16 > slice_bytes || (128ll << (sh - 1)) >= J)) --sh;
+    if (sh == 0 && J > 128) return false;                // 16 bytes of every line: the copy costs too much
+    pl.sh = sh;
+    pl.nslices = static_cast<int>(ceil_div(J, 128ll << sh));
+    pl.steps = static_cast<int>(round_up(ceil_div(I / M, 64 >> sh), M == 16 ? 2 : 4));
+    pl.lds = (static_cast<size_t>(I) << sh) * 16 + kLdsCands * sizeof(int32_t);
+    return static_cast<size_t>(pl.nslices) * static_cast<size_t>(K) * sizeof(int32_t) <= ws_bytes;
+}
+// A layer alone.  Where mask rows are whole cache lines the L2 kernel reaches 22-24 TB/s and the copy does not pay
+// (4096 x 4096 at K = 100 14.5 us from L2, 15.0 from LDS); where rows start inside lines every gather touches two, and
+// large searches gain: 4096 x 11008 37.8 -> 25.9 us, 4096 x 2304 17.2 -> 13.2, while 2048 x 2304 takes 11.3 / 11.2,
+// 1024 x 4608 10.3 / 10.9 and 4096 x 2304 with 32 candidates 9.6 / 11.1.  Rows that are not 16-byte aligned, read word by
+// word from L2, gain earlier (3072 x 1504 20.4 -> 13.7).
+bool alone_from_lds(int64_t I, int64_t J, int K) {
+    const int64_t words = ceil_div(J, 32);
+    return words % 32 != 0 && K >= 32 && I * J >= (words % 4 ? 300000000 : 600000000) / K;
+}
+// Layers of one group call.  The L2 kernel cuts every layer into thousands of wavefronts and the fixed costs of these add
+// up over the layers; the LDS launch costs a copy per workgroup once.  54 ResNet-50 matrices 45 -> 23 us, with 16
+// candidates 20.5 -> 15.6; 48 transformer matrices 38.6 -> 22, but 24 of them (2:8) 24.0 / 24.5 and 4 8.9 / 12.2.
+constexpr int kGroupFromLds = 32;
+// candidates of one slice cut into groups of `cpg`
+void cut_candidates(int K, int64_t groups, int& ngroups, int& cpg) {
+    const int64_t most = ceil_div(K, 4), least = ceil_div(K, kLdsCands);
+    groups = groups > most ? most : groups;
+    groups = groups < least ? least : groups;
+    cpg = static_cast<int>(ceil_div(K, groups));
+    ngroups = static_cast<int>(ceil_div(K, cpg));
+}
+template <typename Kern>
+bool allow_lds(Kern kern, DeviceMemo& memo) {
+    const int dev = DeviceMemo::device();
+    if (memo.get(dev)) return true;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kLdsScoreBytes + kLdsCands * static_cast<int>(sizeof(int32_t))) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    memo.set(dev, 1);
+    return true;
+}
+
+template <int M, bool N2OF4>
+int run_score_lds(const uint32_t* B_bits, int64_t I, int64_t J, int N, const int32_t* perms, int K, const LdsPlan& pl,
+                  int32_t* partial, hipStream_t s) {
+    static DeviceMemo memo;
+    auto kern = k_perm_score_lds<M, N2OF4>;
+    if (!allow_lds(kern, memo)) return BIMASK_ERR_HIP;
+    ScoreLdsP p{B_bits, perms, partial, J, static_cast<int>(I), static_cast<int>(ceil_div(J, 32)), pl.sh, 1, K};
+    cut_candidates(K, 256 / pl.nslices, p.groups, p.cpg);        // one workgroup per CU, one round where that is possible
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(pl.nslices * p.groups)), dim3(kLdsThreads), pl.lds, s, p, K, N);
+    return check_launch();
 }
 
 template <int M>
 int run_score(const uint32_t* B_bits, int64_t I, int64_t J, int N, const int32_t* perms, int K,
-              const PermPlan& pl, int32_t* partial, hipStream_t s) {
+              const PermPlan& pl, int32_t* partial, int& ntiles, hipStream_t s) {
     constexpr int U = M == 16 ? 1 : 2;
+    LdsPlan lp;
+    if (alone_from_lds(I, J, K) && plan_lds(I, J, K, M, pl.ws_bytes, kLdsScoreBytes, lp)) {
+        ntiles = lp.nslices;
+        if (M == 4 && N == 2) return run_score_lds<M, M == 4>(B_bits, I, J, N, perms, K, lp, partial, s);
+        return run_score_lds<M, false>(B_bits, I, J, N, perms, K, lp, partial, s);
+    }
+    ntiles = pl.ntiles;
     const int wpr32 = static_cast<int>(ceil_div(J, 32));
     const int64_t items = static_cast<int64_t>(pl.ntiles) * K;
     const unsigned grid = static_cast<unsigned>(round_up(ceil_div(items, kThreads / 64), 8));
@@ -327,6 +602,44 @@ int run_score_group(const bimask_group_layer* L, const int* which, int cnt, int 
     return check_launch();
 }
 
+// All layers that score from LDS, in one launch whatever the alignment of their rows (two workgroups per CU: half of LDS
+// each where a layer allows it).  54 ResNet-50 matrices at K = 100: 43 us in three launches of the L2 kernel, whose
+// wavefronts see two steps each in small layers, -> 21 us.
+template <int M>
+int run_score_lds_group(const bimask_group_layer* L, const int* which, const LdsPlan* plans, int cnt, int N, int K, hipStream_t s) {
+    static_assert(kLdsGroupCap >= kSearchGroupCap && sizeof(ScoreLdsGroup) <= 3840, "argument tables must fit the kernel arguments");
+    ScoreLdsGroup g{};
+    g.n = cnt;
+    // equal shares, a bit under one workgroup per CU over the layers together (54 ResNet-50 matrices at K = 100: 21 us
+    // with 192 shares, 23-24 with 128, 256 or 384), none below two groups of steps per wavefront
+    int64_t all = 0;
+    size_t lds = 0;
+    for (int l = 0; l < cnt; ++l) {
+        all += static_cast<int64_t>(plans[l].nslices) * K * plans[l].steps;
+        lds = plans[l].lds > lds ? plans[l].lds : lds;
+    }
+    const int64_t share = all / 192 > 128 ? all / 192 : 128;
+    unsigned blocks = 0;
+    for (int l = 0; l < cnt; ++l) {
+        const bimask_group_layer& a = L[which[l]];
+        ScoreLdsP& p = g.p[l];
+        p = ScoreLdsP{a.B_bits, a.perms, static_cast<int32_t*>(a.workspace), a.J, static_cast<int>(a.I),
+                      static_cast<int>(ceil_div(a.J, 32)), plans[l].sh, 1, K};
+        cut_candidates(K, ceil_div(static_cast<int64_t>(K) * plans[l].steps, share), p.groups, p.cpg);
+        g.first[l] = blocks;
+        blocks += static_cast<unsigned>(plans[l].nslices * p.groups);
+    }
+    g.first[cnt] = blocks;
+    auto launch = [&](auto kern, DeviceMemo& memo) {
+        if (!allow_lds(kern, memo)) return static_cast<int>(BIMASK_ERR_HIP);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kLdsThreads), lds, s, g, K, N);
+        return check_launch();
+    };
+    static DeviceMemo memo_2of4, memo_any;
+    if (M == 4 && N == 2) return launch(k_perm_score_lds_group<M, M == 4>, memo_2of4);
+    return launch(k_perm_score_lds_group<M, false>, memo_any);
+}
+
 }  // namespace
 
 // The searches of n independent layers (same N:M and number of candidates) in a few launches:
@@ -336,11 +649,31 @@ int launch_perm_search_group(const bimask_group_layer* L, int n, int N, int M, i
     static_assert(sizeof(FinalGroup) <= 3840 && sizeof(ScoreGroup) <= 3840, "argument tables must fit the kernel arguments");
     for (int b = 0; b < n; b += kSearchGroupCap) {
         const int m = n - b < kSearchGroupCap ? n - b : kSearchGroupCap;
+        int ntiles[kSearchGroupCap], from_lds[kSearchGroupCap], nl = 0;
+        LdsPlan plans[kSearchGroupCap];
+        for (int l = 0; l < m; ++l) {
+            const bimask_group_layer& a = L[b + l];
+            const PermPlan pl = plan_perm_search(a.I, a.J, K, M);
+            ntiles[l] = pl.ntiles;
+            if (plan_lds(a.I, a.J, K, M, pl.ws_bytes, kLdsScoreBytes / 2, plans[nl])) { ntiles[l] = plans[nl].nslices; from_lds[nl++] = b + l; }
+        }
+        if (nl < kGroupFromLds) {                        // few layers: all from L2
+            for (int l = 0; l < nl; ++l) { const bimask_group_layer& a = L[from_lds[l]]; ntiles[from_lds[l] - b] = plan_perm_search(a.I, a.J, K, M).ntiles; }
+            nl = 0;
+        }
+        if (nl) {
+            int rc = BIMASK_ERR_NM;
+            if (M == 4) rc = run_score_lds_group<4>(L, from_lds, plans, nl, N, K, s);
+            else if (M == 8) rc = run_score_lds_group<8>(L, from_lds, plans, nl, N, K, s);
+            else if (M == 16) rc = run_score_lds_group<16>(L, from_lds, plans, nl, N, K, s);
+            if (rc != BIMASK_OK) return rc;
+        }
         for (int cls = 0; cls < 4; ++cls) {              // (rows 16-byte aligned?, 8 or 32 chunks per slice)
             const bool vec = cls & 1;
             const int chunks = (cls & 2) ? 32 : 8;
             int which[kSearchGroupCap], cnt = 0;
-            for (int l = 0; l < m; ++l) {
+            for (int l = 0, skip = 0; l < m; ++l) {
+                if (skip < nl && from_lds[skip] == b + l) { ++skip; continue; }
                 const bimask_group_layer& a = L[b + l];
                 const bool v = aligned16(a.B_bits) && ceil_div(a.J, 32) % 4 == 0;
                 if (v == vec && plan_perm_search(a.I, a.J, K, M).chunks == chunks) which[cnt++] = b + l;
@@ -358,7 +691,7 @@ int launch_perm_search_group(const bimask_group_layer* L, int n, int N, int M, i
             FinalGroupP& p = f.p[l];
             p.partial = static_cast<const int32_t*>(a.workspace); p.perms = a.perms; p.scores = a.scores; p.best = a.best;
             p.best_perm = a.best_perm; p.I = a.I;
-            p.ntiles = plan_perm_search(a.I, a.J, K, M).ntiles;
+            p.ntiles = ntiles[l];
         }
         hipLaunchKernelGGL(k_perm_final_group, dim3(static_cast<unsigned>(m)), dim3(kFinalThreads), 0, s, f, K);
         if (int rc = check_launch()) return rc;
@@ -370,12 +703,14 @@ int launch_perm_search(const uint32_t* B_bits, int64_t I, int64_t J, int N, int 
                        int32_t* scores, int32_t* best, int32_t* best_perm, void* ws, hipStream_t s) {
     const PermPlan pl = plan_perm_search(I, J, K, M);
     int32_t* partial = static_cast<int32_t*>(ws);
-    int rc = BIMASK_ERR_NM;
-    if (M == 4) rc = run_score<4>(B_bits, I, J, N, perms, K, pl, partial, s);
-    else if (M == 8) rc = run_score<8>(B_bits, I, J, N, perms, K, pl, partial, s);
-    else if (M == 16) rc = run_score<16>(B_bits, I, J, N, perms, K, pl, partial, s);
+    int rc = BIMASK_ERR_NM, ntiles = 0;
+    if (M == 4) rc = run_score<4>(B_bits, I, J, N, perms, K, pl, partial, ntiles, s);
+    else if (M == 8) rc = run_score<8>(B_bits, I, J, N, perms, K, pl, partial, ntiles, s);
+    else if (M == 16) rc = run_score<16>(B_bits, I, J, N, perms, K, pl, partial, ntiles, s);
     if (rc != BIMASK_OK) return rc;
-    hipLaunchKernelGGL(k_perm_final, dim3(1), dim3(kFinalThreads), 0, s, partial, pl.ntiles, K, I, perms, scores, best,
+    // long permutations are copied by several workgroups (11008 rows: the whole search 32.1 -> 30.8 us)
+    const unsigned pieces = best_perm && I > 2 * kFinalThreads ? static_cast<unsigned>(I / (2 * kFinalThreads) < 16 ? I / (2 * kFinalThreads) : 16) : 1u;
+    hipLaunchKernelGGL(k_perm_final, dim3(pieces), dim3(kFinalThreads), 0, s, partial, ntiles, K, I, perms, scores, best,
                        best_perm);
     return check_launch();
 }

@@ -184,6 +184,56 @@ def test_perm_search_slice_paths(I, J, N, M):
     assert (best_perm.cpu().numpy() == perms[int(best.item())]).all()
 
 
+def random_mask(I, J, N, M, seed):
+    """(mask as 0/1, packed words on the device); any N-per-group mask will do for the search."""
+    rng = np.random.default_rng(seed)
+    g = np.argsort(rng.random((I, J // M, M)), axis=2) < N
+    Bo = g.reshape(I, J).astype(np.uint8)
+    wpr = (J + 31) // 32
+    bits = np.zeros((I, wpr * 32), dtype=np.uint8)
+    bits[:, :J] = Bo
+    w = (bits.reshape(I, wpr, 32).astype(np.uint64) << np.arange(32, dtype=np.uint64)).sum(axis=2).astype(np.uint32)
+    return Bo, i32_dev(w.view(np.int32))
+
+
+# searches that score from a column slice in LDS: rows of 16-byte and of 4-byte pitch, 2 / 4 / 8 chunks per row, ragged last
+# slices and row blocks, more candidates than one workgroup takes (256), a permutation copied by several workgroups
+@pytest.mark.parametrize("I,J,N,M,K", [(1028, 2052, 2, 4, 300), (1040, 2176, 2, 4, 300), (4992, 260, 2, 4, 310), (2600, 1100, 1, 4, 120),
+                                       (1208, 1256, 4, 8, 257), (1200, 1328, 3, 16, 261), (2100, 2180, 3, 4, 100)])
+def test_perm_search_from_lds(I, J, N, M, K):
+    Bo, B = random_mask(I, J, N, M, 900 + I)
+    perms = perms_of(I, K, 901 + I)
+    scores, best, best_perm = bm.bimask_perm_search(B, I, J, N, M, i32_dev(perms))
+    sc_o = oracle.perm_scores(Bo, perms, N, M)
+    assert (scores.cpu().numpy() == sc_o).all()
+    assert int(best.item()) == oracle.argmax_first(sc_o)
+    assert (best_perm.cpu().numpy() == perms[int(best.item())]).all()
+
+
+@pytest.mark.parametrize("N,M,K", [(2, 4, 16), (1, 4, 19), (4, 8, 23), (2, 16, 17)])
+def test_group_search_from_lds(N, M, K):
+    """32 layers and more in one group call score from LDS; two of these are too tall for it and stay with the other kernel."""
+    import torch
+    shapes = [(M * (1 + 3 * (i % 12)), M * (2 + 5 * (i % 9))) for i in range(30)]
+    shapes += [(2400, 144), (528, 2064), (1008, 1040), (64, 64 * M), (4096, 160), (16 * 313, 256)]
+    entries, refs = [], []
+    for li, (I, J) in enumerate(shapes):
+        Bo, B = random_mask(I, J, N, M, 950 + li)
+        perms = perms_of(I, K, 990 + li)
+        i32 = lambda n: torch.full((n,), 0x55, dtype=torch.int32, device=B.device)
+        ws = torch.empty((max(16, bm.workspace_bytes(bm.WS_PERM_SEARCH, I, J, 0, K, bm.BF16, N, M)),), dtype=torch.uint8, device=B.device)
+        W = torch.empty((I, J), dtype=torch.bfloat16, device=B.device)
+        entries.append(dict(W=W, B_bits=B, perms=i32_dev(perms), scores=i32(K), best=i32(1), best_perm=i32(I), workspace=ws))
+        refs.append((perms, oracle.perm_scores(Bo, perms, N, M)))
+    layers = bm.group_layers(entries)
+    bm.bimask_perm_search_group(layers, N, M, K)
+    torch.cuda.synchronize()
+    for e, (perms, sc), shape in zip(entries, refs, shapes):
+        b = oracle.argmax_first(sc)
+        assert (e["scores"].cpu().numpy() == sc).all() and int(e["best"].item()) == b, shape
+        assert (e["best_perm"].cpu().numpy() == perms[b]).all(), shape
+
+
 def test_duplicate_candidates_pick_the_first():
     I, J, N, M = 64, 128, 2, 4
     Wh = make_w(I, J, synth.BF16, 501)
