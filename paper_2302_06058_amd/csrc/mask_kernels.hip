@@ -384,7 +384,9 @@ k_forward24_group(const GroupTable<FwdGroupP> g, int N) {
 // ---------------------------------------------------------------------------------
 // Backward direction: a workgroup owns a tile of 128 permuted rows x TC columns (TC = 128,
 // or 32 for small matrices so that enough workgroups exist); a thread owns one block of M
-// permuted rows x 8 columns.  Rows of W are gathered through P, every row read is a
+// permuted rows x QC columns: 8, or 2 in the 32-column tiles.  A small matrix is bound by the serial
+// selection of one thread, not by bytes: with 8 columns a 128 x 32 tile kept 64 (M = 8) or 128 (M = 4) of
+// its 256 threads busy.  1536 x 384 at 4:8 13.0 -> 7.4 us, 64 x 128 in fp32 6.9 -> 5.0 us.  Rows of W are gathered through P, every row read is a
 // contiguous 2*TC-byte (bf16) segment.  Transposed outputs go through LDS so
 // that they leave as contiguous runs along the permuted-row axis.
 //   MODE 0: Bbar only   1: + transposed 2-of-4 values/index (N <= 2)   2: + transposed dense masked
@@ -395,6 +397,21 @@ constexpr int kTR = 128;   // permuted rows per tile = one 128-deep stage of the
 // mode 1: fragment-major image of TC output rows x 64 slots (2048 elements per 32 output rows)
 template <int TC> __host__ __device__ constexpr int img_elems() { return TC / 32 * 2048; }
 template <typename DT> __host__ __device__ constexpr int lds_stride_m2() { return kTR + 16 / (int)sizeof(typename DT::raw); }
+
+// two neighbouring entries of a row (vec: the row starts 16-byte aligned, and the first index is even)
+template <typename DT>
+__device__ __forceinline__ void load2(const typename DT::raw* p, bool vec, uint32_t (&w)[Pack<DT>::kWords]) {
+    if constexpr (sizeof(typename DT::raw) == 2) {
+        w[0] = vec ? *reinterpret_cast<const uint32_t*>(p) : static_cast<uint32_t>(p[0]) | static_cast<uint32_t>(p[1]) << 16;
+    } else {
+        if (vec) {
+            const uint2 v = *reinterpret_cast<const uint2*>(p);
+            w[0] = v.x; w[1] = v.y;
+        } else {
+            w[0] = p[0]; w[1] = p[1];
+        }
+    }
+}
 
 template <typename DT, int M, int TC>
 __device__ __forceinline__ void
@@ -409,13 +426,15 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
     extern __shared__ uint4 lds_u4[];
     raw* lds_val = reinterpret_cast<raw*>(lds_u4);
     constexpr int S2 = lds_stride_m2<DT>();
-    constexpr int CPT = TC / 8;                         // 8-column chunks per tile row
+    constexpr int QC = TC == 32 ? 2 : 8;                // columns per thread
+    constexpr int CPT = TC / QC;                        // column chunks per tile row
     uint8_t* lds_meta = reinterpret_cast<uint8_t*>(lds_val + img_elems<TC>());  // mode 1 only: [TC][32] nibbles
 
     const int64_t r0 = static_cast<int64_t>(block_y) * kTR;
     const int64_t c0 = static_cast<int64_t>(block_x) * TC;
     const int ch = threadIdx.x % CPT;
-    const int64_t j0 = c0 + ch * 8;
+    const int64_t j0 = c0 + ch * QC;                    // J is a multiple of 4: two columns are both in or both out
+    const int sh = QC == 8 ? 0 : static_cast<int>(j0 & 7);               // their place in the mask byte
 
     if (mode == 1) {                                    // padding of the operand image is zero
         constexpr int kZeroWords = (img_elems<TC>() * (int)sizeof(raw) + TC * 32) / 16;
@@ -430,72 +449,85 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
     for (int kb = threadIdx.x / CPT; kb < NB; kb += kThreads / CPT) {
         const int64_t rb = r0 + static_cast<int64_t>(kb) * M;
         if (rb >= I) continue;
-        if (j0 >= J) {                                   // pad bytes of the last mask word stay zero
-            if (Bbar_bits && j0 < static_cast<int64_t>(wpr) * 32) {
-#pragma unroll
-                for (int m = 0; m < M; ++m)
-                    reinterpret_cast<uint8_t*>(Bbar_bits)[(rb + m) * wpr * 4 + (j0 >> 3)] = 0;
-            }
-            continue;
-        }
-        uint32_t w[M][PW];
-        uint32_t bb[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int64_t src = perm ? static_cast<int64_t>(perm[rb + m]) : rb + m;
-            load8<DT>(W + src * ldw, j0, J, vec_in, w[m]);
-            bb[m] = Bbar_in ? reinterpret_cast<const uint8_t*>(Bbar_in)[(rb + m) * wpr * 4 + (j0 >> 3)]
-                            : reinterpret_cast<const uint8_t*>(B_bits)[src * wpr * 4 + (j0 >> 3)];
-        }
         uint32_t ob[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) ob[m] = 0;
+        for (int m = 0; m < M; ++m) ob[m] = 0;           // pad bits of the last mask word stay zero
+        uint32_t w[M][PW];
+        uint32_t bb[M];
+        if (j0 < J) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            uint32_t colbits = 0;                       // mask bits of this column block
-#pragma unroll
-            for (int m = 0; m < M; ++m) colbits |= ((bb[m] >> q) & 1u) << m;
-            uint32_t sel;
-            if (Bbar_in) {
-                sel = complete_slots<M>(colbits, N);
-            } else {
-                uint32_t key[M];
-#pragma unroll
-                for (int m = 0; m < M; ++m) key[m] = ((colbits >> m) & 1u) ? (elem<DT>(w[m], q) & DT::kAbs) : 0u;
-                sel = select_top_n<M>(key, N);
+            for (int m = 0; m < M; ++m) {
+                const int64_t src = perm ? static_cast<int64_t>(perm[rb + m]) : rb + m;
+                if constexpr (QC == 8) load8<DT>(W + src * ldw, j0, J, vec_in, w[m]);
+                else load2<DT>(W + src * ldw + j0, vec_in, w[m]);
+                bb[m] = (Bbar_in ? reinterpret_cast<const uint8_t*>(Bbar_in)[(rb + m) * wpr * 4 + (j0 >> 3)]
+                                 : reinterpret_cast<const uint8_t*>(B_bits)[src * wpr * 4 + (j0 >> 3)]) >> sh;
             }
-            const uint32_t keep = Bbar_in ? colbits : (sel & colbits);
 #pragma unroll
-            for (int m = 0; m < M; ++m) ob[m] |= ((keep >> m) & 1u) << q;
-            const int col = ch * 8 + q;
-            if (c0 + col >= J) continue;                 // ragged last chunk: not a row of the operand
-            if (mode == 1) {
-                // N <= 2: every aligned group of 4 permuted rows keeps at most two entries; its slots
-                // are the kept positions completed with the lowest-index other positions
+            for (int q = 0; q < QC; ++q) {
+                uint32_t colbits = 0;                       // mask bits of this column block
 #pragma unroll
-                for (int sg = 0; sg < M / 4; ++sg) {
-                    const uint32_t k4 = (keep >> (4 * sg)) & 15u;
-                    const uint32_t sl = complete_slots<4>(k4, 2);
-                    const int p0 = __builtin_ctz(sl), p1 = 31 - __builtin_clz(sl);
-                    const uint32_t e0 = elem<DT>(w[4 * sg + 0], q), e1 = elem<DT>(w[4 * sg + 1], q),
-                                   e2 = elem<DT>(w[4 * sg + 2], q), e3 = elem<DT>(w[4 * sg + 3], q);
-                    const uint32_t v0 = ((k4 >> p0) & 1u) ? pick4(e0, e1, e2, e3, p0) : 0u;
-                    const uint32_t v1 = ((k4 >> p1) & 1u) ? pick4(e0, e1, e2, e3, p1) : 0u;
-                    // output row = this column, group g4 of the stage's 32: lane half g4/16,
-                    // instruction (g4%16)/4, elements 2(g4%4), 2(g4%4)+1
-                    const int g4 = kb * (M / 4) + sg;
-                    raw* d = lds_val + (((col >> 5) * 4 + ((g4 & 15) >> 2)) * 64 + (col & 31) + 32 * (g4 >> 4)) * 8 + 2 * (g4 & 3);
-                    if constexpr (sizeof(raw) == 2) *reinterpret_cast<uint32_t*>(d) = v0 | (v1 << 16);
-                    else *reinterpret_cast<uint2*>(d) = make_uint2(v0, v1);
-                    lds_meta[col * 32 + g4] = static_cast<uint8_t>(p0 | (p1 << 2));
+                for (int m = 0; m < M; ++m) colbits |= ((bb[m] >> q) & 1u) << m;
+                uint32_t sel;
+                if (Bbar_in) {
+                    sel = complete_slots<M>(colbits, N);
+                } else {
+                    uint32_t key[M];
+#pragma unroll
+                    for (int m = 0; m < M; ++m) key[m] = ((colbits >> m) & 1u) ? (elem<DT>(w[m], q) & DT::kAbs) : 0u;
+                    sel = select_top_n<M>(key, N);
                 }
-            } else if (mode == 2) {
+                const uint32_t keep = Bbar_in ? colbits : (sel & colbits);
 #pragma unroll
-                for (int m = 0; m < M; ++m)
-                    lds_val[col * S2 + kb * M + m] = static_cast<raw>(((keep >> m) & 1u) ? elem<DT>(w[m], q) : 0u);
+                for (int m = 0; m < M; ++m) ob[m] |= ((keep >> m) & 1u) << q;
+                const int col = ch * QC + q;
+                if (c0 + col >= J) continue;                 // ragged last chunk: not a row of the operand
+                if (mode == 1) {
+                    // N <= 2: every aligned group of 4 permuted rows keeps at most two entries; its slots
+                    // are the kept positions completed with the lowest-index other positions
+#pragma unroll
+                    for (int sg = 0; sg < M / 4; ++sg) {
+                        const uint32_t k4 = (keep >> (4 * sg)) & 15u;
+                        const uint32_t sl = complete_slots<4>(k4, 2);
+                        const int p0 = __builtin_ctz(sl), p1 = 31 - __builtin_clz(sl);
+                        const uint32_t e0 = elem<DT>(w[4 * sg + 0], q), e1 = elem<DT>(w[4 * sg + 1], q),
+                                       e2 = elem<DT>(w[4 * sg + 2], q), e3 = elem<DT>(w[4 * sg + 3], q);
+                        const uint32_t v0 = ((k4 >> p0) & 1u) ? pick4(e0, e1, e2, e3, p0) : 0u;
+                        const uint32_t v1 = ((k4 >> p1) & 1u) ? pick4(e0, e1, e2, e3, p1) : 0u;
+                        // output row = this column, group g4 of the stage's 32: lane half g4/16,
+                        // instruction (g4%16)/4, elements 2(g4%4), 2(g4%4)+1
+                        const int g4 = kb * (M / 4) + sg;
+                        raw* d = lds_val + (((col >> 5) * 4 + ((g4 & 15) >> 2)) * 64 + (col & 31) + 32 * (g4 >> 4)) * 8 + 2 * (g4 & 3);
+                        if constexpr (sizeof(raw) == 2) *reinterpret_cast<uint32_t*>(d) = v0 | (v1 << 16);
+                        else *reinterpret_cast<uint2*>(d) = make_uint2(v0, v1);
+                        lds_meta[col * 32 + g4] = static_cast<uint8_t>(p0 | (p1 << 2));
+                    }
+                } else if (mode == 2) {
+                    // the block's M entries are contiguous and start on 8 bytes at least
+                    constexpr int MW = M * (int)sizeof(raw) / 4, PER = 4 / (int)sizeof(raw);
+                    uint32_t pk[MW];
+#pragma unroll
+                    for (int d = 0; d < MW; ++d) {
+                        pk[d] = 0;
+#pragma unroll
+                        for (int e = 0; e < PER; ++e)
+                            pk[d] |= (((keep >> (d * PER + e)) & 1u) ? elem<DT>(w[d * PER + e], q) : 0u) << (16 * e);
+                    }
+                    raw* d = lds_val + col * S2 + kb * M;
+#pragma unroll
+                    for (int x = 0; x < MW; x += 2) reinterpret_cast<uint2*>(d)[x / 2] = make_uint2(pk[x], pk[x + 1]);
+                }
             }
         }
-        if (Bbar_bits) {
+        if constexpr (QC == 2) {                         // four neighbouring lanes share a mask byte (same kb, all here)
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                ob[m] <<= sh;
+                ob[m] |= __shfl_xor(ob[m], 1);
+                ob[m] |= __shfl_xor(ob[m], 2);
+            }
+        }
+        if (Bbar_bits && sh == 0 && j0 < static_cast<int64_t>(wpr) * 32) {
 #pragma unroll
             for (int m = 0; m < M; ++m)
                 reinterpret_cast<uint8_t*>(Bbar_bits)[(rb + m) * wpr * 4 + (j0 >> 3)] = static_cast<uint8_t>(ob[m]);

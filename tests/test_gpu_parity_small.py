@@ -5,6 +5,7 @@ GEMM outputs within 2e-2 (bf16 in, fp32 accumulate) / 1e-5 (fp32) of the float64
 oracle in max|err| / max|ref|."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2302_06058_amd as bm
@@ -148,6 +149,24 @@ def test_small_layers_all_calls(dtype, N, M):
 def test_adversarial_values(dtype, kind):
     for (N, M) in [(2, 4), (4, 8)]:
         check_layer(I=64, J=160, N=N, M=M, dtype=dtype, K=5, seed=300 + N, kind=kind, T=33)
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (1, 16), (7, 16)])
+def test_backward_column_pairs(dtype, N, M):
+    # two columns per thread, a mask byte put together by four lanes: every remainder of J in a mask byte and word,
+    # one row block beyond a tile of 128, rows that start on an odd element (no vector loads)
+    for J in (M, 32 + M, 96 - M):
+        check_layer(I=128 + M, J=J, N=N, M=M, dtype=dtype, K=2, seed=430 + M + J, kind="integers" if J == M else "normal")
+        W = to_dev(make_w(128 + M, J, dtype, 440 + J), dtype)
+        wide = torch.zeros((128 + M, J + 3), dtype=W.dtype, device=W.device)
+        wide[:, 1:J + 1] = W
+        P = i32_dev(perms_of(128 + M, 1, 441))[0]
+        B = bm.bimask_forward_mask(W, N, M)
+        a = bm.bimask_backward_mask_compress(W, N, M, B, P)
+        b = bm.bimask_backward_mask_compress(wide[:, 1:J + 1], N, M, B, P)
+        for x, y in zip(a, b):
+            assert (x is None and y is None) or torch.equal(x, y), (N, M, J)
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
