@@ -9,7 +9,7 @@
 // elements) and read a third time by the GEMM.  Here a workgroup keeps up to 32 WHOLE rows of
 // g(Y) in LDS: they arrive as contiguous 16-byte pieces and are scattered to their permuted
 // positions with 2-byte LDS stores (the inverse permutation sits in LDS), so the gather costs
-// no memory traffic at all.  The four wavefronts then walk over the weight-row tiles (64
+// no memory traffic at all.  The four wavefronts then walk over the weight-row tiles (32-96
 // rows per pass, at most two passes each), streaming the fragment-major compressed weights
 // from L2 two stages ahead and reading every token fragment with two 8-byte LDS loads
 // (row pitch = 2 I + 8 bytes: 32 lanes hit 64 distinct banks).  The output tile is regrouped
@@ -31,16 +31,18 @@ union AFragW { bf16x8 v; u32x4 q; };
 constexpr int kRowResThreads = 256;
 
 // TM weight-row tiles (32 rows each) per wavefront pass, NP passes per wavefront: 4 wavefronts cover
-// 4 * NP * TM * 32 weight rows (256 / 384 / 512 for <2,1> / <3,1> / <2,2>)
+// 4 * NP * TM * 32 weight rows (128 / 256 / 384 / 512 for <1,1> / <2,1> / <3,1> / <2,2>)
 // DENSE: the weight operand is the dense masked matrix of a ratio with N > 2 (fragment-major): two 16-byte
-// fragments per sub-step and two dense 32x32x16 instructions instead of one sparse 32x32x32; one stage ahead.
+// fragments per sub-step and two dense 32x32x16 instructions instead of one sparse 32x32x32; a step is then 64
+// contraction indices instead of 128, so that both formats keep the same number of fragments in flight.
 template <int TM, int NP, bool DENSE>
 __global__ void __launch_bounds__(kRowResThreads, 2)
 k_gemm_sp24_rowres(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, int Adim, int K,
                    const uint16_t* __restrict__ Bsrc, int64_t ldb, const int32_t* __restrict__ perm, int64_t T,
                    uint16_t* __restrict__ C, int64_t ldc, int rpt, bool stream_out) {
-    constexpr int PF = DENSE ? 1 : 2, NBUF = PF + 1;     // weight stages in flight beyond the current one
-    constexpr int NA = DENSE ? 8 : 4;                    // 16-byte weight fragments per row tile and stage
+    constexpr int PF = 2, NBUF = PF + 1;                 // weight steps in flight beyond the current one
+    constexpr int NA = 4;                                // 16-byte weight fragments per row tile and step
+    constexpr int SUB = DENSE ? 2 : 4;                   // sub-steps (32 contraction indices) of a step
     extern __shared__ u32x4 smem_u4[];
     uint8_t* smem = reinterpret_cast<uint8_t*>(smem_u4);
     uint16_t* sInv = reinterpret_cast<uint16_t*>(smem);                  // position of column c in a permuted row
@@ -50,7 +52,8 @@ k_gemm_sp24_rowres(const uint16_t* __restrict__ A, const uint32_t* __restrict__ 
     const int l32 = lane & 31, h = lane >> 5;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * rpt;
     const int rows = static_cast<int>((T - t0) < rpt ? (T - t0) : rpt);
-    const int nks = (K + 127) >> 7;                                      // stages of the padded weight operand
+    const int nks = (K + 127) >> 7;                                      // 128-deep stages of the padded weight operand
+    const int nst = DENSE ? 2 * nks : nks;                               // steps
     const bool Kfull = (K & 127) == 0;
 
     // ---- weight fragments of this wavefront's first pass: requested before anything else, they do
@@ -80,7 +83,7 @@ k_gemm_sp24_rowres(const uint16_t* __restrict__ A, const uint32_t* __restrict__ 
             pm[i] = DENSE ? nullptr : Ameta + (static_cast<int64_t>(rt) * nks * 64 + lane) * 2;  \
         }                                                                                        \
         _Pragma("unroll") for (int s = 0; s < PF; ++s) {                                         \
-            const int stl = s < nks ? s : nks - 1;                                               \
+            const int stl = s < nst ? s : nst - 1;                                               \
             BIMASK_RR_LOAD(s, stl)                                                               \
         }                                                                                        \
     }
@@ -145,18 +148,19 @@ k_gemm_sp24_rowres(const uint16_t* __restrict__ A, const uint32_t* __restrict__ 
         const int rt0 = rtb + (wave + 4 * ps) * TM;                      // first row tile of this pass
         if (rt0 >= ntr) break;                                           // wave-uniform
         if (ps > 0) BIMASK_RR_SETUP(ps)
-        // one stage = 128 contraction indices: 4 x TM sparse matrix instructions; loads past the
-        // last stage are clamped to it (never skipped: the number in flight is known at every wait)
+        // one step: SUB x TM sparse (or 2 SUB x TM dense) matrix instructions; loads past the last step are clamped
+        // to it (never skipped: the number in flight is known at every wait)
 #define BIMASK_RR_STEP(u, st, DO_LOAD)                                                           \
         {                                                                                        \
             if (DO_LOAD) {                                                                       \
-                const int stl = (st) + PF < nks ? (st) + PF : nks - 1;                           \
+                const int stl = (st) + PF < nst ? (st) + PF : nst - 1;                           \
                 BIMASK_RR_LOAD(((u) + PF) % NBUF, stl)                                           \
             }                                                                                    \
-            _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4) {                                   \
+            _Pragma("unroll") for (int s4 = 0; s4 < SUB; ++s4) {                                 \
                 BFragW bf;                                                                       \
                 _Pragma("unroll") for (int x = 0; x < 2; ++x) {                                  \
-                    const int k0 = 8 * ((st) * 16 + 8 * x + 2 * s4 + h);                         \
+                    const int k0 = DENSE ? 8 * (((st) >> 1) * 16 + 8 * x + 2 * (2 * ((st) & 1) + s4) + h) \
+                                         : 8 * ((st) * 16 + 8 * x + 2 * s4 + h);                 \
                     const u32x2* p = reinterpret_cast<const u32x2*>(myrow + 2 * k0);             \
                     const u32x2 lo = p[0], hi = p[1];                                            \
                     u32x4 o = {lo.x, lo.y, hi.x, hi.y};                                          \
@@ -188,13 +192,13 @@ k_gemm_sp24_rowres(const uint16_t* __restrict__ A, const uint32_t* __restrict__ 
         }
         int st0 = 0;
 #pragma unroll 1
-        for (; st0 + NBUF <= nks; st0 += NBUF) {
+        for (; st0 + NBUF <= nst; st0 += NBUF) {
 #pragma unroll
             for (int u = 0; u < NBUF; ++u) BIMASK_RR_STEP(u, st0 + u, true)
         }
 #pragma unroll
         for (int u = 0; u < NBUF - 1; ++u) {
-            if (st0 + u < nks) BIMASK_RR_STEP(u, st0 + u, false)
+            if (st0 + u < nst) BIMASK_RR_STEP(u, st0 + u, false)
         }
 #undef BIMASK_RR_STEP
     }
@@ -302,10 +306,17 @@ int launch_gemm_sp24_rowres(const void* A, const uint32_t* meta, int64_t Adim, i
                            static_cast<int>(Adim), static_cast<int>(K), static_cast<const uint16_t*>(Bsrc), ldb, perm, T, \
                            static_cast<uint16_t*>(C), ldc, best_rpt, stream_out);                            \
     }
+    // The fewest row tiles per wavefront that cover the operand: with more, some wavefronts have none (128 rows at 2 per
+    // wavefront: two of four; 384 at 2 x 2 passes: two take twice the others' share).  Backward, before -> now:
+    // 512 x 128 at 50176 tokens 25.6 -> 19.8 us, 4:8 256 x 128 at 50176 19.1 -> 13.6, 4:8 1536 x 384 at 25216 71.3 -> 65.3,
+    // 4:8 1000 x 296 at 20000 43.5 -> 36.2.
     if (dense) {
-        if (Adim <= 256) BIMASK_ROWRES(2, 1, true)
+        if (Adim <= 128) BIMASK_ROWRES(1, 1, true)
+        else if (Adim <= 256) BIMASK_ROWRES(2, 1, true)
+        else if (Adim <= 384) BIMASK_ROWRES(3, 1, true)
         else BIMASK_ROWRES(2, 2, true)
-    } else if (Adim <= 256 || split) BIMASK_ROWRES(2, 1, false)
+    } else if (Adim <= 128) BIMASK_ROWRES(1, 1, false)
+    else if (Adim <= 256 || split) BIMASK_ROWRES(2, 1, false)
     else if (Adim <= 384) BIMASK_ROWRES(3, 1, false)
     else BIMASK_ROWRES(2, 2, false)
 #undef BIMASK_ROWRES

@@ -169,6 +169,14 @@ def test_backward_column_pairs(dtype, N, M):
             assert (x is None and y is None) or torch.equal(x, y), (N, M, J)
 
 
+@pytest.mark.parametrize("I,J,N,M", [(136, 128, 4, 8), (520, 8, 4, 8), (264, 136, 3, 8), (392, 264, 4, 8), (640, 384, 4, 8), (1000, 392, 4, 8),
+                                     (520, 32, 2, 4), (520, 128, 2, 4), (776, 136, 2, 4)])
+def test_row_resident_backward_row_tiles(I, J, N, M):
+    # weight rows per wavefront 32 / 64 / 96 / 128: the last row tile partly and wholly filled, contractions that end
+    # inside either half of a 128-deep stage, one row of tokens beyond a tile
+    check_layer(I=I, J=J, N=N, M=M, dtype=synth.BF16, K=1, seed=450 + J, T=33)
+
+
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_degenerate_shapes(dtype):
     check_layer(I=4, J=4, N=2, M=4, dtype=dtype, K=1, seed=401, T=1)          # one group, one block
