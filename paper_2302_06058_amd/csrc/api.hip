@@ -238,6 +238,10 @@ int bimask_sparse_gemm_bwd(const void* dY, int64_t T, int64_t lddy, const int32_
         if (!aligned16(workspace)) return BIMASK_ERR_ALIGN;
         if (dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
             return launch_gemm_f32(Wb_values, Wb_index, J, I, sp, dY, T, lddy, perm, dX, lddx, as_stream(stream));
+        if (dtype == BIMASK_BF16 && !sp && gemm_dense_unpermutes(dY, T, lddy, J, I)) {
+            if (int rc = launch_unpermute_dense(Wb_values, J, I, perm, workspace, as_stream(stream))) return rc;
+            return launch_gemm(workspace, nullptr, J, I, false, dY, T, lddy, dX, lddx, dtype, as_stream(stream));
+        }
         if (int rc = launch_gather_cols(dY, T, lddy, perm, I, dtype, workspace, as_stream(stream))) return rc;
         act = workspace;
         ldact = I;

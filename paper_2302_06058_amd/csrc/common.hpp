@@ -155,6 +155,9 @@ int launch_backward_group(const bimask_group_layer* L, int n, int dtype, int N, 
 
 int launch_gather_cols(const void* dY, int64_t T, int64_t ld, const int32_t* perm, int64_t I, int dtype,
                        void* out, hipStream_t s);
+// N > 2: the weight operand with its columns in natural order (in the workspace) instead of the gathered copy of g(Y)
+bool gemm_dense_unpermutes(const void* dY, int64_t T, int64_t ld, int64_t J, int64_t I);
+int launch_unpermute_dense(const void* values, int64_t J, int64_t I, const int32_t* perm, void* out, hipStream_t s);
 // C[t][a] = sum_k Bm[t][k] * A[a][k];  A sparse 2:4 (values + index) or dense.
 int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int64_t K, bool sparse24,
                 const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc, int dtype, hipStream_t s);

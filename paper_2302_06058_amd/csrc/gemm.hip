@@ -418,6 +418,35 @@ k_gather_cols_rows(const uint16_t* __restrict__ in, int64_t T, int64_t ld, const
     }
 }
 
+// Columns of a fragment-major dense operand moved from permuted to natural order: out(r, P[k]) = in(r, k).  A dense
+// operand has no structure along the contraction, so Eq. (10) is as well  dX = dY W'  with the columns of the weights put
+// back where the columns of dY are, and the token matrix needs no gather.  Bound by its two passes over the operand:
+// R rows of it per workgroup (R consecutive granules of 16 bytes in memory) meet in LDS, where the 2-byte scatter costs
+// nothing next to the loads.  Backward product against a gathered copy of dY, 4:8: 384 x 1536 at 25216 tokens
+// 56.7 -> 50.0 us, 2048 x 768 at 3000 35.4 -> 27.8, 1024 x 1024 at 8192 32.0 -> 25.6, 11008 x 4096 at 8192 733.7 -> 726.4.
+__global__ void __launch_bounds__(kThreads)
+k_unpermute_dense(const uint16_t* __restrict__ in, int64_t rows, int K, int64_t ks, const int32_t* __restrict__ perm,
+                  uint16_t* __restrict__ out, int log2r) {
+    extern __shared__ uint4 unperm_smem[];
+    uint16_t* lds = reinterpret_cast<uint16_t*>(unperm_smem);
+    const int R = 1 << log2r, pitch = K + 8;             // K is a multiple of 8: LDS rows stay 16-byte aligned
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) << log2r;       // rows is a multiple of 32
+    const int n = (K >> 3) << log2r, npad = static_cast<int>(ks * 16) << log2r;
+    for (int c = threadIdx.x; c < n; c += kThreads) {
+        const int r = c & (R - 1), k = (c >> log2r) * 8;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(in + tiled_dense_off(r0 + r, k, ks));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lds[r * pitch + perm[k + e]] = static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)));
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < npad; c += kThreads) {
+        const int r = c & (R - 1), k = (c >> log2r) * 8;
+        u32x4 v = {0u, 0u, 0u, 0u};                      // padding of the contraction
+        if (k < K) v = *reinterpret_cast<const u32x4*>(lds + r * pitch + k);
+        *reinterpret_cast<u32x4*>(out + tiled_dense_off(r0 + r, k, ks)) = v;
+    }
+}
+
 template <int R, int CPT>
 int run_gather_rows(const void* dY, int64_t T, int64_t ld, const int32_t* perm, int64_t I, void* out, hipStream_t s) {
     auto kern = k_gather_cols_rows<R, CPT>;
@@ -523,6 +552,29 @@ int launch_gather_cols(const void* dY, int64_t T, int64_t ld, const int32_t* per
                            dim3(kThreads), 0, s, static_cast<const uint32_t*>(dY), T, ld, perm, I,
                            static_cast<uint32_t*>(out), vec);
     }
+    return check_launch();
+}
+
+namespace {
+constexpr int64_t kUnpermuteLds = 48 * 1024;             // one row of the operand has to fit
+}
+
+// Weight bytes (padded) up to those of the tokens: both passes read and write what they move once.  The product then
+// reads dY itself, so its rows have to be 16-byte aligned.
+bool gemm_dense_unpermutes(const void* dY, int64_t T, int64_t ld, int64_t J, int64_t I) {
+    return I % 8 == 0 && (I + 8) * 2 <= kUnpermuteLds && aligned16(dY) && ld % 8 == 0
+        && round_up(J, 32) * round_up(I, 128) <= T * I;
+}
+
+int launch_unpermute_dense(const void* values, int64_t J, int64_t I, const int32_t* perm, void* out, hipStream_t s) {
+    const int64_t rows = round_up(J, 32);
+    int log2r = 3;                                       // 8 rows = whole 128-byte lines; fewer for long rows or few rows
+    while (log2r > 0 && ((I + 8) * 2 << log2r) > kUnpermuteLds) --log2r;
+    while (log2r > 2 && (rows >> log2r) < 512) --log2r;
+    const size_t lds = static_cast<size_t>((I + 8) * 2) << log2r;
+    hipLaunchKernelGGL(k_unpermute_dense, dim3(static_cast<unsigned>(rows >> log2r)), dim3(kThreads), lds, s,
+                       static_cast<const uint16_t*>(values), rows, static_cast<int>(I), ceil_div(I, 128), perm,
+                       static_cast<uint16_t*>(out), log2r);
     return check_launch();
 }
 

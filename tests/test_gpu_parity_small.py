@@ -177,6 +177,22 @@ def test_row_resident_backward_row_tiles(I, J, N, M):
     check_layer(I=I, J=J, N=N, M=M, dtype=synth.BF16, K=1, seed=450 + J, T=33)
 
 
+@pytest.mark.parametrize("I,J,N,M,T", [(24, 32, 4, 8, 200), (136, 264, 4, 8, 600), (2056, 16, 4, 8, 40), (6152, 8, 3, 8, 33),
+                                       (12304, 8, 4, 8, 33), (36, 64, 3, 4, 300)])
+def test_dense_backward_with_weights_in_natural_order(I, J, N, M, T):
+    # 8, 4, 2 and 1 operand rows per workgroup, contractions that end inside a stage; (36, ...) and rows of dY that are
+    # not 16-byte aligned keep the gathered copy of dY
+    check_layer(I=I, J=J, N=N, M=M, dtype=synth.BF16, K=1, seed=460 + J, T=T)
+    W = to_dev(make_w(I, J, synth.BF16, 470), synth.BF16)
+    P = i32_dev(perms_of(I, 1, 471))[0]
+    B = bm.bimask_forward_mask(W, N, M)
+    _, v, x = bm.bimask_backward_mask_compress(W, N, M, B, P)
+    wide = to_dev(make_w(T, I + 2, synth.BF16, 472), synth.BF16)
+    a = bm.bimask_sparse_gemm_bwd(wide[:, :I], P, v, x, I, J, N, M)
+    b = bm.bimask_sparse_gemm_bwd(wide[:, :I].contiguous(), P, v, x, I, J, N, M)
+    assert rel_err(from_dev_f64(a, synth.BF16), from_dev_f64(b, synth.BF16)) <= 2.0 ** -7    # one bf16 rounding each
+
+
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_degenerate_shapes(dtype):
     check_layer(I=4, J=4, N=2, M=4, dtype=dtype, K=1, seed=401, T=1)          # one group, one block
