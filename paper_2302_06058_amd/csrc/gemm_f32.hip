@@ -24,6 +24,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 16;             // output tile: 16 weight rows x 16 tokens
+constexpr int64_t kTilesX = 1 << 20;  // tiles in the x dimension of a launch at most
 
 // one 8-index piece of a weight row: SPARSE: decoded from 4 slot values and 16 index bits
 template <bool SPARSE>
@@ -62,12 +63,14 @@ template <bool SPARSE, bool PERM, int NW>
 __global__ void __launch_bounds__(64 * NW)
 k_gemm_f32(const float* __restrict__ A, const uint32_t* __restrict__ meta, int64_t Adim, int64_t K,
            const float* __restrict__ Bm, int64_t T, int64_t ldb, const int32_t* __restrict__ perm, float* __restrict__ C,
-           int64_t ldc, int tiles_a, bool vecB) {
+           int64_t ldc, uint32_t tiles_a, uint32_t tiles, bool vecB) {
     __shared__ float part[NW][4][64];
+    const uint32_t tile = blockIdx.y * gridDim.x + blockIdx.x;
+    if (tile >= tiles) return;                               // whole workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, q = lane >> 4;
-    const int64_t tt = blockIdx.x / tiles_a;
-    const int64_t a0 = static_cast<int64_t>(blockIdx.x - tt * tiles_a) * kTile, t0 = tt * kTile;
+    const uint32_t tt = tile / tiles_a;
+    const int64_t a0 = static_cast<int64_t>(tile - tt * tiles_a) * kTile, t0 = static_cast<int64_t>(tt) * kTile;
     const int64_t ks = ceil_div(K, 128);
     const int64_t arow = a0 + c;                             // the operand is zero-padded to whole 32-row tiles
     const float* brow = Bm + (t0 + c < T ? t0 + c : T - 1) * ldb;      // clamped: computed, never stored
@@ -115,18 +118,21 @@ k_gemm_f32(const float* __restrict__ A, const uint32_t* __restrict__ meta, int64
 template <bool SPARSE, bool PERM>
 int run_f32(const float* A, const uint32_t* meta, int64_t Adim, int64_t K, const float* Bm, int64_t T, int64_t ldb,
             const int32_t* perm, float* C, int64_t ldc, hipStream_t s) {
-    const int tiles_a = static_cast<int>(ceil_div(Adim, kTile));
-    const int64_t grid = ceil_div(T, kTile) * tiles_a;
-    if (grid > 0x7FFFFFFFll) return BIMASK_ERR_SHAPE;
+    const int64_t tiles = ceil_div(T, kTile) * ceil_div(Adim, kTile);      // below 2^29: the output fits the card
+    if (tiles > 0x7FFFFFFFll) return BIMASK_ERR_SHAPE;
+    // A launch counts the work-items of a dimension in 32 bits and cuts off what is beyond, without an error: 2^24 tiles of
+    // 256 threads in x alone would be none.  x holds 2^20 tiles (2^30 threads at most), y the rest.
+    const uint32_t x = static_cast<uint32_t>(tiles < kTilesX ? tiles : kTilesX);
+    const dim3 grid(x, static_cast<uint32_t>(ceil_div(tiles, x)));
     const bool vecB = aligned16(Bm) && ldb % 4 == 0;
-#define BIMASK_F32(NW)                                                                                        \
-    hipLaunchKernelGGL((k_gemm_f32<SPARSE, PERM, NW>), dim3(static_cast<unsigned>(grid)), dim3(64 * NW), 0, s, A, meta, Adim, K, \
-                       Bm, T, ldb, perm, C, ldc, tiles_a, vecB)
+#define BIMASK_GEMM_F32(NW)                                                                                   \
+    hipLaunchKernelGGL((k_gemm_f32<SPARSE, PERM, NW>), grid, dim3(64 * NW), 0, s, A, meta, Adim, K, Bm, T, ldb, perm, C, ldc, \
+                       static_cast<uint32_t>(ceil_div(Adim, kTile)), static_cast<uint32_t>(tiles), vecB)
     // few tiles: enough wavefronts that each has one or two steps; many tiles fill the chip by themselves
-    if (grid >= 2048 || K <= 128) BIMASK_F32(4);
-    else if (K <= 256) BIMASK_F32(8);
-    else BIMASK_F32(16);
-#undef BIMASK_F32
+    if (tiles >= 2048 || K <= 128) BIMASK_GEMM_F32(4);
+    else if (K <= 256) BIMASK_GEMM_F32(8);
+    else BIMASK_GEMM_F32(16);
+#undef BIMASK_GEMM_F32
     return check_launch();
 }
 

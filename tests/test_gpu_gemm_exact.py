@@ -150,6 +150,26 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
     exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
 
 
+def test_fp32_outputs_beyond_2_to_the_32_elements():
+    """2^24 output tiles of 16 x 16 and more (256 work-items each: beyond what one dimension of a launch counts): the first and
+    the last token rows and the ones around the 2^32nd output equal the product of these rows alone."""
+    import torch
+    I, J, T = 4096, 8, (1 << 20) + 21
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 40 GB of free device memory")
+    rng = np.random.default_rng(7650)
+    W = to_dev(synth.store(int_weights(I, J, rng), synth.F32), synth.F32)
+    X = to_dev(synth.store(sparse_rows(T, J, rng), synth.F32), synth.F32)
+    _, vals, index = bm.bimask_forward_mask_compress(W, 2, 4)
+    Y = bm.bimask_sparse_gemm_fwd(X, vals, index, I, J, 2, 4, Y=torch.full((T, I), -777.0, device=X.device))
+    for a, b in ((0, 64), ((1 << 19) - 32, (1 << 19) + 32), ((1 << 20) - 48, (1 << 20) + 16), (T - 40, T)):
+        part = bm.bimask_sparse_gemm_fwd(X[a:b].contiguous(), vals, index, I, J, 2, 4)
+        assert float(part.abs().max()) > 0 and torch.equal(Y[a:b], part), (a, b)
+    assert bool((Y != -777.0).all())
+    del Y
+    torch.cuda.empty_cache()
+
+
 def test_large_shapes_with_padded_leading_dimensions():
     """The 512 x 128 forward kernel and the row-interleaved gather of the backward pass on activations whose rows
     are longer than the matrices (ldx > J, lddy > I, ldy > I, lddx > J): the outputs must equal those of the
