@@ -188,7 +188,8 @@ BIMASK_API int bimask_sparse_gemm_fwd(const void *X, int64_t T, int64_t ldx, con
 
 /* Backward GEMM, Eq. (10):  dX[t][j] = sum_r dY[t][P[r]] * (Bbar .* W[P,:])[r][j], with the
  * weight operand given in transposed compressed form (transposed = 1); perm = NULL is Eq. (8).
- *   dY  in  T x I (lddy >= I);   dX  out  T x J (lddx >= J).
+ *   dY  in  T x I (lddy >= I);   dX  out  T x J (lddx >= J).  dX may lie on dY only in calls with a
+ *   permutation that ask for a workspace (dY is then copied first).
  *   workspace: bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, ...) bytes (holds dY[:,P], or for
  *   N > 2 the weights with their columns in natural order, when the gather is not fused into the
  *   GEMM; 0 = none needed).  bf16 with N <= 2 fuses it for

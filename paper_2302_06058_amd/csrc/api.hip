@@ -30,6 +30,12 @@ int check_matrix(const void* W, int64_t I, int64_t J, int64_t ldw, int dtype, in
 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
+// Two matrices of T rows that share no byte of the ranges they span.
+bool disjoint(const void* a, int64_t T, int64_t lda, int64_t cols_a, const void* b, int64_t ldb, int64_t cols_b, size_t esz) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 + ((T - 1) * lda + cols_a) * esz <= b0 || b0 + ((T - 1) * ldb + cols_b) * esz <= a0;
+}
+
 // Operand checks shared by the two GEMM entry points.
 int check_gemm(const void* act, int64_t T, int64_t ldact, int64_t kdim, const void* values, const uint32_t* index,
                int64_t I, int64_t J, int dtype, int N, int M, const void* out, int64_t ldout, int64_t outdim) {
@@ -236,9 +242,11 @@ int bimask_sparse_gemm_bwd(const void* dY, int64_t T, int64_t lddy, const int32_
         const size_t need = bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, I, J, T, 0, dtype, N, M);
         if (!workspace || workspace_bytes < need) return BIMASK_ERR_WORKSPACE;
         if (!aligned16(workspace)) return BIMASK_ERR_ALIGN;
-        if (dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
+        // These two read dY while dX is written; dX on top of dY (in place, I = J) takes the copy of dY in the workspace.
+        const bool apart = disjoint(dY, T, lddy, I, dX, lddx, J, esize(dtype));
+        if (apart && dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
             return launch_gemm_f32(Wb_values, Wb_index, J, I, sp, dY, T, lddy, perm, dX, lddx, as_stream(stream));
-        if (dtype == BIMASK_BF16 && !sp && gemm_dense_unpermutes(dY, T, lddy, J, I)) {
+        if (apart && dtype == BIMASK_BF16 && !sp && gemm_dense_unpermutes(dY, T, lddy, J, I)) {
             if (int rc = launch_unpermute_dense(Wb_values, J, I, perm, workspace, as_stream(stream))) return rc;
             return launch_gemm(workspace, nullptr, J, I, false, dY, T, lddy, dX, lddx, dtype, as_stream(stream));
         }

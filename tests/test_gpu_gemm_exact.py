@@ -150,6 +150,27 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
     exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
 
 
+# fp32 with the gather in the token loads and dense bf16 weights in natural order read dY itself while dX is written: dX on top of
+# dY (in place, and one row further down in the same buffer) has to give what a separate output gives
+@pytest.mark.parametrize("C,T,N,M,dtype", [(64, 70, 2, 4, synth.F32), (40, 100, 4, 8, synth.F32), (64, 200, 4, 8, synth.BF16),
+                                           (128, 1000, 3, 4, synth.BF16), (2056, 2300, 4, 8, synth.BF16)])
+def test_backward_product_in_place(C, T, N, M, dtype):
+    import torch
+    rng = np.random.default_rng(7660 + C)
+    W = to_dev(synth.store(int_weights(C, C, rng), dtype), dtype)
+    dY = to_dev(synth.store(sparse_rows(T, C, rng), dtype), dtype)
+    P = i32_dev(rng.permutation(C).astype(np.int32))
+    B = bm.bimask_forward_mask(W, N, M)
+    _, vb, ib = bm.bimask_backward_mask_compress(W, N, M, B, P)
+    want = bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, C, C, N, M)
+    assert float(want.float().abs().max()) > 0
+    for down in (0, 1):
+        buf = torch.zeros((T + 1, C), dtype=dY.dtype, device=dY.device)
+        buf[:T] = dY
+        bm.bimask_sparse_gemm_bwd(buf[:T], P, vb, ib, C, C, N, M, dX=buf[down:T + down])
+        assert torch.equal(buf[down:T + down], want), (C, T, down)
+
+
 def test_fp32_outputs_beyond_2_to_the_32_elements():
     """2^24 output tiles of 16 x 16 and more (256 work-items each: beyond what one dimension of a launch counts): the first and
     the last token rows and the ones around the 2^32nd output equal the product of these rows alone."""
