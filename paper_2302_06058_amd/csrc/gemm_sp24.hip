@@ -316,8 +316,11 @@ k_gemm_sp24(const uint16_t* __restrict__ A, const uint32_t* __restrict__ Ameta, 
     __syncthreads();
     constexpr int UPR = BM / 8;                          // 16-byte units per tile row
 #pragma unroll
-    for (int q = threadIdx.x; q < BN * UPR; q += NT * KG) {
-        const int t = q / UPR, u = q % UPR;
+    for (int it = 0; it < (BN * UPR + NT * KG - 1) / (NT * KG); ++it) {
+        // (a loop over q itself repeats the column bound and the row pointer in every iteration: 128 x 64 1559 instead of
+        // 1527 instructions)
+        const int q = static_cast<int>(threadIdx.x) + NT * KG * it, t = q / UPR, u = q % UPR;
+        if (BN * UPR % (NT * KG) != 0 && q >= BN * UPR) break;           // the 64 x 32 tile: fewer units than threads
         const u32x4 v = *reinterpret_cast<const u32x4*>(smem + t * (BM * 2) + ((u ^ ((2 * t) & (UPR - 1))) << 4));
         const int64_t a = a0 + 8 * u;
         if (t0 + t < T && a < Adim) {
