@@ -73,7 +73,7 @@ def bwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, dY=A, dX=D, ld=0):
 @pytest.mark.parametrize("I,J,T", [(4096, 8, (1 << 20) + 21), (4096, 512, (1 << 20) + 21), (64, 32, 1 << 28), (16, 64, 1 << 30), (65536, 8, 1 << 18)])
 def test_fp32_grids_stay_within_a_launch(rec, I, J, T):
     (l,) = fwd(rec, I, J, T, dtype=bm.F32)               # the fixture checks the dimensions
-    rows = 16 * int(l.args.split(", ")[3])
+    rows = 16 * int((l.args.split(", ") + ["1"])[3])     # weight rows of a workgroup: 16 per row tile
     assert l.kernel == "k_gemm_f32" and l.grid[0] * l.grid[1] >= -(-T // 16) * -(-I // rows)
 
 
