@@ -504,15 +504,29 @@ bool allow_lds(Kern kern, DeviceMemo& memo) {
     return true;
 }
 
+// May the kernels take their LDS?  Where the runtime refuses, the search stays with the L2 kernel.
+template <int M, bool N2OF4>
+bool lds_allowed() {
+    static DeviceMemo memo;
+    return allow_lds(k_perm_score_lds<M, N2OF4>, memo);
+}
+template <int M, bool N2OF4>
+bool lds_group_allowed() {
+    static DeviceMemo memo;
+    return allow_lds(k_perm_score_lds_group<M, N2OF4>, memo);
+}
+template <int M>
+bool lds_group_allowed(int N) { return M == 4 && N == 2 ? lds_group_allowed<M, M == 4>() : lds_group_allowed<M, false>(); }
+
+// BIMASK_ERR_UNSUPPORTED: left to the L2 kernel
 template <int M, bool N2OF4>
 int run_score_lds(const uint32_t* B_bits, int64_t I, int64_t J, int N, const int32_t* perms, int K, const LdsPlan& pl,
                   int32_t* partial, hipStream_t s) {
-    static DeviceMemo memo;
-    auto kern = k_perm_score_lds<M, N2OF4>;
-    if (!allow_lds(kern, memo)) return BIMASK_ERR_HIP;
+    if (!lds_allowed<M, N2OF4>()) return BIMASK_ERR_UNSUPPORTED;
     ScoreLdsP p{B_bits, perms, partial, J, static_cast<int>(I), static_cast<int>(ceil_div(J, 32)), pl.sh, 1, K};
     cut_candidates(K, 256 / pl.nslices, p.groups, p.cpg);        // one workgroup per CU, one round where that is possible
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(pl.nslices * p.groups)), dim3(kLdsThreads), pl.lds, s, p, K, N);
+    hipLaunchKernelGGL((k_perm_score_lds<M, N2OF4>), dim3(static_cast<unsigned>(pl.nslices * p.groups)), dim3(kLdsThreads), pl.lds, s,
+                       p, K, N);
     return check_launch();
 }
 
@@ -522,9 +536,12 @@ int run_score(const uint32_t* B_bits, int64_t I, int64_t J, int N, const int32_t
     constexpr int U = M == 16 ? 1 : 2;
     LdsPlan lp;
     if (alone_from_lds(I, J, K) && plan_lds(I, J, K, M, pl.ws_bytes, kLdsScoreBytes, lp)) {
-        ntiles = lp.nslices;
-        if (M == 4 && N == 2) return run_score_lds<M, M == 4>(B_bits, I, J, N, perms, K, lp, partial, s);
-        return run_score_lds<M, false>(B_bits, I, J, N, perms, K, lp, partial, s);
+        const int rc = M == 4 && N == 2 ? run_score_lds<M, M == 4>(B_bits, I, J, N, perms, K, lp, partial, s)
+                                        : run_score_lds<M, false>(B_bits, I, J, N, perms, K, lp, partial, s);
+        if (rc != BIMASK_ERR_UNSUPPORTED) {
+            ntiles = lp.nslices;
+            return rc;
+        }
     }
     ntiles = pl.ntiles;
     const int wpr32 = static_cast<int>(ceil_div(J, 32));
@@ -630,14 +647,9 @@ int run_score_lds_group(const bimask_group_layer* L, const int* which, const Lds
         blocks += static_cast<unsigned>(plans[l].nslices * p.groups);
     }
     g.first[cnt] = blocks;
-    auto launch = [&](auto kern, DeviceMemo& memo) {
-        if (!allow_lds(kern, memo)) return static_cast<int>(BIMASK_ERR_HIP);
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kLdsThreads), lds, s, g, K, N);
-        return check_launch();
-    };
-    static DeviceMemo memo_2of4, memo_any;
-    if (M == 4 && N == 2) return launch(k_perm_score_lds_group<M, M == 4>, memo_2of4);
-    return launch(k_perm_score_lds_group<M, false>, memo_any);
+    if (M == 4 && N == 2) hipLaunchKernelGGL((k_perm_score_lds_group<M, M == 4>), dim3(blocks), dim3(kLdsThreads), lds, s, g, K, N);
+    else hipLaunchKernelGGL((k_perm_score_lds_group<M, false>), dim3(blocks), dim3(kLdsThreads), lds, s, g, K, N);
+    return check_launch();
 }
 
 }  // namespace
@@ -657,7 +669,8 @@ int launch_perm_search_group(const bimask_group_layer* L, int n, int N, int M, i
             ntiles[l] = pl.ntiles;
             if (plan_lds(a.I, a.J, K, M, pl.ws_bytes, kLdsScoreBytes / 2, plans[nl])) { ntiles[l] = plans[nl].nslices; from_lds[nl++] = b + l; }
         }
-        if (nl < kGroupFromLds) {                        // few layers: all from L2
+        if (nl < kGroupFromLds                           // few layers: all from L2
+            || !(M == 4 ? lds_group_allowed<4>(N) : M == 8 ? lds_group_allowed<8>(N) : lds_group_allowed<16>(N))) {
             for (int l = 0; l < nl; ++l) { const bimask_group_layer& a = L[from_lds[l]]; ntiles[from_lds[l] - b] = plan_perm_search(a.I, a.J, K, M).ntiles; }
             nl = 0;
         }

@@ -85,3 +85,35 @@ def test_backward_product_on_top_of_its_input_copies_it_first(rec, C_, T, N, M, 
     assert bwd(rec, C_, C_, T, N, M, dtype, dX=A - T * row)[0].kernel == direct
     for dX in (A, A + (T - 1) * row, A - (T - 1) * row):
         assert bwd(rec, C_, C_, T, N, M, dtype, dX=dX)[0].kernel.startswith("k_gather_cols"), dX - A
+
+
+def search(rec, I, J, N, M, K):
+    need = bm.workspace_bytes(bm.WS_PERM_SEARCH, I, J, 0, K, bm.BF16, N, M)
+    st, l = rec("bimask_perm_search", A, I, J, N, M, B, K, C, C, D, E, need, None)
+    assert st == 0 and l[-1].kernel == "k_perm_final"
+    return l[0].kernel
+
+
+def group(rec, shapes, N, M, K):
+    arr = (bm.GroupLayer * len(shapes))()
+    for g, (I, J) in zip(arr, shapes):
+        g.I, g.J, g.ldw = I, J, J
+        g.B_bits, g.perms, g.scores, g.best, g.best_perm, g.workspace = A, B, C, C, D, E
+        g.workspace_bytes = bm.workspace_bytes(bm.WS_PERM_SEARCH, I, J, 0, K, bm.BF16, N, M)
+    st, l = rec("bimask_perm_search_group", ctypes.cast(arr, ctypes.c_void_p), len(shapes), N, M, K, None)
+    assert st == 0 and l[-1].kernel == "k_perm_final_group"
+    return [x.kernel for x in l[:-1]]
+
+
+DEIT = [(1152, 384), (384, 384), (1536, 384), (384, 1536)] * 12
+
+
+def test_search_falls_back_where_the_lds_limit_cannot_be_raised(rec):
+    rec.lib.stub_refuse_lds(1)
+    try:
+        for N, M in ((2, 4), (4, 8), (1, 16)):
+            assert search(rec, 3072, 1504, N, M, 100) == "k_perm_score"
+            assert set(group(rec, DEIT, N, M, 100)) == {"k_perm_score_group"}
+    finally:
+        rec.lib.stub_refuse_lds(0)
+    assert search(rec, 3072, 1504, 2, 4, 100) == "k_perm_score_lds"
