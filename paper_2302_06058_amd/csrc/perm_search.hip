@@ -470,19 +470,6 @@ bool plan_lds(int64_t I, int64_t J, int K, int M, size_t ws_bytes, int64_t slice
     pl.lds = (static_cast<size_t>(I) << sh) * 16 + kLdsCands * sizeof(int32_t);
     return static_cast<size_t>(pl.nslices) * static_cast<size_t>(K) * sizeof(int32_t) <= ws_bytes;
 }
-// A layer alone.  Where mask rows are whole cache lines the L2 kernel reaches 22-24 TB/s and the copy does not pay
-// (4096 x 4096 at K = 100 14.5 us from L2, 15.0 from LDS); where rows start inside lines every gather touches two, and
-// large searches gain: 4096 x 11008 37.8 -> 25.9 us, 4096 x 2304 17.2 -> 13.2, while 2048 x 2304 takes 11.3 / 11.2,
-// 1024 x 4608 10.3 / 10.9 and 4096 x 2304 with 32 candidates 9.6 / 11.1.  Rows that are not 16-byte aligned, read word by
-// word from L2, gain earlier (3072 x 1504 20.4 -> 13.7).
-bool alone_from_lds(int64_t I, int64_t J, int K) {
-    const int64_t words = ceil_div(J, 32);
-    return words % 32 != 0 && K >= 32 && I * J >= (words % 4 ? 300000000 : 600000000) / K;
-}
-// Layers of one group call.  The L2 kernel cuts every layer into thousands of wavefronts and the fixed costs of these add
-// up over the layers; the LDS launch costs a copy per workgroup once.  54 ResNet-50 matrices 45 -> 23 us, with 16
-// candidates 20.5 -> 15.6; 48 transformer matrices 38.6 -> 22, but 24 of them (2:8) 24.0 / 24.5 and 4 8.9 / 12.2.
-constexpr int kGroupFromLds = 32;
 // candidates of one slice cut into groups of `cpg`
 void cut_candidates(int K, int64_t groups, int& ngroups, int& cpg) {
     const int64_t most = ceil_div(K, 4), least = ceil_div(K, kLdsCands);
@@ -491,6 +478,41 @@ void cut_candidates(int K, int64_t groups, int& ngroups, int& cpg) {
     cpg = static_cast<int>(ceil_div(K, groups));
     ngroups = static_cast<int>(ceil_div(K, cpg));
 }
+// What either kernel takes, in us: sums of a few counts with measured rates (per ratio: the counting of 2:4 is a formula, that
+// of 16 rows an adder tree of planes).  Alone, over 390 searches from 128 x 128 to 9984 x 20000 with 16 .. 400 candidates,
+// the estimates stray by 7-11 %.
+int ratio_class(int N, int M) { return M == 4 ? (N == 2 ? 0 : 1) : (M == 8 ? 2 : 3); }
+// 16-byte loads of the L2 kernel per lane: M rows per row block, four 4-byte loads where rows start inside 16 bytes
+double l2_loads(int64_t I, int64_t J, int K, int M, const PermPlan& pl) {
+    const int64_t blocks = round_up(ceil_div(I / M, 64 / pl.chunks), M == 16 ? 1 : 2);
+    return static_cast<double>(blocks) * pl.nslices * K * M * (ceil_div(J, 32) % 4 ? 4 : 1);
+}
+// steps of the busiest of a workgroup's 16 wavefronts
+int64_t lds_steps(int cpg, int steps, int M) {
+    const int d = M == 16 ? 2 : 4;
+    return ceil_div(static_cast<int64_t>(cpg) * (steps / d), kLdsThreads / 64) * d;
+}
+// A layer alone.  Where mask rows are whole cache lines the L2 kernel reaches 22-24 TB/s and the copy does not pay
+// (4096 x 4096 at K = 100 14.5 us from L2, 15.0 from LDS); where rows start inside lines every gather touches two, and
+// large searches gain: 4096 x 11008 37.8 -> 25.9 us, 4096 x 2304 17.2 -> 13.2, while 2048 x 2304 takes 11.3 / 11.2,
+// 1024 x 4608 10.3 / 10.9 and 4096 x 2304 with 32 candidates 9.6 / 11.1.  Rows that are not 16-byte aligned, read word by
+// word from L2, gain earlier (3072 x 1504 20.4 -> 13.7).  Other ratios count longer on the same bytes: 4:8 2048 x 4608 at
+// K = 100 18.3 -> 14.2, but 1024 x 11008 15.2 / 17.7 and 4096 x 11008 at 32 candidates 18.6 / 22.9: they compare estimates.
+bool alone_from_lds(int64_t I, int64_t J, int N, int M, int K, const PermPlan& pl, const LdsPlan& lp) {
+    const int64_t words = ceil_div(J, 32);
+    if (words % 32 == 0 || K < 32 || I * J < (words % 4 ? 300000000 : 600000000) / K) return false;
+    if (M == 4 && N == 2) return true;
+    static constexpr struct { double base, step, copy16, copy4, l2_base; } kCost[3] = {      // us; per step, per byte copied by a workgroup
+        {4.6, .725, 2.7e-5, 5.3e-5, 6.8}, {2.1, 1.43, 4.8e-5, 7.2e-5, 7.8}, {2.2, 3.1, 5.1e-5, 7.4e-5, 8.7}};
+    const auto& c = kCost[ratio_class(N, M) - 1];
+    int ngroups, cpg;
+    cut_candidates(K, 256 / lp.nslices, ngroups, cpg);
+    const double rounds = static_cast<double>(ceil_div(static_cast<int64_t>(lp.nslices) * ngroups, 256));
+    const double lds = c.base + rounds * (c.step * lds_steps(cpg, lp.steps, M)
+                                          + (words % 4 ? c.copy4 : c.copy16) * static_cast<double>((I << lp.sh) * 16));
+    return lds < .97 * (c.l2_base + 53e-6 * l2_loads(I, J, K, M, pl));
+}
+
 template <typename Kern>
 bool allow_lds(Kern kern, DeviceMemo& memo) {
     const int dev = DeviceMemo::device();
@@ -503,7 +525,6 @@ bool allow_lds(Kern kern, DeviceMemo& memo) {
     memo.set(dev, 1);
     return true;
 }
-
 // May the kernels take their LDS?  Where the runtime refuses, the search stays with the L2 kernel.
 template <int M, bool N2OF4>
 bool lds_allowed() {
@@ -535,7 +556,7 @@ int run_score(const uint32_t* B_bits, int64_t I, int64_t J, int N, const int32_t
               const PermPlan& pl, int32_t* partial, int& ntiles, hipStream_t s) {
     constexpr int U = M == 16 ? 1 : 2;
     LdsPlan lp;
-    if (alone_from_lds(I, J, K) && plan_lds(I, J, K, M, pl.ws_bytes, kLdsScoreBytes, lp)) {
+    if (plan_lds(I, J, K, M, pl.ws_bytes, kLdsScoreBytes, lp) && alone_from_lds(I, J, N, M, K, pl, lp)) {
         const int rc = M == 4 && N == 2 ? run_score_lds<M, M == 4>(B_bits, I, J, N, perms, K, lp, partial, s)
                                         : run_score_lds<M, false>(B_bits, I, J, N, perms, K, lp, partial, s);
         if (rc != BIMASK_ERR_UNSUPPORTED) {
@@ -619,23 +640,71 @@ int run_score_group(const bimask_group_layer* L, const int* which, int cnt, int 
     return check_launch();
 }
 
+// Layers of one group call.  The L2 kernel cuts every layer into thousands of wavefronts and the fixed costs of these add
+// up over the layers, with a launch per alignment of the rows; the LDS launch costs its copies and at least 7-13 us, and
+// ratios other than 2:4 count longer.  So the two are compared by what they would take, in us, with rates fitted to 290 groups of 2 ..
+// 63 layers (the estimates stray by 7-17 %); the LDS launch has to be the shorter one by 5 %.  2:4, 100 candidates: 54 ResNet-50
+// matrices 45 -> 23 us, 48 transformer matrices 41 -> 23 (with 16 candidates 12.8 / 15.3), 63 of 64 x 64 14.5 / 15.2; 4:8, 100
+// candidates: 48 transformer matrices 46 -> 40, 36 of 1152 x 9216 244 / 306.
+constexpr int kGroupFromLds = 32;                        // layers: below, all from L2
+struct GroupCost {
+    double base, layer, worst, total, copy;              // LDS: per layer; per step of the longest workgroup / of all; per byte
+    double l2_base, l2_class, l2_wave, l2_load16, l2_load4, l2_line;     // L2: per launch after the first, wavefront, load, line
+};
+constexpr GroupCost kGroupCost[4] = {
+    {7.2, .09, .115, 1.03e-3, 1.76e-7, 6.5, 3.4, 4.4e-4, 8.6e-6, 17.3e-6, 1.75e-6},
+    {8.2, .07, .257, 2.18e-3, 1.63e-7, 6.3, 4.0, 3.8e-4, 3.7e-6, 13.6e-6, 5.33e-6},
+    {13.5, .02, .080, 4.96e-3, 1.63e-7, 7.0, 5.3, 6.0e-4, 24.4e-6, 16.2e-6, 2.25e-6},
+    {10.6, .05, 1.65, 7.86e-3, 1.07e-7, 7.3, 5.0, 7.1e-4, 25.1e-6, 14.9e-6, 2.20e-6}};
+
+// equal shares, a bit under one workgroup per CU over the layers together (54 ResNet-50 matrices at K = 100: 21 us
+// with 192 shares, 23-24 with 128, 256 or 384), none below two groups of steps per wavefront
+int64_t lds_share(const LdsPlan* plans, int cnt, int K) {
+    int64_t all = 0;
+    for (int l = 0; l < cnt; ++l) all += static_cast<int64_t>(plans[l].nslices) * K * plans[l].steps;
+    return all / 192 > 128 ? all / 192 : 128;
+}
+// which class of the L2 launches a layer belongs to: (rows 16-byte aligned?, 8 or 32 chunks per slice)
+int l2_class(const bimask_group_layer& a, int K, int M) {
+    return (aligned16(a.B_bits) && ceil_div(a.J, 32) % 4 == 0 ? 1 : 0) | (plan_perm_search(a.I, a.J, K, M).chunks == 32 ? 2 : 0);
+}
+// others: bit set of the classes that stay with the L2 kernel whatever is decided here
+bool group_from_lds(const bimask_group_layer* L, const int* which, const LdsPlan* plans, int cnt, int N, int M, int K, unsigned others) {
+    if (cnt < kGroupFromLds) return false;
+    const GroupCost& c = kGroupCost[ratio_class(N, M)];
+    const int64_t share = lds_share(plans, cnt, K);
+    int64_t worst = 0;
+    double total = 0, copy = 0, l2 = c.l2_base - c.l2_class;
+    unsigned classes = others;
+    for (int l = 0; l < cnt; ++l) {
+        const bimask_group_layer& a = L[which[l]];
+        int ngroups, cpg;
+        cut_candidates(K, ceil_div(static_cast<int64_t>(K) * plans[l].steps, share), ngroups, cpg);
+        const int64_t steps = lds_steps(cpg, plans[l].steps, M), wgs = static_cast<int64_t>(plans[l].nslices) * ngroups;
+        worst = steps > worst ? steps : worst;
+        total += static_cast<double>(steps) * wgs;
+        copy += static_cast<double>((a.I << plans[l].sh) * 16) * wgs;
+        const PermPlan pl = plan_perm_search(a.I, a.J, K, M);
+        const int64_t words = ceil_div(a.J, 32);
+        const int cls = l2_class(a, K, M);
+        if (!((classes >> cls) & 1u)) l2 += c.l2_class;
+        classes |= 1u << cls;
+        l2 += c.l2_wave * pl.ntiles * K + (words % 4 ? c.l2_load4 : c.l2_load16) * l2_loads(a.I, a.J, K, M, pl)
+            + c.l2_line * static_cast<double>(a.I * K * (ceil_div(words, 32) + (words % 32 ? 1 : 0)));
+    }
+    const double lds = c.base + c.layer * cnt + c.worst * worst + c.total * total + c.copy * copy;
+    return lds < .95 * l2;
+}
+
 // All layers that score from LDS, in one launch whatever the alignment of their rows (two workgroups per CU: half of LDS
-// each where a layer allows it).  54 ResNet-50 matrices at K = 100: 43 us in three launches of the L2 kernel, whose
-// wavefronts see two steps each in small layers, -> 21 us.
+// each where a layer allows it).
 template <int M>
 int run_score_lds_group(const bimask_group_layer* L, const int* which, const LdsPlan* plans, int cnt, int N, int K, hipStream_t s) {
     static_assert(kLdsGroupCap >= kSearchGroupCap && sizeof(ScoreLdsGroup) <= 3840, "argument tables must fit the kernel arguments");
     ScoreLdsGroup g{};
     g.n = cnt;
-    // equal shares, a bit under one workgroup per CU over the layers together (54 ResNet-50 matrices at K = 100: 21 us
-    // with 192 shares, 23-24 with 128, 256 or 384), none below two groups of steps per wavefront
-    int64_t all = 0;
+    const int64_t share = lds_share(plans, cnt, K);
     size_t lds = 0;
-    for (int l = 0; l < cnt; ++l) {
-        all += static_cast<int64_t>(plans[l].nslices) * K * plans[l].steps;
-        lds = plans[l].lds > lds ? plans[l].lds : lds;
-    }
-    const int64_t share = all / 192 > 128 ? all / 192 : 128;
     unsigned blocks = 0;
     for (int l = 0; l < cnt; ++l) {
         const bimask_group_layer& a = L[which[l]];
@@ -645,6 +714,7 @@ int run_score_lds_group(const bimask_group_layer* L, const int* which, const Lds
         cut_candidates(K, ceil_div(static_cast<int64_t>(K) * plans[l].steps, share), p.groups, p.cpg);
         g.first[l] = blocks;
         blocks += static_cast<unsigned>(plans[l].nslices * p.groups);
+        lds = plans[l].lds > lds ? plans[l].lds : lds;
     }
     g.first[cnt] = blocks;
     if (M == 4 && N == 2) hipLaunchKernelGGL((k_perm_score_lds_group<M, M == 4>), dim3(blocks), dim3(kLdsThreads), lds, s, g, K, N);
@@ -662,18 +732,18 @@ int launch_perm_search_group(const bimask_group_layer* L, int n, int N, int M, i
     for (int b = 0; b < n; b += kSearchGroupCap) {
         const int m = n - b < kSearchGroupCap ? n - b : kSearchGroupCap;
         int ntiles[kSearchGroupCap], from_lds[kSearchGroupCap], nl = 0;
+        unsigned others = 0;
         LdsPlan plans[kSearchGroupCap];
         for (int l = 0; l < m; ++l) {
             const bimask_group_layer& a = L[b + l];
             const PermPlan pl = plan_perm_search(a.I, a.J, K, M);
             ntiles[l] = pl.ntiles;
-            if (plan_lds(a.I, a.J, K, M, pl.ws_bytes, kLdsScoreBytes / 2, plans[nl])) { ntiles[l] = plans[nl].nslices; from_lds[nl++] = b + l; }
+            if (plan_lds(a.I, a.J, K, M, pl.ws_bytes, kLdsScoreBytes / 2, plans[nl])) from_lds[nl++] = b + l;
+            else others |= 1u << l2_class(a, K, M);
         }
-        if (nl < kGroupFromLds                           // few layers: all from L2
-            || !(M == 4 ? lds_group_allowed<4>(N) : M == 8 ? lds_group_allowed<8>(N) : lds_group_allowed<16>(N))) {
-            for (int l = 0; l < nl; ++l) { const bimask_group_layer& a = L[from_lds[l]]; ntiles[from_lds[l] - b] = plan_perm_search(a.I, a.J, K, M).ntiles; }
-            nl = 0;
-        }
+        if (!group_from_lds(L, from_lds, plans, nl, N, M, K, others)
+            || !(M == 4 ? lds_group_allowed<4>(N) : M == 8 ? lds_group_allowed<8>(N) : lds_group_allowed<16>(N))) nl = 0;
+        for (int l = 0; l < nl; ++l) ntiles[from_lds[l] - b] = plans[l].nslices;
         if (nl) {
             int rc = BIMASK_ERR_NM;
             if (M == 4) rc = run_score_lds_group<4>(L, from_lds, plans, nl, N, K, s);
@@ -688,8 +758,7 @@ int launch_perm_search_group(const bimask_group_layer* L, int n, int N, int M, i
             for (int l = 0, skip = 0; l < m; ++l) {
                 if (skip < nl && from_lds[skip] == b + l) { ++skip; continue; }
                 const bimask_group_layer& a = L[b + l];
-                const bool v = aligned16(a.B_bits) && ceil_div(a.J, 32) % 4 == 0;
-                if (v == vec && plan_perm_search(a.I, a.J, K, M).chunks == chunks) which[cnt++] = b + l;
+                if (l2_class(a, K, M) == cls) which[cnt++] = b + l;
             }
             if (cnt == 0) continue;
             int rc = BIMASK_ERR_NM;

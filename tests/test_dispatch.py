@@ -10,6 +10,7 @@ import subprocess
 import pytest
 
 import paper_2302_06058_amd as bm
+import test_gpu_parity_small as small
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 Launch = collections.namedtuple("Launch", "kernel args grid threads lds")
@@ -105,7 +106,31 @@ def group(rec, shapes, N, M, K):
     return [x.kernel for x in l[:-1]]
 
 
+def test_searches_of_the_parity_tests_reach_the_kernels_they_name(rec):
+    for c in small.LDS_SEARCHES:
+        assert search(rec, *c) == "k_perm_score_lds", c
+    for N, M, K in small.GROUP_SEARCHES_LDS:
+        assert group(rec, small.group_search_shapes(M), N, M, K)[0] == "k_perm_score_lds_group", (N, M, K)
+    for N, M, K in small.GROUP_SEARCHES_L2:
+        assert set(group(rec, small.group_search_shapes(M), N, M, K)) == {"k_perm_score_group"}, (N, M, K)
+
+
 DEIT = [(1152, 384), (384, 384), (1536, 384), (384, 1536)] * 12
+
+
+def test_search_scores_from_lds_where_that_is_shorter(rec):
+    for I, J, N, M, K in ((4096, 11008, 2, 4, 100), (3072, 1504, 4, 8, 100), (2048, 4608, 4, 8, 100)):
+        assert search(rec, I, J, N, M, K) == "k_perm_score_lds", (I, J, N, M, K)
+    for I, J, N, M, K in ((4096, 4096, 2, 4, 100), (1024, 11008, 4, 8, 100), (1024, 11008, 1, 16, 100), (4096, 11008, 1, 4, 32), (4096, 11008, 4, 8, 32)):
+        assert search(rec, I, J, N, M, K) == "k_perm_score", (I, J, N, M, K)
+
+
+def test_group_search_scores_from_lds_where_that_is_shorter(rec):
+    assert group(rec, DEIT, 2, 4, 100) == ["k_perm_score_lds_group"]
+    assert group(rec, DEIT, 4, 8, 100) == ["k_perm_score_lds_group"]
+    for shapes, N, M, K in ((DEIT, 2, 4, 16), ([(64, 64)] * 63, 2, 4, 40), ([(64, 64)] * 63, 1, 16, 100), ([(512, 1152)] * 32, 1, 16, 40),
+                            ([(1152, 9216)] * 36, 4, 8, 100), ([(1152, 9216)] * 36, 1, 16, 100), (DEIT[:24], 2, 4, 100)):
+        assert set(group(rec, shapes, N, M, K)) == {"k_perm_score_group"}, (shapes[0], len(shapes), N, M, K)
 
 
 def test_search_falls_back_where_the_lds_limit_cannot_be_raised(rec):

@@ -241,8 +241,11 @@ def random_mask(I, J, N, M, seed):
 
 # searches that score from a column slice in LDS: rows of 16-byte and of 4-byte pitch, 2 / 4 / 8 chunks per row, ragged last
 # slices and row blocks, more candidates than one workgroup takes (256), a permutation copied by several workgroups
-@pytest.mark.parametrize("I,J,N,M,K", [(1028, 2052, 2, 4, 300), (1040, 2176, 2, 4, 300), (4992, 260, 2, 4, 310), (2600, 1100, 1, 4, 120),
-                                       (1208, 1256, 4, 8, 257), (1200, 1328, 3, 16, 261), (2100, 2180, 3, 4, 100)])
+LDS_SEARCHES = [(1028, 2052, 2, 4, 300), (1040, 2176, 2, 4, 300), (4992, 260, 2, 4, 310), (2600, 1100, 1, 4, 120),
+                (1608, 1256, 4, 8, 300), (1600, 1328, 3, 16, 261), (2100, 2180, 3, 4, 100)]
+
+
+@pytest.mark.parametrize("I,J,N,M,K", LDS_SEARCHES + [(1208, 1256, 4, 8, 257), (1200, 1328, 3, 16, 261)])     # (the last two from L2)
 def test_perm_search_from_lds(I, J, N, M, K):
     Bo, B = random_mask(I, J, N, M, 900 + I)
     perms = perms_of(I, K, 901 + I)
@@ -253,12 +256,23 @@ def test_perm_search_from_lds(I, J, N, M, K):
     assert (best_perm.cpu().numpy() == perms[int(best.item())]).all()
 
 
-@pytest.mark.parametrize("N,M,K", [(2, 4, 16), (1, 4, 19), (4, 8, 23), (2, 16, 17)])
-def test_group_search_from_lds(N, M, K):
-    """32 layers and more in one group call score from LDS; two of these are too tall for it and stay with the other kernel."""
-    import torch
+def group_search_shapes(M):
+    """36 layers, two of them too tall for LDS."""
     shapes = [(M * (1 + 3 * (i % 12)), M * (2 + 5 * (i % 9))) for i in range(30)]
-    shapes += [(2400, 144), (528, 2064), (1008, 1040), (64, 64 * M), (4096, 160), (16 * 313, 256)]
+    return shapes + [(2400, 144), (528, 2064), (1008, 1040), (64, 64 * M), (4096, 160), (16 * 313, 256)]
+
+
+# few candidates: all layers from L2; many: the eligible ones score from LDS in one launch
+GROUP_SEARCHES_L2 = [(2, 4, 16), (1, 4, 19), (4, 8, 23), (2, 16, 17)]
+GROUP_SEARCHES_LDS = [(2, 4, 160), (1, 4, 161), (4, 8, 257), (2, 16, 257)]
+
+
+@pytest.mark.parametrize("N,M,K", GROUP_SEARCHES_L2 + GROUP_SEARCHES_LDS)
+def test_group_search_from_lds(N, M, K):
+    """32 layers and more in one group call score from LDS where that is shorter; two of these are too tall for it and stay with
+    the other kernel."""
+    import torch
+    shapes = group_search_shapes(M)
     entries, refs = [], []
     for li, (I, J) in enumerate(shapes):
         Bo, B = random_mask(I, J, N, M, 950 + li)
