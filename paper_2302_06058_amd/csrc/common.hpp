@@ -170,7 +170,8 @@ bool gemm_f32_fuses_gather(int64_t T, int64_t Adim, int64_t K);
 // workgroup tile (weight rows x tokens) of the streaming 2:4 kernel
 enum class Sp24Tile { k256x64, k128x64, k256x128, k64x64, k64x32Split, k64x64Split };
 // One 64 x 32 tile per CU at most: the contraction is split inside the workgroup.  512 x 2048 at 784 tokens (200 tiles)
-// 9.6 -> 6.5 us and 1024 x 1024 at 512 (256) 6.1 -> 5.0, but 2048 x 512 at 784 (800) 5.5 -> 12.3.
+// 9.6 -> 6.5 us, 1024 x 1024 at 512 (256) 6.1 -> 5.0.  A second round costs more than the split saves: 512 x 1152 at 1088
+// tokens (272 tiles) 6.7 us, with this tile 9.3; at 3200 (800) 7.7 / 17.6.
 inline bool gemm_few_tiles(int64_t Adim, int64_t T) { return ceil_div(Adim, 64) * ceil_div(T, 32) <= 256; }
 int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bm, int64_t T,
                      int64_t ldb, void* C, int64_t ldc, Sp24Tile tile, hipStream_t s);

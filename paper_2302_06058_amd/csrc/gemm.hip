@@ -588,15 +588,25 @@ int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int
                 const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc, int dtype, hipStream_t s) {
     if (dtype == BIMASK_F32) return launch_gemm_f32(A_values, A_index, Adim, K, sparse24, Bm, T, ldb, nullptr, C, ldc, s);
     if (sparse24) {
+        // A 64 x 32 or 64 x 64 tile per CU at most: split the contraction inside the workgroup (4096 x 4096 at 64 tokens
+        // 17.5 -> 8.9 us, at 256 18.3 -> 15.4).  Three stages and more gain, four where token rows are read in 4-byte pieces
+        // (512 x 264 at 64 tokens 4.6 -> 4.1 us; 512 x 260 with rows of 524 bytes 6.0, split 6.6).  One stage has nothing to
+        // split; two pay for it only against the resident kernel, with 16-byte token rows and enough of them (512 x 192 at 64
+        // tokens 5.1 -> 4.0 us, at 4 tokens 3.8 / 3.9; 512 x 256, streamed otherwise, at 16 3.8 / 4.1; 4-byte pieces
+        // 512 x 132 at 32 5.2 / 6.4).  Up to 64 rows the 64 x 64 tile is the shorter with one group (64 x 576 at 13000 tokens
+        // 5.1 us, two groups 5.9).
+        const bool rows16 = aligned16(Bm) && ldb % 8 == 0 && K % 8 == 0, deep = K > (rows16 ? 256 : 384);
+        const bool two_stages = rows16 && K > 128 && T >= 16 && (K < 256 || Adim > 512);
+        const bool split32 = (deep || two_stages) && gemm_few_tiles(Adim, T);
+        const bool split64 = deep && Adim > 64 && ceil_div(Adim, 64) * ceil_div(T, 64) <= 256;
         if (K <= 512) {
             // narrow weights: wavefront-private tiles; short contractions (below 256, or below 384 with more
             // than 512 weight rows): token tile resident in LDS, reused by every weight tile; otherwise the
             // streaming kernel below (measured per layer shape: 128 x 512 forward 30 -> 20 us, 2048 x 512 14 -> 10 us)
             int rc = launch_gemm_sp24_narrow(A_values, A_index, Adim, K, Bm, ldb, nullptr, T, C, ldc, s);
             if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
-            // with few tokens a workgroup or two would walk all weight rows: 2048 x 256 at 64 tokens 5.1 us resident, 4.6
-            // split; a single stage has nothing to split (64 x 128 at one token 4.1 against 4.7)
-            if ((K < 256 || (K < 384 && Adim > 512)) && (K <= 128 || !gemm_few_tiles(Adim, T))) {
+            // (with few tokens a workgroup or two would walk all weight rows: 2048 x 256 at 64 tokens 5.3 us resident, 4.4 split)
+            if ((K < 256 || (K < 384 && Adim > 512)) && !split32) {
                 rc = launch_gemm_sp24_resident(A_values, A_index, Adim, K, Bm, ldb, nullptr, T, C, ldc, s);
                 if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
             }
@@ -614,9 +624,6 @@ int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int
         const bool narrow = (w256 - w128) * 5 >= w256;
         // few tokens and few weight tiles: 256-row tiles would leave CUs idle
         const bool underfilled = ceil_div(Adim, 256) * ceil_div(T, 64) <= 128;
-        // a 64 x 32 or 64 x 64 tile per CU at most: split the contraction inside the workgroup (4096 x 4096 at 64 tokens
-        // 17.5 -> 8.9 us, at 256 18.3 -> 15.4)
-        const bool split32 = gemm_few_tiles(Adim, T), split64 = ceil_div(Adim, 64) * ceil_div(T, 64) <= 256;
         const Sp24Tile tile = split32 ? Sp24Tile::k64x32Split
                             : split64 ? Sp24Tile::k64x64Split
                             : Adim <= 64 ? Sp24Tile::k64x64

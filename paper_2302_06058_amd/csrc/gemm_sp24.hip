@@ -413,7 +413,10 @@ int launch_gemm_sp24(const void* A, const uint32_t* meta, int64_t Adim, int64_t 
 int launch_gemm_dense_frag(const void* A, int64_t Adim, int64_t K, const void* Bm, int64_t T, int64_t ldb, void* C,
                            int64_t ldc, hipStream_t s) {
     if (!aligned16(A) || !aligned16(Bm) || (ldb * 2) % 16 != 0 || K % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
-    if (gemm_few_tiles(Adim, T)) return run_dense_frag<64, 32, 2, 1, 1, 4>(A, Adim, K, Bm, T, ldb, C, ldc, s);
+    // few tiles: a single stage, or up to two with at most 64 rows, gains nothing from the split (512 x 128 at 256 tokens 4.2 us,
+    // split 4.5; 64 x 256 at 784 3.8 / 4.4), longer contractions do (64 x 512 at 784 4.9 -> 4.6, 512 x 264 at 256 5.7 -> 4.6)
+    if (K > (Adim <= 64 ? 256 : 128) && gemm_few_tiles(Adim, T))
+        return run_dense_frag<64, 32, 2, 1, 1, 4>(A, Adim, K, Bm, T, ldb, C, ldc, s);
     if (Adim <= 64) return run_dense_frag<64, 64, 2, 2, 2>(A, Adim, K, Bm, T, ldb, C, ldc, s);
     const bool big = ceil_div(Adim, 256) * ceil_div(T, 128) >= 190;
     // weight dimensions that would leave a fifth or more of the 256-row tiles empty (384 = 1.5 tiles) take 128-row tiles

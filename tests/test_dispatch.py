@@ -88,6 +88,20 @@ def test_backward_product_on_top_of_its_input_copies_it_first(rec, C_, T, N, M, 
         assert bwd(rec, C_, C_, T, N, M, dtype, dX=dX)[0].kernel.startswith("k_gather_cols"), dX - A
 
 
+# the tile of the streaming kernel (weight rows, tokens, wavefronts M and N, groups), or another kernel
+@pytest.mark.parametrize("I,J,T,N,M,ld,want", [
+    (512, 264, 64, 2, 4, 0, "64, 32, 2, 1, 4"), (512, 384, 1024, 2, 4, 0, "64, 32, 2, 1, 4"), (512, 1152, 2000, 2, 4, 0, "64, 64, 2, 2, 2"),
+    (512, 256, 64, 2, 4, 0, "128, 64, 4, 1, 1"), (1000, 256, 64, 2, 4, 0, "64, 32, 2, 1, 4"), (1000, 256, 8, 2, 4, 0, "k_gemm_sp24_resident"),
+    (512, 192, 64, 2, 4, 0, "64, 32, 2, 1, 4"), (512, 192, 8, 2, 4, 0, "k_gemm_sp24_resident"), (512, 128, 64, 2, 4, 0, "k_gemm_sp24_resident"),
+    (512, 132, 64, 2, 4, 0, "k_gemm_sp24_resident"), (512, 260, 64, 2, 4, 0, "128, 64, 4, 1, 1"), (512, 264, 64, 2, 4, 266, "128, 64, 4, 1, 1"),
+    (512, 388, 64, 2, 4, 0, "64, 32, 2, 1, 4"), (64, 576, 8000, 2, 4, 0, "64, 32, 2, 1, 4"), (64, 576, 13000, 2, 4, 0, "64, 64, 2, 2, 1"),
+    (64, 256, 784, 4, 8, 0, "64, 64, 2, 2, 1"), (64, 264, 784, 4, 8, 0, "64, 32, 2, 1, 4"), (512, 128, 256, 4, 8, 0, "128, 64, 4, 1, 1"),
+    (512, 136, 256, 4, 8, 0, "64, 32, 2, 1, 4")])
+def test_split_contractions_are_taken_where_they_gain(rec, I, J, T, N, M, ld, want):
+    (l,) = fwd(rec, I, J, T, N, M, ld=ld)
+    assert (l.args.startswith(want + ", ") if l.kernel == "k_gemm_sp24" else l.kernel == want), l
+
+
 def search(rec, I, J, N, M, K):
     need = bm.workspace_bytes(bm.WS_PERM_SEARCH, I, J, 0, K, bm.BF16, N, M)
     st, l = rec("bimask_perm_search", A, I, J, N, M, B, K, C, C, D, E, need, None)
