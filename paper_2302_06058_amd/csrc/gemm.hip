@@ -425,12 +425,12 @@ k_gather_cols_rows(const uint16_t* __restrict__ in, int64_t T, int64_t ld, const
 // nothing next to the loads.  Backward product against a gathered copy of dY, 4:8: 384 x 1536 at 25216 tokens
 // 56.7 -> 50.0 us, 2048 x 768 at 3000 35.4 -> 27.8, 1024 x 1024 at 8192 32.0 -> 25.6, 11008 x 4096 at 8192 733.7 -> 726.4.
 __global__ void __launch_bounds__(kThreads)
-k_unpermute_dense(const uint16_t* __restrict__ in, int64_t rows, int K, int64_t ks, const int32_t* __restrict__ perm,
+k_unpermute_dense(const uint16_t* __restrict__ in, int K, int64_t ks, const int32_t* __restrict__ perm,
                   uint16_t* __restrict__ out, int log2r) {
     extern __shared__ uint4 unperm_smem[];
     uint16_t* lds = reinterpret_cast<uint16_t*>(unperm_smem);
     const int R = 1 << log2r, pitch = K + 8;             // K is a multiple of 8: LDS rows stay 16-byte aligned
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) << log2r;       // rows is a multiple of 32
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) << log2r;       // the operand is padded to whole 32-row tiles
     const int n = (K >> 3) << log2r, npad = static_cast<int>(ks * 16) << log2r;
     for (int c = threadIdx.x; c < n; c += kThreads) {
         const int r = c & (R - 1), k = (c >> log2r) * 8;
@@ -557,23 +557,32 @@ int launch_gather_cols(const void* dY, int64_t T, int64_t ld, const int32_t* per
 
 namespace {
 constexpr int64_t kUnpermuteLds = 48 * 1024;             // one row of the operand has to fit
+// operand rows per workgroup (log2): 8 = whole 128-byte lines; fewer for long rows or few rows
+int unpermute_rows_log2(int64_t I, int64_t rows) {
+    int log2r = 3;
+    while (log2r > 0 && ((I + 8) * 2 << log2r) > kUnpermuteLds) --log2r;
+    while (log2r > 2 && (rows >> log2r) < 512) --log2r;
+    return log2r;
 }
+}  // namespace
 
-// Weight bytes (padded) up to those of the tokens: both passes read and write what they move once.  The product then
-// reads dY itself, so its rows have to be 16-byte aligned.
+// Weight bytes (padded) up to those of the tokens: both passes read and write what they move once.  Where LDS takes only two
+// rows or one, the operand moves as 32- or 16-byte pieces and the line is lower: 8192 x 2240 at 3000 tokens 137 us with the
+// gathered copy, 144 un-permuted, 8192 x 2048 134 / 134; 16384 x 1472 at 3000 283 / 313, 16384 x 1024 210 / 210.  The product
+// then reads dY itself, so its rows have to be 16-byte aligned.
 bool gemm_dense_unpermutes(const void* dY, int64_t T, int64_t ld, int64_t J, int64_t I) {
-    return I % 8 == 0 && (I + 8) * 2 <= kUnpermuteLds && aligned16(dY) && ld % 8 == 0
-        && round_up(J, 32) * round_up(I, 128) <= T * I;
+    if (I % 8 != 0 || (I + 8) * 2 > kUnpermuteLds || !aligned16(dY) || ld % 8 != 0) return false;
+    const int64_t weights = round_up(J, 32) * round_up(I, 128), tokens = T * I;
+    const int log2r = unpermute_rows_log2(I, round_up(J, 32));
+    return log2r >= 2 ? weights <= tokens : log2r == 1 ? 3 * weights <= 2 * tokens : 3 * weights <= tokens;
 }
 
 int launch_unpermute_dense(const void* values, int64_t J, int64_t I, const int32_t* perm, void* out, hipStream_t s) {
     const int64_t rows = round_up(J, 32);
-    int log2r = 3;                                       // 8 rows = whole 128-byte lines; fewer for long rows or few rows
-    while (log2r > 0 && ((I + 8) * 2 << log2r) > kUnpermuteLds) --log2r;
-    while (log2r > 2 && (rows >> log2r) < 512) --log2r;
+    const int log2r = unpermute_rows_log2(I, rows);
     const size_t lds = static_cast<size_t>((I + 8) * 2) << log2r;
     hipLaunchKernelGGL(k_unpermute_dense, dim3(static_cast<unsigned>(rows >> log2r)), dim3(kThreads), lds, s,
-                       static_cast<const uint16_t*>(values), rows, static_cast<int>(I), ceil_div(I, 128), perm,
+                       static_cast<const uint16_t*>(values), static_cast<int>(I), ceil_div(I, 128), perm,
                        static_cast<uint16_t*>(out), log2r);
     return check_launch();
 }

@@ -14,6 +14,13 @@ namespace {
 struct Dim { uint32_t x, y, z; };
 struct Config { Dim grid, block; size_t lds; void* stream; };
 std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
+// a demangled name without return type, namespaces and parameters
+std::string plain(std::string k) {
+    for (const char* drop : {"void ", "bimask::", "(anonymous namespace)::"})
+        for (size_t at; (at = k.find(drop)) != std::string::npos;) k.erase(at, std::strlen(drop));
+    k.resize(k.find('('));
+    return k;
+}
 Config pending;
 std::string record;                                      // one line per launch
 bool refuse_lds = false;
@@ -36,10 +43,7 @@ int __hipPopCallConfiguration(Dim* grid, Dim* block, size_t* lds, void** stream)
     return 0;
 }
 int hipLaunchKernel(const void* f, Dim grid, Dim block, void**, size_t lds, void*) {
-    std::string k = names()[f];
-    for (const char* drop : {"void ", "bimask::", "(anonymous namespace)::"})
-        for (size_t at; (at = k.find(drop)) != std::string::npos;) k.erase(at, std::strlen(drop));
-    k.resize(k.find('('));                               // without the parameters
+    const std::string k = plain(names()[f]);
     char line[160];
     std::snprintf(line, sizeof line, "|%u,%u,%u|%u|%zu\n", grid.x, grid.y, grid.z, block.x * block.y * block.z, lds);
     record += k + line;
@@ -52,6 +56,12 @@ int hipGetSymbolAddress(void** p, const void*) { *p = device_array; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 2; return 0; }
 
 __attribute__((visibility("default"))) const char* stub_launches() { return record.c_str(); }
+__attribute__((visibility("default"))) const char* stub_kernels() {         // every kernel of the library, one a line
+    static std::string all;
+    if (all.empty())
+        for (const auto& n : names()) all += plain(n.second) + "\n";
+    return all.c_str();
+}
 __attribute__((visibility("default"))) void stub_clear() { record.clear(); }
 __attribute__((visibility("default"))) void stub_refuse_lds(int on) { refuse_lds = on != 0; }
 }

@@ -40,7 +40,7 @@ def rec(tmp_path_factory):
     for name, (res, args) in bm._SIGNATURES.items():
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
-    lib.stub_launches.restype = ctypes.c_char_p
+    lib.stub_launches.restype = lib.stub_kernels.restype = ctypes.c_char_p
 
     def call(name, *args):
         lib.stub_clear()
@@ -64,9 +64,9 @@ def fwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, ld=0, X=A):
     return l
 
 
-def bwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, dY=A, dX=D, ld=0):
+def bwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, dY=A, dX=D, ld=0, perm=C):
     need = bm.workspace_bytes(bm.WS_GEMM_BWD, I, J, T, 0, dtype, N, M)
-    st, l = rec("bimask_sparse_gemm_bwd", dY, T, ld or I, C, B, C, I, J, dtype, N, M, dX, J, E, need, None)
+    st, l = rec("bimask_sparse_gemm_bwd", dY, T, ld or I, perm, B, C, I, J, dtype, N, M, dX, J, E, need, None)
     assert st == 0
     return l
 
@@ -100,6 +100,17 @@ def test_backward_product_on_top_of_its_input_copies_it_first(rec, C_, T, N, M, 
 def test_split_contractions_are_taken_where_they_gain(rec, I, J, T, N, M, ld, want):
     (l,) = fwd(rec, I, J, T, N, M, ld=ld)
     assert (l.args.startswith(want + ", ") if l.kernel == "k_gemm_sp24" else l.kernel == want), l
+
+
+def test_dense_backward_puts_the_weights_in_natural_order(rec):
+    for (I, J, N, M, T), rows in small.NATURAL_ORDER.items():
+        l = bwd(rec, I, J, T, N, M)
+        assert (l[0].lds == (I + 8) * 2 * rows and l[0].kernel == "k_unpermute_dense") if rows else l[0].kernel.startswith("k_gather_cols"), (I, J, T)
+        if rows:
+            assert bwd(rec, I, J, T, N, M, ld=I + 24)[0].kernel == "k_unpermute_dense"
+            assert bwd(rec, I, J, T, N, M, ld=I + 2)[0].kernel.startswith("k_gather_cols")
+    for I, J, T, natural in ((4096, 2976, 3000, True), (8192, 2240, 3000, False), (8192, 1984, 3000, True), (16384, 1472, 3000, False), (16384, 992, 3000, True)):
+        assert (bwd(rec, I, J, T, 4, 8)[0].kernel == "k_unpermute_dense") == natural, (I, J, T)
 
 
 def search(rec, I, J, N, M, K):

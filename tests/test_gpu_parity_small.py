@@ -177,11 +177,15 @@ def test_row_resident_backward_row_tiles(I, J, N, M):
     check_layer(I=I, J=J, N=N, M=M, dtype=synth.BF16, K=1, seed=450 + J, T=33)
 
 
-@pytest.mark.parametrize("I,J,N,M,T", [(24, 32, 4, 8, 200), (136, 264, 4, 8, 600), (2056, 16, 4, 8, 40), (6152, 8, 3, 8, 33),
-                                       (12304, 8, 4, 8, 33), (36, 64, 3, 4, 300)])
+# (I, J, N, M, T): operand rows per workgroup (0: too few tokens for the weights, or rows that are no multiple of 8)
+NATURAL_ORDER = {(24, 32, 4, 8, 200): 4, (136, 264, 4, 8, 600): 4, (2056, 16, 4, 8, 40): 4, (6152, 8, 3, 8, 64): 2, (12304, 8, 4, 8, 128): 1,
+                 (64, 4104, 4, 8, 8400): 8, (6152, 8, 3, 8, 33): 0, (12304, 8, 4, 8, 33): 0, (36, 64, 3, 4, 300): 0}
+
+
+@pytest.mark.parametrize("I,J,N,M,T", list(NATURAL_ORDER))
 def test_dense_backward_with_weights_in_natural_order(I, J, N, M, T):
-    # 8, 4, 2 and 1 operand rows per workgroup, contractions that end inside a stage; (36, ...) and rows of dY that are
-    # not 16-byte aligned keep the gathered copy of dY
+    # contractions that end inside a stage, a ragged last tile of operand rows; without a row count, and with rows of dY that are
+    # not 16-byte aligned, the gathered copy of dY
     check_layer(I=I, J=J, N=N, M=M, dtype=synth.BF16, K=1, seed=460 + J, T=T)
     W = to_dev(make_w(I, J, synth.BF16, 470), synth.BF16)
     P = i32_dev(perms_of(I, 1, 471))[0]
@@ -191,6 +195,12 @@ def test_dense_backward_with_weights_in_natural_order(I, J, N, M, T):
     a = bm.bimask_sparse_gemm_bwd(wide[:, :I], P, v, x, I, J, N, M)
     b = bm.bimask_sparse_gemm_bwd(wide[:, :I].contiguous(), P, v, x, I, J, N, M)
     assert rel_err(from_dev_f64(a, synth.BF16), from_dev_f64(b, synth.BF16)) <= 2.0 ** -7    # one bf16 rounding each
+    if I % 8 == 0:                                       # longer rows on 16-byte boundaries: the same kernels, bit for bit
+        wide = to_dev(make_w(T, I + 24, synth.BF16, 473), synth.BF16)
+        out = torch.full((T, J + 8), 3.0, dtype=torch.bfloat16, device=wide.device)
+        a = bm.bimask_sparse_gemm_bwd(wide[:, 8:I + 8], P, v, x, I, J, N, M, dX=out[:, :J])
+        b = bm.bimask_sparse_gemm_bwd(wide[:, 8:I + 8].contiguous(), P, v, x, I, J, N, M)
+        assert torch.equal(a, b) and bool((out[:, J:] == 3.0).all())
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
