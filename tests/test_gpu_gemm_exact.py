@@ -142,12 +142,43 @@ def test_fp32_gemms_are_exact(N, M):
     exact_layer(136, 264, 300, N, M, synth.F32, 7500 + M)
 
 
-# 16 x 16 tiles; 4 / 8 / 16 wavefronts by contraction length and tile count; gather in the token loads or as a pass
-@pytest.mark.parametrize("I,J,T", [(8, 8, 5), (16, 136, 37), (40, 264, 70), (520, 24, 131), (264, 520, 1040), (24, 136, 16400)])
+# 16 x 16 tiles; 1 / 2 / 4 / 8 / 16 wavefronts by contraction length and tile count; gather in the token loads or as a pass; 64 weight
+# rows per workgroup where there are many tiles (the last workgroup with 1 and 3 row tiles, the last row tile half filled)
+F32_SHAPES = [(8, 8, 5), (16, 136, 37), (40, 264, 70), (520, 24, 131), (264, 520, 1040), (24, 136, 16400),
+              (136, 56, 37), (72, 40, 50), (104, 48, 20000), (72, 136, 33000), (24, 136, 60000)]
+
+
+@pytest.mark.parametrize("I,J,T", F32_SHAPES)
 @pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
 @pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
 def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
     exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
+
+
+@pytest.mark.parametrize("I,J,T", [(40, 72, 37), (72, 40, 50), (264, 136, 300), (136, 72, 33000)])
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
+def test_fp32_rows_at_any_pitch(I, J, T, N, M):
+    """Token rows that start on 16 bytes and on 4, in wider buffers: what the packed call gives, and the padding untouched."""
+    import torch
+    rng = np.random.default_rng(7670 + I)
+    W = to_dev(synth.store(int_weights(I, J, rng), synth.F32), synth.F32)
+    X = to_dev(synth.store(sparse_rows(T, J, rng), synth.F32), synth.F32)
+    dY = to_dev(synth.store(sparse_rows(T, I, rng), synth.F32), synth.F32)
+    P = i32_dev(rng.permutation(I).astype(np.int32))
+    B, v, x = bm.bimask_forward_mask_compress(W, N, M)
+    Y = bm.bimask_sparse_gemm_fwd(X, v, x, I, J, N, M)
+    for perm in (P, None):
+        _, vb, xb = bm.bimask_backward_mask_compress(W, N, M, B, perm)
+        dX = bm.bimask_sparse_gemm_bwd(dY, perm, vb, xb, I, J, N, M)
+        for at, extra in ((4, 8), (1, 3)):
+            wide = lambda a, fill: torch.full((T, a + extra), fill, dtype=torch.float32, device=W.device)
+            Xw, dYw, Yw, dXw = wide(J, float("nan")), wide(I, float("nan")), wide(I, 3.0), wide(J, 3.0)
+            Xw[:, at:at + J], dYw[:, at:at + I] = X, dY
+            bm.bimask_sparse_gemm_fwd(Xw[:, at:at + J], v, x, I, J, N, M, Y=Yw[:, at:at + I])
+            bm.bimask_sparse_gemm_bwd(dYw[:, at:at + I], perm, vb, xb, I, J, N, M, dX=dXw[:, at:at + J])
+            for out, want, c in ((Yw, Y, I), (dXw, dX, J)):
+                assert torch.equal(out[:, at:at + c], want)
+                assert bool((out[:, :at] == 3.0).all()) and bool((out[:, at + c:] == 3.0).all())
 
 
 # fp32 with the gather in the token loads and dense bf16 weights in natural order read dY itself while dX is written: dX on top of
