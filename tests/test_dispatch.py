@@ -10,7 +10,9 @@ import subprocess
 import pytest
 
 import paper_2302_06058_amd as bm
+import test_gpu_gemm_exact as exact
 import test_gpu_parity_small as small
+from paper_2302_06058_amd import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 Launch = collections.namedtuple("Launch", "kernel args grid threads lds")
@@ -111,6 +113,17 @@ def test_dense_backward_puts_the_weights_in_natural_order(rec):
             assert bwd(rec, I, J, T, N, M, ld=I + 2)[0].kernel.startswith("k_gather_cols")
     for I, J, T, natural in ((4096, 2976, 3000, True), (8192, 2240, 3000, False), (8192, 1984, 3000, True), (16384, 1472, 3000, False), (16384, 992, 3000, True)):
         assert (bwd(rec, I, J, T, 4, 8)[0].kernel == "k_unpermute_dense") == natural, (I, J, T)
+
+
+def test_exact_products_reach_every_instance_of_the_gemm_kernels(rec):
+    reached = set()
+    for I, J, T, N, M, dtype in exact.exact_products():
+        code = bm.F32 if dtype == synth.F32 else bm.BF16
+        reached.update(fwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code, perm=None))
+    names = {f"{l.kernel}<{l.args}>" if l.args else l.kernel for l in reached}
+    families = ("k_gemm_sp24", "k_gemm_f32", "k_unpermute_dense", "k_gather_cols_rows")
+    missing = {k for k in rec.lib.stub_kernels().decode().splitlines() if k.startswith(families)} - names
+    assert not missing, sorted(missing)
 
 
 def search(rec, I, J, N, M, K):

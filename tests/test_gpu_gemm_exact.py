@@ -68,36 +68,53 @@ def exact_layer(I, J, T, N, M, dtype, seed, perm=True):
     assert bad_x.shape[0] == 0, f"backward: {bad_x.shape[0]} wrong outputs, first at (t, j) = {bad_x[0].tolist()}"
 
 
-# (I, J, T): forward kernel / backward kernel (with a permutation)
+# (I, J, T): forward kernel / backward kernel with a permutation.  "split 64 x 32": the streaming kernel with the contraction split over
+# groups of wavefronts; "ragged": the contraction ends inside a 128-deep stage, "4-byte rows": it is no multiple of 8
 SP24_SHAPES = [
     (64, 148, 300),      # wavefront-private, 296-byte rows / wavefront-private, 5 row tiles, 296-byte output rows
     (256, 64, 300),      # wavefront-private, two sibling wavefronts / wavefront-private 2 x 2 stages
-    (224, 64, 150),      # wavefront-private, 7 row tiles over 2 x 4 / ...
+    (224, 64, 150),      # wavefront-private, 7 row tiles over 2 x 4 / wavefront-private 2 x 2 stages
     (64, 512, 600),      # wavefront-private, 4 stages / resident-token 256 x 64
-    (160, 128, 200),     # wavefront-private, 5 row tiles / wavefront-private split
-    (128, 256, 700),     # streaming 128 x 64 / wavefront-private split with the fused gather
-    (512, 128, 300),     # resident-token 256 x 64, one stage / resident-token 128 x 32 ... 4 stages: 256 x 64
-    (1024, 192, 300),    # resident-token, two stages / streaming after the separate gather (few tokens)
-    (256, 124, 300),     # resident-token / resident-token 128 x 32, two stages
+    (160, 128, 200),     # wavefront-private, 5 row tiles / resident-token 128 x 32, two stages
+    (128, 256, 700),     # streaming 128 x 64 / wavefront-private, two sibling wavefronts, with the fused gather
+    (64, 128, 200),      # wavefront-private, two row tiles / wavefront-private, sibling wavefronts
+    (32, 128, 200),      # wavefront-private, one row tile, 1 stage / wavefront-private
+    (32, 256, 200),      # ... 2 stages / wavefront-private
+    (32, 384, 200),      # ... 3 stages / resident-token
+    (32, 512, 200),      # ... 4 stages / resident-token
+    (96, 128, 200),      # wavefront-private, 3 row tiles / wavefront-private
+    (512, 128, 300),     # resident-token 256 x 64, one stage / resident-token 256 x 64, 4 stages
+    (1024, 192, 300),    # split 64 x 32, ragged / row-resident, weight rows split over the grid
+    (256, 124, 300),     # wavefront-private / resident-token 128 x 32, two stages
     (124, 128, 300),     # wavefront-private / resident-token 128 x 32, one stage, contraction 124
-    (512, 128, 16400),   # ... / row-resident <2,1> (at least 512 tiles of 32 tokens)
+    (512, 128, 16400),   # resident-token / row-resident <1,1> (at least 512 tiles of 32 tokens)
+    (512, 256, 16400),   # streaming 256 x 128 / row-resident <2,1>
     (384, 384, 16400),   # streaming 128 x 64 / row-resident <3,1>
-    (512, 512, 16400),   # streaming 256 x 64 / row-resident <2,2>
-    (1536, 384, 400),    # streaming / row-resident, 12 stages
-    (2048, 512, 600),    # streaming / row-resident <2,2>, 16 stages
-    (64, 576, 500),      # streaming 64 x 64 with a ragged last stage / resident-token 256 x 64
-    (64, 576, 66000),    # ... / resident-token 256 x 64, persistent
-    (256, 576, 66000),   # streaming 256 x 128 / resident-token 256 x 64 persistent, two stages
-    (256, 2304, 2400),   # streaming 256 x 64, 18 stages / resident-token, two stages
-    (384, 640, 700),     # streaming 128 x 64 (384 rows = 1.5 tiles of 256)
-    (2100, 64, 600),     # resident-token, ragged rows / separate gather, then streaming 64 x 64 with 17 stages
-    (1024, 1028, 300),   # streaming, ragged last stage / separate gather
-    (2560, 1024, 2600),  # streaming 256 x 128 both ways (the tile of the largest layers), separate gather
+    (512, 512, 16400),   # streaming 256 x 128 / row-resident <2,2>
+    (1536, 384, 400),    # split 64 x 64 / row-resident, 12 stages, weight rows split over the grid
+    (2048, 512, 600),    # streaming 128 x 64 / row-resident, 16 stages, weight rows split over the grid
+    (64, 576, 500),      # split 64 x 32, ragged / resident-token 256 x 64
+    (64, 576, 66000),    # streaming 64 x 64, ragged / resident-token 256 x 64, persistent
+    (64, 640, 9000),     # streaming 64 x 64, whole stages / resident-token
+    (64, 644, 9000),     # streaming 64 x 64, 4-byte rows / resident-token
+    (256, 576, 66000),   # streaming 256 x 128, ragged / resident-token 256 x 64 persistent, two stages
+    (256, 2304, 2400),   # split 64 x 64 / resident-token, two stages
+    (384, 640, 700),     # split 64 x 32 / resident-token, three stages
+    (384, 640, 2800),    # streaming 128 x 64 (384 rows = 1.5 tiles of 256), whole stages / resident-token
+    (384, 648, 2800),    # ... ragged
+    (384, 644, 2800),    # ... 4-byte rows
+    (256, 640, 12500),   # streaming 256 x 64, whole stages / resident-token
+    (256, 648, 12500),   # ... ragged
+    (256, 644, 12500),   # ... 4-byte rows
+    (512, 644, 12200),   # streaming 256 x 128, 4-byte rows / resident-token
+    (2100, 64, 600),     # resident-token, ragged rows / separate gather, then split 64 x 32 with 4-byte rows, 17 stages
+    (1024, 1028, 300),   # split 64 x 32, 4-byte rows / separate gather, then split 64 x 32
+    (2560, 1024, 2600),  # streaming 256 x 128 / separate gather, then streaming 256 x 64
     (4096, 2048, 8200),  # forward: 512 x 128 tiles (8 x 65 tiles, the last token tile ragged) / separate gather, streaming 256 x 128
     (3200, 1152, 22037), # 512 x 128 tiles both ways (the backward one behind the separate gather): 6.25 and 2.25 weight tiles, ragged last token tile
     (1024, 1152, 65600), # 512 x 128 tiles: two / three weight tiles, 513 token tiles (65 per XCD, the last XCD's run shorter)
-    (4352, 256, 2051),   # ... / separate gather with four token rows interleaved per tile (8.5 KB rows), ragged last tile
-    (8704, 128, 2305),   # ... / separate gather with two token rows interleaved per tile (17 KB rows), one row in the last tile
+    (4352, 256, 2051),   # resident-token / separate gather with four token rows interleaved per tile (8.5 KB rows), ragged last tile, split 64 x 64
+    (8704, 128, 2305),   # resident-token / separate gather with two token rows interleaved per tile (17 KB rows), one row in the last tile, split 64 x 32
     (4224, 1024, 11200), # 512 x 128 tiles: nine weight tiles (the last with 128 rows) x 88 token tiles, 99 tiles per XCD on 32 workgroups (3 or 4 each)
 ]
 
@@ -114,17 +131,26 @@ def test_other_ratios_on_the_sparse_cores_are_exact(N, M):
     exact_layer(64, 128, 200, N, M, synth.BF16, 7200 + M + N)
 
 
-@pytest.mark.parametrize("I,J,T", [(384, 384, 500), (1536, 384, 600), (384, 1536, 1600), (136, 1032, 1100), (64, 72, 80),
-                                   (1152, 384, 16400)])
+# dense operand: streaming tiles 64 x 64, 128 x 64 and 256 x 128 with whole and ragged stages (the split tiles are below); row-resident
+# with 1, 2, 3 row tiles per wavefront and 2 in two passes, contractions of 2 to 9 stages
+DENSE_SHAPES = [(384, 384, 500), (1536, 384, 600), (384, 1536, 1600), (136, 1032, 1100), (64, 72, 80), (1152, 384, 16400),
+                (64, 640, 9000), (64, 648, 9000), (384, 640, 2800), (384, 648, 2800), (512, 640, 12200), (512, 648, 12200),
+                (256, 128, 300), (384, 256, 700), (520, 512, 300), (648, 256, 300)]
+
+
+@pytest.mark.parametrize("I,J,T", DENSE_SHAPES)
 @pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
 def test_dense_core_gemms_4of8_are_exact(I, J, T, perm):
     exact_layer(I, J, T, 4, 8, synth.BF16, 7300 + I + J, perm=perm)
 
 
-# few output tiles: the contraction split over groups of wavefronts (64 x 32 tiles by 4, 64 x 64 by 2): one stage per group
-# and fewer, whole and partial last steps, ragged rows, tokens and stages, token rows of 16-byte pitch and of 8-byte pitch
-@pytest.mark.parametrize("I,J,T", [(68, 132, 35), (64, 260, 70), (136, 136, 37), (192, 648, 165), (512, 1152, 290), (1000, 520, 251),
-                                   (64, 4096, 1030), (1024, 1024, 1000), (960, 904, 1001), (900, 908, 1023)])
+# few output tiles: the contraction split over groups of wavefronts (64 x 32 tiles by 4, 64 x 64 by 2): two stages and three, whole and
+# partial last steps, ragged rows, tokens and stages, token rows of 16-byte pitch and of 8-byte pitch
+SPLIT_SHAPES = [(68, 132, 35), (64, 260, 70), (136, 136, 37), (192, 648, 165), (512, 1152, 290), (1000, 520, 251),
+                (64, 4096, 1030), (1024, 1024, 1000), (960, 904, 1001), (900, 908, 1023)]
+
+
+@pytest.mark.parametrize("I,J,T", SPLIT_SHAPES)
 @pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
 def test_split_contractions_are_exact(I, J, T, perm):
     exact_layer(I, J, T, 2, 4, synth.BF16, 7700 + I + J, perm=perm)
@@ -136,10 +162,13 @@ def test_tiles_of_256_x_64_stay_exact_where_the_tiles_fill_the_chip():
     exact_layer(256, 640, 12500, 2, 4, synth.BF16, 7900)
 
 
+F32_SMALL = [(64, 128, 40), (136, 264, 300)]
+
+
 @pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
 def test_fp32_gemms_are_exact(N, M):
-    exact_layer(64, 128, 40, N, M, synth.F32, 7400 + M)
-    exact_layer(136, 264, 300, N, M, synth.F32, 7500 + M)
+    for q, (I, J, T) in enumerate(F32_SMALL):
+        exact_layer(I, J, T, N, M, synth.F32, 7400 + 100 * q + M)
 
 
 # 16 x 16 tiles; 1 / 2 / 4 / 8 / 16 wavefronts by contraction length and tile count; gather in the token loads or as a pass; 64 weight
@@ -153,6 +182,17 @@ F32_SHAPES = [(8, 8, 5), (16, 136, 37), (40, 264, 70), (520, 24, 131), (264, 520
 @pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
 def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
     exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
+
+
+def exact_products():
+    """(I, J, T, N, M, dtype) of every layer above; each with and without a permutation."""
+    for shape in SP24_SHAPES + SPLIT_SHAPES:
+        yield *shape, 2, 4, synth.BF16
+    for shape in DENSE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
+        yield *shape, 4, 8, synth.BF16
+    for shape in F32_SMALL + F32_SHAPES:
+        yield *shape, 2, 4, synth.F32
+        yield *shape, 4, 8, synth.F32
 
 
 @pytest.mark.parametrize("I,J,T", [(40, 72, 37), (72, 40, 50), (264, 136, 300), (136, 72, 33000)])
