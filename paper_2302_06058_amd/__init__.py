@@ -141,8 +141,17 @@ def workspace_bytes(kind: int, I: int, J: int, T: int, K: int, dtype: int, N: in
     return int(lib().bimask_workspace_bytes(kind, I, J, T, K, dtype, N, M))
 
 
+_PLAIN_TYPES: set = set()
+
+
 def _empty(shape, dtype, like):
-    return like.new_empty(shape, dtype=dtype)
+    """A plain tensor on the device of `like`.  new_empty makes one of a plain tensor; of a subclass it makes the subclass, and it
+    refuses a tensor with named dimensions."""
+    if type(like) in _PLAIN_TYPES and not like.has_names():
+        return like.new_empty(shape, dtype=dtype)
+    import torch
+    _PLAIN_TYPES.update((torch.Tensor, torch.nn.Parameter))
+    return torch.empty(shape, dtype=dtype, device=like.device)
 
 
 def _empty_i32(shape, like):
@@ -205,7 +214,7 @@ def bimask_forward_mask_compress(W, N: int, M: int, B_bits=None, values=None, in
     if B_bits is None:
         B_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = W.new_empty(_values_shape(I, J, N, M))
+        values = _empty(_values_shape(I, J, N, M), W.dtype, W)
     if index is None and N <= 2:
         index = _empty_i32(_index_shape(I, J, N, M), W)
     _check("bimask_forward_mask_compress",
@@ -302,7 +311,7 @@ def bimask_backward_mask_compress(W, N: int, M: int, B_bits, perm=None, Bbar_bit
     if Bbar_bits is None:
         Bbar_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = W.new_empty(_values_shape(J, I, N, M))
+        values = _empty(_values_shape(J, I, N, M), W.dtype, W)
     if index is None and N <= 2:
         index = _empty_i32(_index_shape(J, I, N, M), W)
     _check("bimask_backward_mask_compress",
@@ -332,7 +341,7 @@ def bimask_sparse_gemm_fwd(X, Wf_values, Wf_index, I: int, J: int, N: int, M: in
     T = X.shape[0]
     ldx = _rowmajor(X)
     if Y is None:
-        Y = X.new_empty((T, I))
+        Y = _empty((T, I), X.dtype, X)
     ldy = _rowmajor(Y)
     wsb = _nbytes(workspace)
     _check("bimask_sparse_gemm_fwd",
@@ -346,7 +355,7 @@ def bimask_sparse_gemm_bwd(dY, perm, Wb_values, Wb_index, I: int, J: int, N: int
     T = dY.shape[0]
     lddy = _rowmajor(dY)
     if dX is None:
-        dX = dY.new_empty((T, J))
+        dX = _empty((T, J), dY.dtype, dY)
     lddx = _rowmajor(dX)
     if workspace is None and perm is not None:
         import torch

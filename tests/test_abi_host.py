@@ -110,6 +110,21 @@ def test_argument_errors_are_reported_before_any_launch(call, args, want):
     assert getattr(bm.lib(), call)(*args) == want
 
 
+@pytest.mark.filterwarnings("ignore:Named tensors")
+def test_outputs_are_plain_tensors_whatever_the_inputs_are():
+    """Outputs that the wrappers allocate: torch.Tensor without names, for a subclass, a Parameter and a tensor with named dimensions."""
+    import torch
+
+    class Sub(torch.Tensor):
+        pass
+
+    base = torch.zeros((2, 3), dtype=torch.bfloat16)
+    for like in (base, base.as_subclass(Sub), torch.nn.Parameter(base), base.rename("T", "J")):
+        out = bm._empty((4, 5), torch.int32, like)
+        assert type(out) is torch.Tensor and out.shape == (4, 5) and out.dtype == torch.int32 and out.names == (None, None)
+        assert not out.requires_grad and out.device == like.device
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(bm, "_lib", None)
     monkeypatch.setattr(bm, "LIB_PATH", "/nonexistent/libbimask.so")
