@@ -192,7 +192,8 @@ BIMASK_API int bimask_sparse_gemm_fwd(const void *X, int64_t T, int64_t ldx, con
  *   permutation that ask for a workspace (dY is then copied first).
  *   workspace: bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, ...) bytes (holds dY[:,P], or for
  *   N > 2 the weights with their columns in natural order, when the gather is not fused into the
- *   GEMM; 0 = none needed).  bf16 with N <= 2 fuses it for
+ *   GEMM; 0 = none needed; fp32 with a permutation always needs it, small products leave it
+ *   untouched).  bf16 with N <= 2 fuses it for
  *   I <= 512 and for 512 < I <= 2048 with J <= min(I, 512), I and J multiples of 8; bf16 with
  *   N > 2 for 128 < I <= 2048 with J <= min(I, 512), I and J multiples of 8.  Apart from the
  *   N <= 2, I <= 512 range these move rows in 16-byte pieces: dY, dX 16-byte aligned, lddy, lddx

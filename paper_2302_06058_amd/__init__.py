@@ -145,13 +145,16 @@ _PLAIN_TYPES: set = set()
 
 
 def _empty(shape, dtype, like):
-    """A plain tensor on the device of `like`.  new_empty makes one of a plain tensor; of a subclass it makes the subclass, and it
-    refuses a tensor with named dimensions."""
-    if type(like) in _PLAIN_TYPES and not like.has_names():
-        return like.new_empty(shape, dtype=dtype)
+    """A plain tensor on the device of `like` (dtype None: of its type).  new_empty makes one of a plain tensor; of a subclass it
+    makes the subclass, and it raises for a tensor with named dimensions."""
+    if type(like) in _PLAIN_TYPES:
+        try:
+            return like.new_empty(shape, dtype=dtype) if dtype else like.new_empty(shape)
+        except RuntimeError:
+            pass
     import torch
     _PLAIN_TYPES.update((torch.Tensor, torch.nn.Parameter))
-    return torch.empty(shape, dtype=dtype, device=like.device)
+    return torch.empty(shape, dtype=dtype or like.dtype, device=like.device)
 
 
 def _empty_i32(shape, like):
@@ -214,7 +217,7 @@ def bimask_forward_mask_compress(W, N: int, M: int, B_bits=None, values=None, in
     if B_bits is None:
         B_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = _empty(_values_shape(I, J, N, M), W.dtype, W)
+        values = _empty(_values_shape(I, J, N, M), None, W)
     if index is None and N <= 2:
         index = _empty_i32(_index_shape(I, J, N, M), W)
     _check("bimask_forward_mask_compress",
@@ -311,7 +314,7 @@ def bimask_backward_mask_compress(W, N: int, M: int, B_bits, perm=None, Bbar_bit
     if Bbar_bits is None:
         Bbar_bits = _empty_i32((I, mask_words(J)), W)
     if values is None:
-        values = _empty(_values_shape(J, I, N, M), W.dtype, W)
+        values = _empty(_values_shape(J, I, N, M), None, W)
     if index is None and N <= 2:
         index = _empty_i32(_index_shape(J, I, N, M), W)
     _check("bimask_backward_mask_compress",
@@ -341,7 +344,7 @@ def bimask_sparse_gemm_fwd(X, Wf_values, Wf_index, I: int, J: int, N: int, M: in
     T = X.shape[0]
     ldx = _rowmajor(X)
     if Y is None:
-        Y = _empty((T, I), X.dtype, X)
+        Y = _empty((T, I), None, X)
     ldy = _rowmajor(Y)
     wsb = _nbytes(workspace)
     _check("bimask_sparse_gemm_fwd",
@@ -355,7 +358,7 @@ def bimask_sparse_gemm_bwd(dY, perm, Wb_values, Wb_index, I: int, J: int, N: int
     T = dY.shape[0]
     lddy = _rowmajor(dY)
     if dX is None:
-        dX = _empty((T, J), dY.dtype, dY)
+        dX = _empty((T, J), None, dY)
     lddx = _rowmajor(dX)
     if workspace is None and perm is not None:
         import torch

@@ -384,11 +384,12 @@ k_forward24_group(const GroupTable<FwdGroupP> g, int N) {
 // ---------------------------------------------------------------------------------
 // Backward direction: a workgroup owns a tile of 128 permuted rows x TC columns (TC = 128,
 // or 32 for small matrices so that enough workgroups exist); a thread owns one block of M
-// permuted rows x QC columns: 8, or 2 in the 32-column tiles.  A small matrix is bound by the serial
-// selection of one thread, not by bytes: with 8 columns a 128 x 32 tile kept 64 (M = 8) or 128 (M = 4) of
-// its 256 threads busy.  1536 x 384 at 4:8 13.0 -> 7.4 us, 64 x 128 in fp32 6.9 -> 5.0 us.  Rows of W are gathered through P, every row read is a
-// contiguous 2*TC-byte (bf16) segment.  Transposed outputs go through LDS so
+// permuted rows x QC columns (8, or 2 in the 32-column tiles).  Rows of W are gathered through P,
+// every row read is a contiguous 2*TC-byte (bf16) segment.  Transposed outputs go through LDS so
 // that they leave as contiguous runs along the permuted-row axis.
+// A small matrix is bound by the serial selection of one thread, not by bytes: with 8 columns a
+// 128 x 32 tile kept 64 (M = 8) or 128 (M = 4) of its 256 threads busy; with 2 columns 1536 x 384
+// at 4:8 takes 7.4 us instead of 13.0, 64 x 128 in fp32 5.0 instead of 6.9.
 //   MODE 0: Bbar only   1: + transposed 2-of-4 values/index (N <= 2)   2: + transposed dense masked
 // Bbar_in != nullptr: Bbar is read instead of selected (stand-alone compression).
 // ---------------------------------------------------------------------------------

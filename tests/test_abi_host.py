@@ -123,6 +123,8 @@ def test_outputs_are_plain_tensors_whatever_the_inputs_are():
         out = bm._empty((4, 5), torch.int32, like)
         assert type(out) is torch.Tensor and out.shape == (4, 5) and out.dtype == torch.int32 and out.names == (None, None)
         assert not out.requires_grad and out.device == like.device
+        out = bm._empty((4,), None, like)
+        assert type(out) is torch.Tensor and out.dtype == torch.bfloat16 and out.names == (None,) and not out.requires_grad
 
 
 def test_missing_library_fails_loudly(monkeypatch):
