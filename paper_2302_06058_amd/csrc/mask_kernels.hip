@@ -384,12 +384,13 @@ k_forward24_group(const GroupTable<FwdGroupP> g, int N) {
 // ---------------------------------------------------------------------------------
 // Backward direction: a workgroup owns a tile of 128 permuted rows x TC columns (TC = 128,
 // or 32 for small matrices so that enough workgroups exist); a thread owns one block of M
-// permuted rows x QC columns (8, or 2 in the 32-column tiles).  Rows of W are gathered through P,
-// every row read is a contiguous 2*TC-byte (bf16) segment.  Transposed outputs go through LDS so
-// that they leave as contiguous runs along the permuted-row axis.
-// A small matrix is bound by the serial selection of one thread, not by bytes: with 8 columns a
-// 128 x 32 tile kept 64 (M = 8) or 128 (M = 4) of its 256 threads busy; with 2 columns 1536 x 384
-// at 4:8 takes 7.4 us instead of 13.0, 64 x 128 in fp32 5.0 instead of 6.9.
+// permuted rows x QC columns (8; in the 32-column tiles 2, or 4 for M = 4 and more than 64 rows).  Rows of
+// W are gathered through P, every row read is a contiguous 2*TC-byte (bf16) segment.  Transposed outputs
+// go through LDS so that they leave as contiguous runs along the permuted-row axis.
+// A small matrix is bound by the serial selection of one thread and by rounds of loads, not by bytes: the
+// columns per thread are what gives all 256 threads one block each.  With 8 a 128 x 32 tile kept 64 (M = 8)
+// or 128 (M = 4) of them busy, with 2 and M = 4 it takes two rounds: 1536 x 384 at 4:8 13.0 us with 8
+// columns, 7.4 with 2; in fp32 at 2:4 512 x 512 6.2 us with 2, 5.2 with 4, 64 x 128 4.3 / 4.7.
 //   MODE 0: Bbar only   1: + transposed 2-of-4 values/index (N <= 2)   2: + transposed dense masked
 // Bbar_in != nullptr: Bbar is read instead of selected (stand-alone compression).
 // ---------------------------------------------------------------------------------
@@ -399,22 +400,28 @@ constexpr int kTR = 128;   // permuted rows per tile = one 128-deep stage of the
 template <int TC> __host__ __device__ constexpr int img_elems() { return TC / 32 * 2048; }
 template <typename DT> __host__ __device__ constexpr int lds_stride_m2() { return kTR + 16 / (int)sizeof(typename DT::raw); }
 
-// two neighbouring entries of a row (vec: the row starts 16-byte aligned, and the first index is even)
-template <typename DT>
-__device__ __forceinline__ void load2(const typename DT::raw* p, bool vec, uint32_t (&w)[Pack<DT>::kWords]) {
-    if constexpr (sizeof(typename DT::raw) == 2) {
-        w[0] = vec ? *reinterpret_cast<const uint32_t*>(p) : static_cast<uint32_t>(p[0]) | static_cast<uint32_t>(p[1]) << 16;
-    } else {
-        if (vec) {
+// Q = 2 or 4 neighbouring entries of a row (vec: the row starts 16-byte aligned, and the first index is a multiple of Q)
+template <typename DT, int Q>
+__device__ __forceinline__ void load_few(const typename DT::raw* p, bool vec, uint32_t (&w)[Pack<DT>::kWords]) {
+    constexpr int W = Q * (int)sizeof(typename DT::raw) / 4;             // words: 1, 2 or 4
+    if (vec) {
+        if constexpr (W == 1) w[0] = *reinterpret_cast<const uint32_t*>(p);
+        else if constexpr (W == 2) {
             const uint2 v = *reinterpret_cast<const uint2*>(p);
             w[0] = v.x; w[1] = v.y;
         } else {
-            w[0] = p[0]; w[1] = p[1];
+            const uint4 v = *reinterpret_cast<const uint4*>(p);
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
         }
+    } else {
+#pragma unroll
+        for (int d = 0; d < W; ++d)
+            if constexpr (sizeof(typename DT::raw) == 2) w[d] = static_cast<uint32_t>(p[2 * d]) | static_cast<uint32_t>(p[2 * d + 1]) << 16;
+            else w[d] = p[d];
     }
 }
 
-template <typename DT, int M, int TC>
+template <typename DT, int M, int TC, int QC>
 __device__ __forceinline__ void
 backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t ldw, int N,
               const uint32_t* __restrict__ B_bits, const uint32_t* __restrict__ Bbar_in,
@@ -427,14 +434,13 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
     extern __shared__ uint4 lds_u4[];
     raw* lds_val = reinterpret_cast<raw*>(lds_u4);
     constexpr int S2 = lds_stride_m2<DT>();
-    constexpr int QC = TC == 32 ? 2 : 8;                // columns per thread
-    constexpr int CPT = TC / QC;                        // column chunks per tile row
+    constexpr int CPT = TC / QC;                        // column chunks per tile row (QC: columns per thread)
     uint8_t* lds_meta = reinterpret_cast<uint8_t*>(lds_val + img_elems<TC>());  // mode 1 only: [TC][32] nibbles
 
     const int64_t r0 = static_cast<int64_t>(block_y) * kTR;
     const int64_t c0 = static_cast<int64_t>(block_x) * TC;
     const int ch = threadIdx.x % CPT;
-    const int64_t j0 = c0 + ch * QC;                    // J is a multiple of 4: two columns are both in or both out
+    const int64_t j0 = c0 + ch * QC;                    // J is a multiple of 4: the columns are all in or all out
     const int sh = QC == 8 ? 0 : static_cast<int>(j0 & 7);               // their place in the mask byte
 
     if (mode == 1) {                                    // padding of the operand image is zero
@@ -460,7 +466,7 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
             for (int m = 0; m < M; ++m) {
                 const int64_t src = perm ? static_cast<int64_t>(perm[rb + m]) : rb + m;
                 if constexpr (QC == 8) load8<DT>(W + src * ldw, j0, J, vec_in, w[m]);
-                else load2<DT>(W + src * ldw + j0, vec_in, w[m]);
+                else load_few<DT, QC>(W + src * ldw + j0, vec_in, w[m]);
                 bb[m] = (Bbar_in ? reinterpret_cast<const uint8_t*>(Bbar_in)[(rb + m) * wpr * 4 + (j0 >> 3)]
                                  : reinterpret_cast<const uint8_t*>(B_bits)[src * wpr * 4 + (j0 >> 3)]) >> sh;
             }
@@ -520,12 +526,12 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
                 }
             }
         }
-        if constexpr (QC == 2) {                         // four neighbouring lanes share a mask byte (same kb, all here)
+        if constexpr (QC < 8) {                          // 8 / QC neighbouring lanes share a mask byte (same kb, all here)
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 ob[m] <<= sh;
                 ob[m] |= __shfl_xor(ob[m], 1);
-                ob[m] |= __shfl_xor(ob[m], 2);
+                if constexpr (QC == 2) ob[m] |= __shfl_xor(ob[m], 2);
             }
         }
         if (Bbar_bits && sh == 0 && j0 < static_cast<int64_t>(wpr) * 32) {
@@ -583,8 +589,13 @@ k_backward(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t
            const int32_t* __restrict__ perm, uint32_t* __restrict__ Bbar_bits,
            typename DT::raw* __restrict__ values, uint32_t* __restrict__ index, int mode,
            int wpr, bool vec_in, bool vec_out) {
-    backward_body<DT, M, TC>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, wpr, vec_in, vec_out,
-                             blockIdx.x, blockIdx.y);
+#define BIMASK_BODY(QC) backward_body<DT, M, TC, QC>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, wpr, \
+                                                     vec_in, vec_out, blockIdx.x, blockIdx.y)
+    if constexpr (TC != 32) BIMASK_BODY(8);
+    else if constexpr (M != 4) BIMASK_BODY(2);
+    else if (I - static_cast<int64_t>(blockIdx.y) * kTR <= kTR / 2) BIMASK_BODY(2);
+    else BIMASK_BODY(4);
+#undef BIMASK_BODY
 }
 
 struct BwdGenGroupP {
@@ -607,9 +618,14 @@ k_backward_group(const GroupTable<BwdGenGroupP> g, int N, int mode) {
     const int l = group_layer_of(g, blockIdx.x);
     const BwdGenGroupP& p = g.p[l];
     const unsigned local = blockIdx.x - g.first[l];
-    backward_body<DT, M, 32>(static_cast<const raw*>(p.W), p.I, p.J, p.ldw, N, p.B_bits, nullptr, p.perm, p.Bbar_bits,
-                             static_cast<raw*>(p.values), p.index, mode, p.wpr, p.vec_in != 0, p.vec_out != 0,
-                             local % p.gx, local / p.gx);
+    const unsigned bx = local % p.gx, by = local / p.gx;
+#define BIMASK_BODY(QC) backward_body<DT, M, 32, QC>(static_cast<const raw*>(p.W), p.I, p.J, p.ldw, N, p.B_bits, nullptr, p.perm, \
+                                                     p.Bbar_bits, static_cast<raw*>(p.values), p.index, mode, p.wpr, p.vec_in != 0, \
+                                                     p.vec_out != 0, bx, by)
+    if constexpr (M != 4) BIMASK_BODY(2);
+    else if (p.I - static_cast<int64_t>(by) * kTR <= kTR / 2) BIMASK_BODY(2);
+    else BIMASK_BODY(4);
+#undef BIMASK_BODY
 }
 
 // ---------------------------------------------------------------------------------

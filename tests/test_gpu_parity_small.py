@@ -152,21 +152,22 @@ def test_adversarial_values(dtype, kind):
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
-@pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (1, 16), (7, 16)])
+@pytest.mark.parametrize("N,M", [(2, 4), (3, 4), (4, 8), (1, 16), (7, 16)])
 def test_backward_column_pairs(dtype, N, M):
-    # two columns per thread, a mask byte put together by four lanes: every remainder of J in a mask byte and word,
-    # one row block beyond a tile of 128, rows that start on an odd element (no vector loads)
-    for J in (M, 32 + M, 96 - M):
-        check_layer(I=128 + M, J=J, N=N, M=M, dtype=dtype, K=2, seed=430 + M + J, kind="integers" if J == M else "normal")
-        W = to_dev(make_w(128 + M, J, dtype, 440 + J), dtype)
-        wide = torch.zeros((128 + M, J + 3), dtype=W.dtype, device=W.device)
+    # two columns per thread, or four (M = 4, more than 64 rows in the tile), a mask byte put together by four lanes or two: every
+    # remainder of J in a mask byte and word, tiles of 64 rows, one block more, and one block beyond 128, rows that start on an
+    # odd element (no vector loads)
+    for I, J in [(128 + M, J) for J in (M, 32 + M, 96 - M)] + [(64, 32 + M), (64 + M, 32 + M)]:
+        check_layer(I=I, J=J, N=N, M=M, dtype=dtype, K=2, seed=430 + M + J, kind="integers" if J == M else "normal")
+        W = to_dev(make_w(I, J, dtype, 440 + J), dtype)
+        wide = torch.zeros((I, J + 3), dtype=W.dtype, device=W.device)
         wide[:, 1:J + 1] = W
-        P = i32_dev(perms_of(128 + M, 1, 441))[0]
+        P = i32_dev(perms_of(I, 1, 441))[0]
         B = bm.bimask_forward_mask(W, N, M)
         a = bm.bimask_backward_mask_compress(W, N, M, B, P)
         b = bm.bimask_backward_mask_compress(wide[:, 1:J + 1], N, M, B, P)
         for x, y in zip(a, b):
-            assert (x is None and y is None) or torch.equal(x, y), (N, M, J)
+            assert (x is None and y is None) or torch.equal(x, y), (N, M, I, J)
 
 
 @pytest.mark.parametrize("I,J,N,M", [(136, 128, 4, 8), (520, 8, 4, 8), (264, 136, 3, 8), (392, 264, 4, 8), (640, 384, 4, 8), (1000, 392, 4, 8),
