@@ -414,7 +414,9 @@ int launch_gemm_dense_frag(const void* A, int64_t Adim, int64_t K, const void* B
                            int64_t ldc, hipStream_t s) {
     if (!aligned16(A) || !aligned16(Bm) || (ldb * 2) % 16 != 0 || K % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
     // few tiles: a single stage, or up to two with at most 64 rows, gains nothing from the split (512 x 128 at 256 tokens 4.2 us,
-    // split 4.5; 64 x 256 at 784 3.8 / 4.4), longer contractions do (64 x 512 at 784 4.9 -> 4.6, 512 x 264 at 256 5.7 -> 4.6)
+    // split 4.5; 64 x 256 at 784 3.8 / 4.4), longer contractions do (64 x 512 at 784 4.9 -> 4.6, 512 x 264 at 256 5.7 -> 4.6).
+    // Beyond 256 tiles only the deepest would (512 x 2304 at 1088 tokens 15.1 us, split 14.7, 512 x 1152 9.3 / 11.0, 512 x 4608
+    // 27.5 / 24.2): not worth an instance of the 64 x 64 split.
     if (K > (Adim <= 64 ? 256 : 128) && gemm_few_tiles(Adim, T))
         return run_dense_frag<64, 32, 2, 1, 1, 4>(A, Adim, K, Bm, T, ldb, C, ldc, s);
     if (Adim <= 64) return run_dense_frag<64, 64, 2, 2, 2>(A, Adim, K, Bm, T, ldb, C, ldc, s);
