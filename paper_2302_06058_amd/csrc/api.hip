@@ -1,7 +1,6 @@
 // extern "C" boundary of the Bi-Mask library: argument validation on the host, then
 // kernel launches on the caller's stream.  See include/bimask.h for the contract.
 #include "common.hpp"
-#include <cstdlib>
 
 using namespace bimask;
 
@@ -236,16 +235,20 @@ int bimask_sparse_gemm_bwd(const void* dY, int64_t T, int64_t lddy, const int32_
             return launch_gemm_sp24_resident(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream));
         // rows of g(Y) that fit LDS whole: gather fused as well, rows move in 16-byte pieces
         if (!aligned16(dY) || !aligned16(dX) || lddy % 8 || lddx % 8) return BIMASK_ERR_ALIGN;
-        return launch_gemm_sp24_rowres(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
+        return launch_gemm_sp24_coltile(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
     }
     if (perm) {
         const size_t need = bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, I, J, T, 0, dtype, N, M);
         if (!workspace || workspace_bytes < need) return BIMASK_ERR_WORKSPACE;
         if (!aligned16(workspace)) return BIMASK_ERR_ALIGN;
-        // These two read dY while dX is written; dX on top of dY (in place, I = J) takes the copy of dY in the workspace.
+        // These read dY while dX is written; dX on top of dY (in place, I = J) takes the copy of dY in the workspace.
         const bool apart = disjoint(dY, T, lddy, I, dX, lddx, J, esize(dtype));
         if (apart && dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
             return launch_gemm_f32(Wb_values, Wb_index, J, I, sp, dY, T, lddy, perm, dX, lddx, as_stream(stream));
+        if (apart && dtype == BIMASK_BF16) {
+            const int rc = launch_gemm_sp24_coltile(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
+            if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
+        }
         if (apart && dtype == BIMASK_BF16 && !sp && gemm_dense_unpermutes(dY, T, lddy, J, I)) {
             if (int rc = launch_unpermute_dense(Wb_values, J, I, perm, workspace, as_stream(stream))) return rc;
             return launch_gemm(workspace, nullptr, J, I, false, dY, T, lddy, dX, lddx, dtype, as_stream(stream));

@@ -191,12 +191,10 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
 // wavefront-private variant for narrow weights (Adim <= 256 with K <= 128, Adim <= 64 with K <= 256); BIMASK_ERR_UNSUPPORTED otherwise
 int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
                             int64_t ldb, const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s);
-// backward GEMM with whole rows of g(Y) resident in LDS (512 < K <= 2048, Adim <= 512): gather fused;
-// BIMASK_ERR_UNSUPPORTED otherwise
-// (dense: the weight operand is the dense masked matrix of a ratio with N > 2, meta unused)
-int launch_gemm_sp24_rowres(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
-                            int64_t ldb, const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s,
-                            bool dense = false);
+// backward GEMM on token tiles turned column by column in LDS (128 < K <= 2048), gather fused; BIMASK_ERR_UNSUPPORTED outside what it
+// takes and where another kernel is the faster (dense: the weight operand is the dense masked matrix of a ratio with N > 2, meta unused)
+int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
+                             const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s, bool dense);
 // true when the backward GEMM needs the gathered copy of g(Y) in the workspace
 // Debug helper: one flag per candidate, 1 = a permutation of 0 .. I-1 (bitmap of I bits in LDS).
 constexpr int64_t kCheckPermsMaxRows = 1 << 20;
@@ -207,9 +205,9 @@ int launch_perm_refine(const uint32_t* B_bits, int64_t I, int64_t J, int N, int 
                        const int32_t* swaps, int64_t S, int32_t* perm_out, int32_t* result, hipStream_t s);
 int launch_perm_refine_group(const bimask_group_layer* L, int n, int N, int M, hipStream_t s);
 bool gemm_bwd_needs_gather(int64_t I, int64_t J, int dtype, int N, int M);
-// Shapes (output rows Adim, contraction K) the row-resident backward kernel takes.
-bool gemm_sp24_rowres_shape(int64_t Adim, int64_t K);
+// Shapes (output rows Adim, contraction K) that kernel always takes: no other kernel has the gather fused for them.
+bool gemm_sp24_coltile_shape(int64_t Adim, int64_t K);
 // The same for dense masked weights (N > 2), which have no other fused path: 128 < K <= 2048, Adim <= min(K, 512).
-bool gemm_dense_rowres_shape(int64_t Adim, int64_t K);
+bool gemm_dense_coltile_shape(int64_t Adim, int64_t K);
 
 }  // namespace bimask

@@ -589,8 +589,8 @@ int launch_unpermute_dense(const void* values, int64_t J, int64_t I, const int32
 
 bool gemm_bwd_needs_gather(int64_t I, int64_t J, int dtype, int N, int M) {
     if (dtype != BIMASK_BF16) return true;
-    if (!uses_sp24(N, M)) return !gemm_dense_rowres_shape(J, I);
-    return !(I <= 512 || gemm_sp24_rowres_shape(J, I));
+    if (!uses_sp24(N, M)) return !gemm_dense_coltile_shape(J, I);
+    return !(I <= 512 || gemm_sp24_coltile_shape(J, I));
 }
 
 int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int64_t K, bool sparse24,

@@ -351,15 +351,12 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
                               hipStream_t s) {
     if (K > 512) return BIMASK_ERR_UNSUPPORTED;
     if (!aligned16(A) || !aligned16(meta)) return BIMASK_ERR_ALIGN;
-    {   // narrow weights: one wavefront per token tile, weights in registers
-        const int rc = launch_gemm_sp24_narrow(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
+    if (perm) {                                          // Eq. (10)'s gather: a token tile turned column by column, where it gains
+        const int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
     }
-    if (perm && K > 128 && ceil_div(T, 32) >= 512) {
-        // Eq. (10)'s gather with many tokens: whole rows of g(Y) in LDS, 16-32 rows per workgroup (512 x 128
-        // backward at 50176 tokens 41 -> 29 us, 384 x 384 at 25216 tokens 22 -> 20 us; fewer tokens: 512 x 512
-        // at 12544 was 15 -> 16.5 us, hence the bound); takes aligned operands only, else the kernels below
-        const int rc = launch_gemm_sp24_rowres(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
+    {   // narrow weights: one wavefront per token tile, weights in registers
+        const int rc = launch_gemm_sp24_narrow(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
     }
     const int nstg = static_cast<int>(ceil_div(K, 128));

@@ -84,15 +84,15 @@ SP24_SHAPES = [
     (32, 512, 200),      # ... 4 stages / resident-token
     (96, 128, 200),      # wavefront-private, 3 row tiles / wavefront-private
     (512, 128, 300),     # resident-token 256 x 64, one stage / resident-token 256 x 64, 4 stages
-    (1024, 192, 300),    # split 64 x 32, ragged / row-resident, weight rows split over the grid
+    (1024, 192, 300),    # split 64 x 32, ragged / column tile
     (256, 124, 300),     # wavefront-private / resident-token 128 x 32, two stages
     (124, 128, 300),     # wavefront-private / resident-token 128 x 32, one stage, contraction 124
-    (512, 128, 16400),   # resident-token / row-resident <1,1> (at least 512 tiles of 32 tokens)
-    (512, 256, 16400),   # streaming 256 x 128 / row-resident <2,1>
-    (384, 384, 16400),   # streaming 128 x 64 / row-resident <3,1>
-    (512, 512, 16400),   # streaming 256 x 128 / row-resident <2,2>
-    (1536, 384, 400),    # split 64 x 64 / row-resident, 12 stages, weight rows split over the grid
-    (2048, 512, 600),    # streaming 128 x 64 / row-resident, 16 stages, weight rows split over the grid
+    (512, 128, 16400),   # resident-token / column tile
+    (512, 256, 16400),   # streaming 256 x 128 / column tile
+    (384, 384, 16400),   # streaming 128 x 64 / column tile
+    (512, 512, 16400),   # streaming 256 x 128 / column tile
+    (1536, 384, 400),    # split 64 x 64 / column tile, 12 stages
+    (2048, 512, 600),    # streaming 128 x 64 / column tile, 16 stages
     (64, 576, 500),      # split 64 x 32, ragged / resident-token 256 x 64
     (64, 576, 66000),    # streaming 64 x 64, ragged / resident-token 256 x 64, persistent
     (64, 640, 9000),     # streaming 64 x 64, whole stages / resident-token
@@ -131,8 +131,8 @@ def test_other_ratios_on_the_sparse_cores_are_exact(N, M):
     exact_layer(64, 128, 200, N, M, synth.BF16, 7200 + M + N)
 
 
-# dense operand: streaming tiles 64 x 64, 128 x 64 and 256 x 128 with whole and ragged stages (the split tiles are below); row-resident
-# with 1, 2, 3 row tiles per wavefront and 2 in two passes, contractions of 2 to 9 stages
+# dense operand: streaming tiles 64 x 64, 128 x 64 and 256 x 128 with whole and ragged stages (the split tiles are below); column tiles
+# with contractions of 2 to 9 stages
 DENSE_SHAPES = [(384, 384, 500), (1536, 384, 600), (384, 1536, 1600), (136, 1032, 1100), (64, 72, 80), (1152, 384, 16400),
                 (64, 640, 9000), (64, 648, 9000), (384, 640, 2800), (384, 648, 2800), (512, 640, 12200), (512, 648, 12200),
                 (256, 128, 300), (384, 256, 700), (520, 512, 300), (648, 256, 300)]
@@ -156,6 +156,20 @@ def test_split_contractions_are_exact(I, J, T, perm):
     exact_layer(I, J, T, 2, 4, synth.BF16, 7700 + I + J, perm=perm)
     if I % 8 == 0 and J % 8 == 0:
         exact_layer(I, J, T, 4, 8, synth.BF16, 7800 + I + J, perm=perm)
+
+
+# Backward on column tiles: 1, 2, 3 row tiles per wavefront, up to 32 and up to 64 tokens, few and many pieces per fetching thread;
+# contractions of 2 (136 terms) to 16 stages, even and odd, ragged in the last one; one tile per workgroup and up to seven, the
+# last one short; a last workgroup and a last row of four tokens that are not full; pieces of weight rows over the grid; 8 outputs
+COLTILE_SHAPES = [(136, 8, 37), (136, 8, 8200), (136, 136, 8200), (136, 264, 8200), (160, 392, 2049), (144, 136, 5001), (160, 264, 5001),
+                  (264, 264, 5001), (264, 264, 8200), (384, 136, 1101), (640, 64, 2050), (648, 8, 12301), (648, 520, 5001), (648, 776, 5001),
+                  (1000, 264, 3000), (1152, 384, 16390), (1536, 264, 3000), (1536, 776, 2049), (1800, 136, 2049), (2048, 512, 8203), (512, 128, 60001)]
+
+
+@pytest.mark.parametrize("I,J,T", COLTILE_SHAPES)
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
+def test_column_tiles_are_exact(I, J, T, N, M):
+    exact_layer(I, J, T, N, M, synth.BF16, 7950 + I + J)
 
 
 def test_tiles_of_256_x_64_stay_exact_where_the_tiles_fill_the_chip():
@@ -186,9 +200,9 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
 
 def exact_products():
     """(I, J, T, N, M, dtype) of every layer above; each with and without a permutation."""
-    for shape in SP24_SHAPES + SPLIT_SHAPES:
+    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES:
         yield *shape, 2, 4, synth.BF16
-    for shape in DENSE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
+    for shape in DENSE_SHAPES + COLTILE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
         yield *shape, 4, 8, synth.BF16
     for shape in F32_SMALL + F32_SHAPES:
         yield *shape, 2, 4, synth.F32
