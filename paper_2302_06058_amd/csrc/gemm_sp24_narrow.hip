@@ -15,6 +15,7 @@
 // distinct banks.  Rows whose byte length is no multiple of 16 (K or Adim = 8 m + 4) must be
 // contiguous in memory; a 32-token tile is then one 16-byte-aligned block.
 #include "common.hpp"
+#include <type_traits>
 
 namespace bimask {
 namespace {
@@ -310,19 +311,203 @@ k_gemm_sp24_narrow(const uint16_t* __restrict__ A_all, const uint32_t* __restric
 #undef BIMASK_NARROW_SHAPE
 }
 
-template <int TM, int NSTG>
-int run_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
-               const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s) {
-    auto kern = k_gemm_sp24_narrow<TM, NSTG>;
-    const int in_bytes = 32 * narrow_pitch(static_cast<int>(K)) + NSTG * 256;   // fragment reads may run past row 31
-    const int out_bytes = 32 * narrow_pitch(static_cast<int>(Adim < TM * 32 ? Adim : TM * 32)) + 16;
-    const int lds = NSTG * 512 + (((in_bytes > out_bytes ? in_bytes : out_bytes) + 15) & ~15);
-    if (lds > 48 * 1024) return BIMASK_ERR_UNSUPPORTED;
-    // wavefronts per CU by LDS and registers; the grid is a multiple of the CU count in which every
-    // wavefront gets the same number of tiles (+-1)
-    // (the answer depends on the kernel, the LDS size and the device: remembered per instantiation and device,
-    // LDS size and answer in one word)
-    static DeviceMemo memo;
+// Rows that are no multiple of 16 bytes stay with the kernel above.
+// Token rows and output rows in 16-byte pieces (K and Adim multiples of 8): every load and every store of a tile is unconditional,
+// which is what keeps the next tile's rows in flight.  Where a piece is loaded under a condition the compiler cannot count what is
+// outstanding and waits for the previous load -- and for the previous tile's stores -- before each one.  Pieces and rows that do
+// not exist repeat one that does (loads), go to a spare row (LDS) or store the last piece once more; all tiles but the last one of
+// the matrix are full, and only that one's stores are conditional.  Bound by memory; the kernel above, with conditions -> this
+// one, us: 64 -> 256 columns at 200704 tokens 34.1 -> 28.9 (4.5 TB/s), with the gather 38.6 -> 29.2, 128 -> 256 with the gather
+// 43.1 -> 33.7, 512 -> 64 at 100000 38.4 -> 29.7, 64 -> 128 at 3000 5.1 -> 3.2.
+// NP: pieces per lane and tile (K <= 16 NP); WHOLE: K = 16 NP and Adim a multiple of 32 TM, known at compile time.
+template <int TM, int NP, bool PERM, bool WHOLE>
+__global__ void __launch_bounds__(64, narrow_waves_per_simd(TM, (NP + 7) / 8))
+k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __restrict__ Ameta_all, int Adim_all, int K_arg,
+                        const uint16_t* __restrict__ Bsrc, int ldb, const int32_t* __restrict__ perm, int64_t T,
+                        uint16_t* __restrict__ C_all, int ldc, int nsplit, bool stream_out) {
+    constexpr int NSTG = (NP + 7) / 8, NOUT = TM * 2;
+    const int split = (static_cast<int>(blockIdx.x) >> 3) % nsplit;
+    const int64_t wave_id = ((static_cast<int64_t>(blockIdx.x) >> 3) / nsplit) * 8 + (blockIdx.x & 7);
+    const int64_t nwaves = gridDim.x / nsplit;
+    uint16_t* __restrict__ C = C_all + split * (TM * 32);
+    const int K = WHOLE ? 16 * NP : K_arg, G = K / 8, pitchB = 2 * K + 8;
+    const int AW = WHOLE || Adim_all - split * (TM * 32) >= TM * 32 ? TM * 32 : Adim_all - split * (TM * 32);
+    const int UPR = AW / 8, pitchC = 2 * AW + 8;
+    extern __shared__ u32x4 smem_u4[];
+    // positions of the columns (Eq. (10)'s gather; byte offsets inside a row), then the token rows, later the output rows
+    int32_t* sInv = reinterpret_cast<int32_t*>(smem_u4);
+    uint8_t* area = reinterpret_cast<uint8_t*>(smem_u4) + (PERM ? NSTG * 512 : 0);
+    const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5;
+    // piece lane + 64 it of a tile is piece g of row r; the walk from one `it` to the next adds 64 = dr G + dg
+    const int rB = lane / G, gB = lane - rB * G, drB = 64 / G, dgB = 64 - drB * G;
+    const int rC = lane / UPR, gC = lane - rC * UPR, drC = 64 / UPR, dgC = 64 - drC * UPR;
+    const int64_t ntiles = ceil_div(T, 32);
+    int64_t tile = wave_id;
+    if (tile >= ntiles) return;
+    // (The walks start from copies the optimiser cannot see through: hoisted out of the tile loop, the addresses of all pieces
+    // would occupy a few dozen registers for the whole kernel.)
+
+    u32x4 v[NP];
+    auto load = [&](int64_t tl) {
+        const int64_t t0 = tl * 32;
+        const int last = static_cast<int>(T - t0 < 32 ? T - t0 : 32) - 1;
+        const uint8_t* base = reinterpret_cast<const uint8_t*>(Bsrc + t0 * ldb);
+        int r = rB, g = gB;
+        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));       // see above
+#pragma unroll
+        for (int it = 0; it < NP; ++it) {
+            v[it] = *reinterpret_cast<const u32x4*>(base + static_cast<uint32_t>((r < last ? r : last) * (2 * ldb) + 16 * g));
+            r += drB; g += dgB;
+            if (dgB != 0 && g >= G) { g -= G; r += 1; }
+        }
+    };
+    load(tile);
+    u32x4 ra[NSTG][TM][4];
+    u32x2 rmeta[NSTG][TM];
+    const int rt_last = (Adim_all + 31) / 32 - 1;            // row tiles beyond it re-read it (computed, never stored)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int rt = WHOLE || split * TM + i < rt_last ? split * TM + i : rt_last;
+        const uint16_t* pa = A_all + (static_cast<int64_t>(rt) * NSTG * 256 + lane) * 8;
+        const uint32_t* pm = Ameta_all + (static_cast<int64_t>(rt) * NSTG * 64 + lane) * 2;
+#pragma unroll
+        for (int st = 0; st < NSTG; ++st) {
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4)
+                ra[st][i][s4] = *reinterpret_cast<const u32x4*>(pa + (st * 4 + s4) * 512);
+            rmeta[st][i] = *reinterpret_cast<const u32x2*>(pm + st * 128);
+        }
+    }
+    if constexpr (PERM) {                                    // column c = P[r] goes to position r
+        for (int r = lane; r < K; r += 64) sInv[perm[r]] = 2 * r;
+    }
+
+    auto put = [&]() {                                       // registers -> LDS rows
+        wave_lds_fence();                                    // the previous tile's output rows have been read
+        int r = rB, g = gB;
+        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+#pragma unroll
+        for (int it = 0; it < NP; ++it) {
+            uint8_t* row = area + (WHOLE || r < 32 ? r : 32) * pitchB;
+            if constexpr (PERM) {
+                const u32x4 i0 = *reinterpret_cast<const u32x4*>(sInv + 8 * g);
+                const u32x4 i1 = *reinterpret_cast<const u32x4*>(sInv + 8 * g + 4);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<uint16_t*>(row + (e < 4 ? i0[e & 3] : i1[e & 3])) = static_cast<uint16_t>(v[it][e >> 1] >> (16 * (e & 1)));
+            } else {
+                u32x2* d = reinterpret_cast<u32x2*>(row + 16 * g);
+                d[0] = (u32x2){v[it].x, v[it].y};
+                d[1] = (u32x2){v[it].z, v[it].w};
+            }
+            r += drB; g += dgB;
+            if (dgB != 0 && g >= G) { g -= G; r += 1; }
+        }
+        wave_lds_fence();
+    };
+    // products of the tile in LDS, output rows regrouped through the same area
+    auto multiply = [&](int64_t tl, auto last_c) {
+        f32x16 acc[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][q] = 0.f;
+        const uint8_t* myrow = area + l32 * pitchB + 16 * h;
+#pragma unroll
+        for (int st = 0; st < NSTG; ++st) {
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4) {
+                BFragN bf;
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    bf.q[x] = (u32x4){0u, 0u, 0u, 0u};
+                    const int g = 16 * st + 8 * x + 2 * s4;  // granules g and g + 1 (one per lane half); the weights beyond K are zero
+                    if (g < 2 * NP) {
+                        const u32x2* p = reinterpret_cast<const u32x2*>(myrow + 16 * g);
+                        const u32x2 lo = p[0], hi = p[1];
+                        const bool in = WHOLE || st + 1 < NSTG || g + h < G;
+                        bf.q[x] = in ? (u32x4){lo.x, lo.y, hi.x, hi.y} : (u32x4){0u, 0u, 0u, 0u};
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    AFragN af;
+                    af.q = ra[st][i][s4];
+                    const int idx = static_cast<int>(s4 < 2 ? rmeta[st][i].x : rmeta[st][i].y);
+                    if (s4 & 1)
+                        acc[i] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af.v, bf.v, acc[i], idx, 0, 1);
+                    else
+                        acc[i] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af.v, bf.v, acc[i], idx, 0, 0);
+                }
+            }
+        }
+        wave_lds_fence();                                    // all fragment reads precede the overwrite
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint32_t xlo = pack_bf16(acc[i][8 * p + 0], acc[i][8 * p + 1]);
+                const uint32_t xhi = pack_bf16(acc[i][8 * p + 2], acc[i][8 * p + 3]);
+                const uint32_t ylo = pack_bf16(acc[i][8 * p + 4], acc[i][8 * p + 5]);
+                const uint32_t yhi = pack_bf16(acc[i][8 * p + 6], acc[i][8 * p + 7]);
+                const auto slo = __builtin_amdgcn_permlane32_swap(xlo, ylo, false, false);
+                const auto shi = __builtin_amdgcn_permlane32_swap(xhi, yhi, false, false);
+                const int a0 = i * 32 + 16 * p + 8 * h;      // first of this lane's 8 weight rows
+                if (WHOLE || a0 + 8 <= AW) {
+                    u32x2* d = reinterpret_cast<u32x2*>(area + l32 * pitchC + 2 * a0);
+                    d[0] = (u32x2){slo[0], shi[0]};
+                    d[1] = (u32x2){slo[1], shi[1]};
+                }
+            }
+        wave_lds_fence();
+        const int64_t t0 = tl * 32;
+        uint8_t* base = reinterpret_cast<uint8_t*>(C + t0 * ldc);
+        u32x4 o[NOUT];
+        int r = rC, g = gC;
+        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+#pragma unroll
+        for (int it = 0; it < NOUT; ++it) {
+            const bool in = WHOLE || r < 32;
+            const u32x2* p = reinterpret_cast<const u32x2*>(area + (in ? r : 31) * pitchC + 16 * (in ? g : UPR - 1));
+            const u32x2 lo = p[0], hi = p[1];
+            o[it] = (u32x4){lo.x, lo.y, hi.x, hi.y};
+            r += drC; g += dgC;
+            if (dgC != 0 && g >= UPR) { g -= UPR; r += 1; }
+        }
+        r = rC; g = gC;
+        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+#pragma unroll
+        for (int it = 0; it < NOUT; ++it) {
+            const bool in = WHOLE || r < 32;
+            const int rr = in ? r : 31;
+            u32x4* dst = reinterpret_cast<u32x4*>(base + static_cast<uint32_t>(rr * (2 * ldc) + 16 * (in ? g : UPR - 1)));
+            if (!decltype(last_c)::value || t0 + rr < T) {
+                if (stream_out) __builtin_nontemporal_store(o[it], dst);
+                else *dst = o[it];
+            }
+            r += drC; g += dgC;
+            if (dgC != 0 && g >= UPR) { g -= UPR; r += 1; }
+        }
+    };
+
+    // (a branch around the loads alone would copy their registers where it joins, and wait for them there; the weights are waited
+    // for here, vmcnt(0), or every tile would wait for the previous one's stores before it uses them)
+    put();
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    for (int64_t next = tile + nwaves; next < ntiles; next += nwaves) {
+        load(next);                                          // in flight during this tile's arithmetic
+        multiply(tile, std::false_type{});
+        tile = next;
+        put();
+    }
+    multiply(tile, std::true_type{});
+}
+
+// Wavefronts per CU by LDS and registers; the grid is a multiple of the CU count in which every wavefront gets the same number of
+// tiles (+-1).  (The occupancy depends on the kernel, the LDS size and the device: remembered per instantiation and device, LDS
+// size and answer in one word.)
+template <typename Kern>
+int narrow_grid(Kern kern, DeviceMemo& memo, int lds, int nsplit, int64_t T, unsigned& grid) {
     const int dev = DeviceMemo::device();
     const uint64_t known = memo.get(dev);
     int wpc = (known >> 32) == static_cast<uint64_t>(lds) ? static_cast<int>(known & 0xFFFFFFFFu) : 0;
@@ -332,20 +517,55 @@ int run_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, con
         memo.set(dev, (static_cast<uint64_t>(lds) << 32) | static_cast<uint32_t>(wpc));
     }
     if (wpc > 16) wpc = 16;
-    const int nsplit = static_cast<int>(ceil_div(Adim, TM * 32));
     const int64_t ntiles = ceil_div(T, 32);
     const int64_t slots = 256 * wpc / nsplit;                                   // token tiles in flight on the chip
     const int64_t rounds = ceil_div(ntiles, slots);
     int64_t nwaves = ceil_div(ceil_div(ntiles, rounds), 256) * 256;
     if (nwaves > round_up(ntiles, 8)) nwaves = round_up(ntiles, 8);
-    const unsigned grid = static_cast<unsigned>(nwaves * nsplit);
-    // whole rows leave as full 128-byte lines when the output is contiguous or its row pieces are whole lines
-    const bool stream_out = nsplit == 1
+    grid = static_cast<unsigned>(nwaves * nsplit);
+    return BIMASK_OK;
+}
+
+// whole rows leave as full 128-byte lines when the output is contiguous or its row pieces are whole lines
+bool narrow_streams_out(const void* C, int64_t Adim, int64_t ldc, int tm, int nsplit) {
+    return nsplit == 1
         ? (ldc == Adim || (Adim % 64 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0))
-        : ((TM * 32) % 64 == 0 && Adim % 64 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0);
+        : ((tm * 32) % 64 == 0 && Adim % 64 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0);
+}
+
+template <int TM, int NSTG>
+int run_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
+               const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s) {
+    auto kern = k_gemm_sp24_narrow<TM, NSTG>;
+    const int in_bytes = 32 * narrow_pitch(static_cast<int>(K)) + NSTG * 256;   // fragment reads may run past row 31
+    const int out_bytes = 32 * narrow_pitch(static_cast<int>(Adim < TM * 32 ? Adim : TM * 32)) + 16;
+    const int lds = NSTG * 512 + (((in_bytes > out_bytes ? in_bytes : out_bytes) + 15) & ~15);
+    if (lds > 48 * 1024) return BIMASK_ERR_UNSUPPORTED;
+    const int nsplit = static_cast<int>(ceil_div(Adim, TM * 32));
+    static DeviceMemo memo;
+    unsigned grid;
+    if (int rc = narrow_grid(kern, memo, lds, nsplit, T, grid)) return rc;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64), static_cast<size_t>(lds), s, static_cast<const uint16_t*>(A), meta,
                        static_cast<int>(Adim), static_cast<int>(K), static_cast<const uint16_t*>(Bsrc),
-                       static_cast<int>(ldb), perm, T, static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit, stream_out);
+                       static_cast<int>(ldb), perm, T, static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit,
+                       narrow_streams_out(C, Adim, ldc, TM, nsplit));
+    return check_launch();
+}
+
+template <int TM, int NP, bool PERM, bool WHOLE>
+int run_narrow_rows(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb, const int32_t* perm,
+                    int64_t T, void* C, int64_t ldc, hipStream_t s) {
+    auto kern = k_gemm_sp24_narrow_rows<TM, NP, PERM, WHOLE>;
+    const int k = static_cast<int>(K), a = static_cast<int>(Adim < TM * 32 ? Adim : TM * 32);
+    const int in_bytes = (WHOLE ? 32 : 33) * (2 * k + 8) + 256, out_bytes = 32 * (2 * a + 8);      // fragment reads may run past row 31
+    const int lds = (PERM ? (NP + 7) / 8 * 512 : 0) + (((in_bytes > out_bytes ? in_bytes : out_bytes) + 15) & ~15);
+    const int nsplit = static_cast<int>(ceil_div(Adim, TM * 32));
+    static DeviceMemo memo;
+    unsigned grid;
+    if (int rc = narrow_grid(kern, memo, lds, nsplit, T, grid)) return rc;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), static_cast<size_t>(lds), s, static_cast<const uint16_t*>(A), meta,
+                       static_cast<int>(Adim), k, static_cast<const uint16_t*>(Bsrc), static_cast<int>(ldb), perm, T,
+                       static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit, narrow_streams_out(C, Adim, ldc, TM, nsplit));
     return check_launch();
 }
 
@@ -361,6 +581,51 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
     if (K % 8 != 0 ? (ldb != K || perm) : ldb % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
     if (Adim % 8 != 0 ? ldc != Adim : ldc % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
     const int nstg = static_cast<int>(ceil_div(K, 128)), tm = static_cast<int>(ceil_div(Adim, 32));
+#define BIMASK_ROWS(TM_, NP_, W_)                                                                                     \
+    return perm ? run_narrow_rows<TM_, NP_, true, W_>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s)                \
+                : run_narrow_rows<TM_, NP_, false, W_>(A, meta, Adim, K, Bsrc, ldb, nullptr, T, C, ldc, s);
+#define BIMASK_ROWS_PLAIN(TM_, NP_) return run_narrow_rows<TM_, NP_, false, false>(A, meta, Adim, K, Bsrc, ldb, nullptr, T, C, ldc, s);
+    if (K % 8 == 0 && Adim % 8 == 0) {
+        if (K == 64) {                                       // the first ResNet stage: pieces and row tiles all whole
+            if (Adim == 64) BIMASK_ROWS(2, 4, true)
+            if (Adim == 128 || Adim == 256) BIMASK_ROWS(4, 4, true)
+        } else if (K == 128) {
+            if (Adim == 64) BIMASK_ROWS(2, 8, true)
+            if (Adim == 128 || Adim == 256) BIMASK_ROWS(4, 8, true)
+        } else if (K == 256 && Adim == 64) BIMASK_ROWS(2, 16, true)
+        if (K <= 64) {
+            switch (tm) {
+                case 1: BIMASK_ROWS(1, 4, false)
+                case 2: BIMASK_ROWS(2, 4, false)
+                case 3: case 6: BIMASK_ROWS(3, 4, false)     // six to eight row tiles: two wavefronts per token tile
+                case 4: case 7: case 8: BIMASK_ROWS(4, 4, false)
+                case 5: BIMASK_ROWS(5, 4, false)
+                default: break;
+            }
+        } else if (nstg == 1) {
+            switch (tm) {
+                case 1: BIMASK_ROWS(1, 8, false)
+                case 2: BIMASK_ROWS(2, 8, false)
+                case 3: case 6: BIMASK_ROWS(3, 8, false)
+                case 4: case 7: case 8: BIMASK_ROWS(4, 8, false)
+                case 5: BIMASK_ROWS(5, 8, false)
+                default: break;
+            }
+        } else if (!perm && (tm <= 2 || (tm <= 4 && nstg == 2 && T >= 16384))) {
+            // longer contractions: at most 64 weight rows, all their fragments in registers (with a permutation: column tiles).
+            // Up to 128 rows on two wavefronts per token tile gain with two stages and many tokens (256 -> 128 columns at 200704
+            // tokens 36.2 -> 32.0 us, 224 -> 88 at 30096 10.1 -> 7.6; 256 -> 104 at 15659 5.2, two wavefronts 5.9).
+            switch (nstg) {
+                case 2: if (tm == 1) BIMASK_ROWS_PLAIN(1, 16) else BIMASK_ROWS_PLAIN(2, 16)
+                case 3: if (tm == 1) BIMASK_ROWS_PLAIN(1, 24) else BIMASK_ROWS_PLAIN(2, 24)
+                case 4: if (tm == 1) BIMASK_ROWS_PLAIN(1, 32) else BIMASK_ROWS_PLAIN(2, 32)
+                default: break;
+            }
+        }
+        return BIMASK_ERR_UNSUPPORTED;
+    }
+#undef BIMASK_ROWS_PLAIN
+#undef BIMASK_ROWS
 #define BIMASK_NARROW(TM_, NSTG_) return run_narrow<TM_, NSTG_>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
     if (nstg == 1) {
         switch (tm) {

@@ -172,6 +172,22 @@ def test_column_tiles_are_exact(I, J, T, N, M):
     exact_layer(I, J, T, N, M, synth.BF16, 7950 + I + J)
 
 
+# Wavefront-private tiles: rows in 16-byte pieces, 1 to 5 row tiles (6 to 8 on two wavefronts), 1 to 4 stages, every piece and row tile
+# whole or ragged; rows that are no multiple of 16 bytes; three token rows in the last tile; more tiles than wavefronts on the chip
+NARROW_SHAPES = [(24, 56, 67), (56, 24, 67), (64, 88, 131), (88, 64, 131), (48, 120, 99), (120, 48, 99), (56, 152, 163), (152, 56, 163),
+                 (24, 120, 99), (120, 24, 99), (88, 120, 131), (120, 88, 131), (152, 120, 163), (120, 152, 163), (176, 56, 195), (56, 248, 259),
+                 (24, 248, 259), (24, 376, 387), (56, 376, 387), (24, 504, 515), (56, 504, 515), (104, 200, 16403),
+                 (64, 64, 99), (128, 64, 131), (64, 128, 131), (128, 128, 131), (64, 256, 259), (256, 64, 32771),
+                 (28, 64, 99), (28, 256, 259), (28, 384, 387), (28, 512, 515), (60, 256, 259), (60, 384, 387), (60, 512, 515), (92, 128, 131), (156, 128, 163),
+                 (60, 64, 99), (56, 24, 140003), (88, 120, 140003), (64, 64, 140003)]
+
+
+@pytest.mark.parametrize("I,J,T", NARROW_SHAPES)
+@pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
+def test_wavefront_private_tiles_are_exact(I, J, T, perm):
+    exact_layer(I, J, T, 2, 4, synth.BF16, 8050 + I + J, perm=perm)
+
+
 def test_tiles_of_256_x_64_stay_exact_where_the_tiles_fill_the_chip():
     exact_layer(256, 640, 12500, 2, 4, synth.BF16, 7900)
 
@@ -200,7 +216,7 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
 
 def exact_products():
     """(I, J, T, N, M, dtype) of every layer above; each with and without a permutation."""
-    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES:
+    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES + NARROW_SHAPES:
         yield *shape, 2, 4, synth.BF16
     for shape in DENSE_SHAPES + COLTILE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
         yield *shape, 4, 8, synth.BF16
