@@ -11,6 +11,7 @@
 // bf16, other: v_mfma_f32_32x32x16_bf16 on the dense masked weights (this file)
 // fp32       : v_mfma_f32_16x16x4_f32, contraction split over the wavefronts (gemm_f32.hip)
 #include "common.hpp"
+#include <type_traits>
 
 namespace bimask {
 namespace {
@@ -320,8 +321,8 @@ k_gather_cols_lds(const raw* __restrict__ in, int64_t T, int64_t ld, const int32
 // an 8 x R transpose of half-words in registers, R contiguous 16-byte LDS writes) and for the emit (8 LDS
 // reads, the transpose back, R 16-byte stores), and keeps the chunks' permutation entries in registers as
 // LDS byte offsets.  Persistent grid; the loads of the next tile are in flight while a tile is emitted.
-// Measured at 8192 tokens: 8 KB rows (R = 8) 29 us against 38 us row-major, 22 KB rows (R = 2) 87 us against
-// 92 us; a plain device-to-device copy of the same arrays takes 24 / 64 us.
+// Bound by memory, with all of a tile's loads in flight at once: 22 KB rows (R = 2) at 8192 tokens 89 -> 71 us (5.1 TB/s; a plain
+// device-to-device copy of the same arrays takes 64), the backward product with 8.5 KB rows (R = 4) at 9000 tokens 101 -> 91.
 template <int R> struct GatherVec;
 template <> struct GatherVec<2> { using type = uint32_t; };
 template <> struct GatherVec<4> { using type = uint2; };
@@ -337,85 +338,93 @@ k_gather_cols_rows(const uint16_t* __restrict__ in, int64_t T, int64_t ld, const
     uint8_t* buf = reinterpret_cast<uint8_t*>(gather_smem);
     const int chunks = I / 8;
     const int64_t ntiles = ceil_div(T, R);
-    int p[CPT][8];
+    // Threads beyond the last chunk repeat it: no load or store but the last tile's is conditional.  (Behind a condition the
+    // compiler cannot count what is in flight, and waits for the previous load and the previous tile's stores before each one:
+    // 48 permutation entries and then 12 pieces a tile, one after the other.)
+    int cc[CPT], p[CPT][8];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
         const int c = threadIdx.x + kThreads * k;
+        cc[k] = c < chunks ? c : chunks - 1;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) p[k][e] = c < chunks ? perm[c * 8 + e] * (2 * R) : 0;
+        for (int e = 0; e < 8; ++e) p[k][e] = perm[cc[k] * 8 + e];
     }
     // the loads of a tile are issued before the previous tile is emitted: they are in flight during its LDS reads and stores
     uint4 v[CPT][R];
     auto load_tile = [&](int64_t tile) {
         const int64_t t0 = tile * R;
 #pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = threadIdx.x + kThreads * k;
-            if (c < chunks) {
+        for (int k = 0; k < CPT; ++k)
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int64_t t = t0 + r < T ? t0 + r : T - 1;      // rows beyond T repeat the last row (never stored)
-                    v[k][r] = *reinterpret_cast<const uint4*>(in + t * ld + c * 8);
+            for (int r = 0; r < R; ++r) {
+                const int64_t t = t0 + r < T ? t0 + r : T - 1;          // rows beyond T repeat the last row (never stored)
+                v[k][r] = *reinterpret_cast<const uint4*>(in + t * ld + cc[k] * 8);
+            }
+    };
+    int64_t tile = blockIdx.x;                           // the grid is no larger than the number of tiles
+    load_tile(tile);
+#pragma unroll
+    for (int k = 0; k < CPT; ++k)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[k][e] *= 2 * R;
+    auto put_tile = [&]() {
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            // 8 columns x R rows: column e of the chunk -> R half-words (rows 0 .. R-1)
+            uint32_t o[8][W];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const uint32_t a = reinterpret_cast<const uint32_t*>(&v[k][2 * w])[e >> 1];
+                    const uint32_t b = reinterpret_cast<const uint32_t*>(&v[k][2 * w + 1])[e >> 1];
+                    o[e][w] = (e & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
+                }
+            uint32_t* dst = reinterpret_cast<uint32_t*>(buf + static_cast<size_t>(cc[k]) * (16 * R));
+#pragma unroll
+            for (int q = 0; q < 8 * W; ++q)              // R 16-byte writes: 8 columns x W dwords
+                if ((q & 3) == 0)
+                    *reinterpret_cast<uint4*>(dst + q) = make_uint4(o[(q + 0) / W][(q + 0) % W], o[(q + 1) / W][(q + 1) % W],
+                                                                    o[(q + 2) / W][(q + 2) % W], o[(q + 3) / W][(q + 3) % W]);
+        }
+    };
+    auto emit_tile = [&](int64_t t0, auto last_c) {
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            uint32_t g[8][W];                            // permuted column e of the chunk, R rows
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const vec x = *reinterpret_cast<const vec*>(buf + p[k][e]);
+#pragma unroll
+                for (int w = 0; w < W; ++w) g[e][w] = reinterpret_cast<const uint32_t*>(&x)[w];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!decltype(last_c)::value || t0 + r < T) {
+                    uint32_t wd[4];
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t a = g[2 * d][r >> 1], b = g[2 * d + 1][r >> 1];
+                        wd[d] = (r & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
+                    }
+                    typedef unsigned int gv4 __attribute__((ext_vector_type(4)));
+                    const gv4 pk = {wd[0], wd[1], wd[2], wd[3]};
+                    __builtin_nontemporal_store(pk, reinterpret_cast<gv4*>(out + (t0 + r) * I + cc[k] * 8));
                 }
             }
         }
     };
-    if (static_cast<int64_t>(blockIdx.x) < ntiles) load_tile(blockIdx.x);
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t t0 = tile * R;
-        __syncthreads();                                 // the previous tile has been emitted
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = threadIdx.x + kThreads * k;
-            if (c < chunks) {
-                // 8 columns x R rows: column e of the chunk -> R half-words (rows 0 .. R-1)
-                uint32_t o[8][W];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        const uint32_t a = reinterpret_cast<const uint32_t*>(&v[k][2 * w])[e >> 1];
-                        const uint32_t b = reinterpret_cast<const uint32_t*>(&v[k][2 * w + 1])[e >> 1];
-                        o[e][w] = (e & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
-                    }
-                uint32_t* dst = reinterpret_cast<uint32_t*>(buf + static_cast<size_t>(c) * (16 * R));
-#pragma unroll
-                for (int q = 0; q < 8 * W; ++q)          // R 16-byte writes: 8 columns x W dwords
-                    if ((q & 3) == 0)
-                        *reinterpret_cast<uint4*>(dst + q) = make_uint4(o[(q + 0) / W][(q + 0) % W], o[(q + 1) / W][(q + 1) % W],
-                                                                        o[(q + 2) / W][(q + 2) % W], o[(q + 3) / W][(q + 3) % W]);
-            }
-        }
+    for (;;) {
+        put_tile();
         __syncthreads();
-        if (tile + gridDim.x < ntiles) load_tile(tile + gridDim.x);
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = threadIdx.x + kThreads * k;
-            if (c < chunks) {
-                uint32_t g[8][W];                        // permuted column e of the chunk, R rows
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const vec x = *reinterpret_cast<const vec*>(buf + p[k][e]);
-#pragma unroll
-                    for (int w = 0; w < W; ++w) g[e][w] = reinterpret_cast<const uint32_t*>(&x)[w];
-                }
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (t0 + r < T) {
-                        uint32_t wd[4];
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            const uint32_t a = g[2 * d][r >> 1], b = g[2 * d + 1][r >> 1];
-                            wd[d] = (r & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
-                        }
-                        typedef unsigned int gv4 __attribute__((ext_vector_type(4)));
-                        const gv4 pk = {wd[0], wd[1], wd[2], wd[3]};
-                        __builtin_nontemporal_store(pk, reinterpret_cast<gv4*>(out + (t0 + r) * I + c * 8));
-                    }
-                }
-            }
-        }
+        const int64_t next = tile + gridDim.x;
+        if (next >= ntiles) break;
+        load_tile(next);
+        emit_tile(tile * R, std::false_type{});          // not the matrix's last tile: full
+        tile = next;
+        __syncthreads();                                 // the tile has been emitted
     }
+    emit_tile(tile * R, std::true_type{});
 }
 
 // Columns of a fragment-major dense operand moved from permuted to natural order: out(r, P[k]) = in(r, k).  A dense
