@@ -120,6 +120,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, r);
 }
 
+// A 16-byte store, streaming (past L2 and the last-level cache, for whole lines) or plain.  The empty statements keep the
+// compiler from making the two one: it would drop the streaming hint, and outputs that nobody reads again soon would push the
+// next call's operands out of the last-level cache.
+template <typename V>
+__device__ __forceinline__ void store16(const V& v, V* p, bool stream) {
+    if (stream) {
+        __builtin_nontemporal_store(v, p);
+    } else {
+        asm volatile("");
+        *p = v;
+        asm volatile("");
+    }
+}
+
 // launchers implemented in the .hip files -------------------------------------------
 int launch_forward(const void* W, int64_t I, int64_t J, int64_t ldw, int dtype, int N, int M,
                    const uint32_t* mask_in, uint32_t* B_bits, void* values, uint32_t* index,

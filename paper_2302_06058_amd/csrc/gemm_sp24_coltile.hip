@@ -83,8 +83,7 @@ k_gemm_sp24_coltile(const uint16_t* __restrict__ A, const uint32_t* __restrict__
             const u32x2 lo = p[0], hi = p[1];
             const u32x4 o = {lo.x, lo.y, hi.x, hi.y};
             u32x4* dst = reinterpret_cast<u32x4*>(C + (t0 + t) * ldc + a_base + 8 * u);
-            if (stream_out) __builtin_nontemporal_store(o, dst);
-            else *dst = o;
+            store16(o, dst, stream_out);
         }
     };
 

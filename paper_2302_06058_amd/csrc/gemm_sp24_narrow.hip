@@ -474,20 +474,21 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
             r += drC; g += dgC;
             if (dgC != 0 && g >= UPR) { g -= UPR; r += 1; }
         }
-        r = rC; g = gC;
-        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+        auto emit = [&](bool stream) {
+            int re = rC, ge = gC;
+            if constexpr (!WHOLE) asm volatile("" : "+v"(re), "+v"(ge));
 #pragma unroll
-        for (int it = 0; it < NOUT; ++it) {
-            const bool in = WHOLE || r < 32;
-            const int rr = in ? r : 31;
-            u32x4* dst = reinterpret_cast<u32x4*>(base + static_cast<uint32_t>(rr * (2 * ldc) + 16 * (in ? g : UPR - 1)));
-            if (!decltype(last_c)::value || t0 + rr < T) {
-                if (stream_out) __builtin_nontemporal_store(o[it], dst);
-                else *dst = o[it];
+            for (int it = 0; it < NOUT; ++it) {
+                const bool in = WHOLE || re < 32;
+                const int rr = in ? re : 31;
+                u32x4* dst = reinterpret_cast<u32x4*>(base + static_cast<uint32_t>(rr * (2 * ldc) + 16 * (in ? ge : UPR - 1)));
+                if (!decltype(last_c)::value || t0 + rr < T) store16(o[it], dst, stream);
+                re += drC; ge += dgC;
+                if (dgC != 0 && ge >= UPR) { ge -= UPR; re += 1; }
             }
-            r += drC; g += dgC;
-            if (dgC != 0 && g >= UPR) { g -= UPR; r += 1; }
-        }
+        };
+        if (stream_out) emit(true);
+        else emit(false);
     };
 
     // (a branch around the loads alone would copy their registers where it joins, and wait for them there; the weights are waited
