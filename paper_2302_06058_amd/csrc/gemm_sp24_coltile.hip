@@ -396,7 +396,7 @@ int run_coltile(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, co
             return BIMASK_ERR_HIP;
         attr_set.set(dev, 1);
     }
-    const bool stream_out = (Adim * 2) % 128 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0;
+    const bool stream_out = streams_out(C, Adim, ldc, p.pieces == 1);
     hipLaunchKernelGGL(kern, dim3(p.grid, p.pieces), dim3(kColThreads), p.lds, s, static_cast<const uint16_t*>(A), meta,
                        static_cast<int>(Adim), static_cast<int>(K), static_cast<const uint16_t*>(Bsrc), ldb, perm, T,
                        static_cast<uint16_t*>(C), ldc, p.chunk, p.rpt, col_pitch(p.rpt), stream_out);

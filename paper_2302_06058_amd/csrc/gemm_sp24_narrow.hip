@@ -296,8 +296,7 @@ k_gemm_sp24_narrow(const uint16_t* __restrict__ A_all, const uint32_t* __restric
                         const u32x2 lo = p[0], hi = p[1];
                         const u32x4 o = {lo.x, lo.y, hi.x, hi.y};
                         u32x4* dst = reinterpret_cast<u32x4*>(base + gofs);
-                        if (stream_out) __builtin_nontemporal_store(o, dst);
-                        else *dst = o;
+                        store16(o, dst, stream_out);
                     }
                     u += dgC; lofs += lstep; gofs += gstep;
                     if (u >= UPR) { u -= UPR; lofs += lcarry; gofs += gcarry; }
@@ -527,13 +526,6 @@ int narrow_grid(Kern kern, DeviceMemo& memo, int lds, int nsplit, int64_t T, uns
     return BIMASK_OK;
 }
 
-// whole rows leave as full 128-byte lines when the output is contiguous or its row pieces are whole lines
-bool narrow_streams_out(const void* C, int64_t Adim, int64_t ldc, int tm, int nsplit) {
-    return nsplit == 1
-        ? (ldc == Adim || (Adim % 64 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0))
-        : ((tm * 32) % 64 == 0 && Adim % 64 == 0 && ldc % 64 == 0 && (reinterpret_cast<uintptr_t>(C) & 127u) == 0);
-}
-
 template <int TM, int NSTG>
 int run_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
                const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s) {
@@ -549,7 +541,7 @@ int run_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, con
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64), static_cast<size_t>(lds), s, static_cast<const uint16_t*>(A), meta,
                        static_cast<int>(Adim), static_cast<int>(K), static_cast<const uint16_t*>(Bsrc),
                        static_cast<int>(ldb), perm, T, static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit,
-                       narrow_streams_out(C, Adim, ldc, TM, nsplit));
+                       streams_out(C, Adim, ldc, nsplit == 1));
     return check_launch();
 }
 
@@ -566,7 +558,7 @@ int run_narrow_rows(const void* A, const uint32_t* meta, int64_t Adim, int64_t K
     if (int rc = narrow_grid(kern, memo, lds, nsplit, T, grid)) return rc;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64), static_cast<size_t>(lds), s, static_cast<const uint16_t*>(A), meta,
                        static_cast<int>(Adim), k, static_cast<const uint16_t*>(Bsrc), static_cast<int>(ldb), perm, T,
-                       static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit, narrow_streams_out(C, Adim, ldc, TM, nsplit));
+                       static_cast<uint16_t*>(C), static_cast<int>(ldc), nsplit, streams_out(C, Adim, ldc, nsplit == 1));
     return check_launch();
 }
 
