@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbimask.so")
 SOURCES = ["api.hip", "mask_kernels.hip", "perm_search.hip", "perm_refine.hip", "gemm.hip", "gemm_f32.hip", "gemm_sp24.hip", "gemm_sp24_big.hip",
-           "gemm_sp24_resident.hip", "gemm_sp24_narrow.hip", "gemm_sp24_coltile.hip"]
+           "gemm_sp24_resident.hip", "gemm_sp24_narrow.hip", "gemm_sp24_coltile.hip", "gemm_sp24_wide.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     "-Wall", "-Wextra", "-Wno-unused-parameter",

@@ -246,7 +246,9 @@ int bimask_sparse_gemm_bwd(const void* dY, int64_t T, int64_t lddy, const int32_
         if (apart && dtype == BIMASK_F32 && gemm_f32_fuses_gather(T, J, I))
             return launch_gemm_f32(Wb_values, Wb_index, J, I, sp, dY, T, lddy, perm, dX, lddx, as_stream(stream));
         if (apart && dtype == BIMASK_BF16) {
-            const int rc = launch_gemm_sp24_coltile(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
+            int rc = launch_gemm_sp24_coltile(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
+            if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
+            rc = launch_gemm_sp24_wide(Wb_values, Wb_index, J, I, dY, lddy, perm, T, dX, lddx, as_stream(stream), !sp);
             if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
         }
         if (apart && dtype == BIMASK_BF16 && !sp && gemm_dense_unpermutes(dY, T, lddy, J, I)) {

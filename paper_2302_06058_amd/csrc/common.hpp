@@ -217,6 +217,9 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
 // takes and where another kernel is the faster (dense: the weight operand is the dense masked matrix of a ratio with N > 2, meta unused)
 int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
                              const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s, bool dense);
+// wide outputs, contractions up to 512, either operand format, perm or not; BIMASK_ERR_UNSUPPORTED as above
+int launch_gemm_sp24_wide(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
+                          const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s, bool dense);
 // true when the backward GEMM needs the gathered copy of g(Y) in the workspace
 // Debug helper: one flag per candidate, 1 = a permutation of 0 .. I-1 (bitmap of I bits in LDS).
 constexpr int64_t kCheckPermsMaxRows = 1 << 20;

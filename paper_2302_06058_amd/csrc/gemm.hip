@@ -605,6 +605,8 @@ bool gemm_bwd_needs_gather(int64_t I, int64_t J, int dtype, int N, int M) {
 int launch_gemm(const void* A_values, const uint32_t* A_index, int64_t Adim, int64_t K, bool sparse24,
                 const void* Bm, int64_t T, int64_t ldb, void* C, int64_t ldc, int dtype, hipStream_t s) {
     if (dtype == BIMASK_F32) return launch_gemm_f32(A_values, A_index, Adim, K, sparse24, Bm, T, ldb, nullptr, C, ldc, s);
+    const int rc = launch_gemm_sp24_wide(A_values, A_index, Adim, K, Bm, ldb, nullptr, T, C, ldc, s, !sparse24);
+    if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
     if (sparse24) {
         // A 64 x 32 or 64 x 64 tile per CU at most: split the contraction inside the workgroup (4096 x 4096 at 64 tokens
         // 17.5 -> 8.9 us, at 256 18.3 -> 15.4).  Three stages and more gain, four where token rows are read in 4-byte pieces

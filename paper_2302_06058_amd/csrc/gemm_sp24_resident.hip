@@ -355,7 +355,9 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
     // that the wavefront-private kernel carries as whole pieces (200704 tokens 32.8 -> 28.8 us, 50000 11.1 / 10.6)
     const bool stream = K == 256 && Adim == 64 && T >= 32768;
     if (perm && !stream) {
-        const int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
+        int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
+        if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
+        rc = launch_gemm_sp24_wide(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
     }
     {   // narrow weights: one wavefront per token tile, weights in registers

@@ -188,6 +188,20 @@ def test_wavefront_private_tiles_are_exact(I, J, T, perm):
     exact_layer(I, J, T, 2, 4, synth.BF16, 8050 + I + J, perm=perm)
 
 
+# Wide outputs: tiles of 64 and of 128 tokens, one piece of weight rows and several, contractions that end inside a stage (1 to 4
+# stages), row tiles and wavefront tiles that are not full, a last token tile of a few rows, fewer wavefront tiles than wavefronts
+WIDE_SHAPES = [(1032, 264, 4099), (1536, 384, 25003), (1096, 392, 9001), (2056, 504, 5003), (392, 1544, 17003), (504, 1096, 20011), (512, 4608, 3139),
+               (640, 136, 5003), (288, 136, 16401), (160, 544, 16403),
+               (264, 136, 65500)]                                      # just outside: the persistent form of the resident kernel
+WIDE_DENSE_SHAPES = [(264, 104, 4099), (1032, 200, 9001), (1536, 384, 25003), (104, 520, 4101), (320, 1032, 9001), (136, 1096, 30011),
+                     (1056, 64, 2051), (72, 544, 4100)]
+
+
+@pytest.mark.parametrize("I,J,T,N,M", [(*s, 2, 4) for s in WIDE_SHAPES] + [(*s, 4, 8) for s in WIDE_DENSE_SHAPES])
+def test_wide_outputs_are_exact(I, J, T, N, M):
+    exact_layer(I, J, T, N, M, synth.BF16, 8150 + I + J)
+
+
 def test_tiles_of_256_x_64_stay_exact_where_the_tiles_fill_the_chip():
     exact_layer(256, 640, 12500, 2, 4, synth.BF16, 7900)
 
@@ -216,9 +230,9 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
 
 def exact_products():
     """(I, J, T, N, M, dtype) of every layer above; each with and without a permutation."""
-    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES + NARROW_SHAPES:
+    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES + NARROW_SHAPES + WIDE_SHAPES:
         yield *shape, 2, 4, synth.BF16
-    for shape in DENSE_SHAPES + COLTILE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
+    for shape in DENSE_SHAPES + COLTILE_SHAPES + WIDE_DENSE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
         yield *shape, 4, 8, synth.BF16
     for shape in F32_SMALL + F32_SHAPES:
         yield *shape, 2, 4, synth.F32
