@@ -381,14 +381,11 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
         case 3: return run_resident<256, 64, WAVES, 3>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
         default: return run_resident<256, 64, WAVES, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
     }
-    if (ceil_div(T, 64) >= 1024) {
-        // many token tiles per CU: persistent workgroups fetch the next tile's rows during the current one
-        switch (nstg) {
-            case 1: return run_resident<256, 64, 8, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, 64, s);
-            case 2: return run_resident<256, 64, 8, 2, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, 64, s);
-            default: break;
-        }
-    }
+    // Many token tiles per CU and one stage: persistent workgroups fetch the next tile's rows during the current one.  With two stages
+    // the fetched rows don't fit in registers beside the fragments (74 spilled: 160 -> 552 columns at 168539 tokens 191.9 us against 93.0
+    // with a workgroup per tile, 216 -> 216 at 99193 48.0 / 30.6).
+    if (nstg == 1 && ceil_div(T, 64) >= 1024)
+        return run_resident<256, 64, 8, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, 64, s);
     BIMASK_RES(8)
 #undef BIMASK_RES
 }

@@ -192,7 +192,7 @@ def test_wavefront_private_tiles_are_exact(I, J, T, perm):
 # stages), row tiles and wavefront tiles that are not full, a last token tile of a few rows, fewer wavefront tiles than wavefronts
 WIDE_SHAPES = [(1032, 264, 4099), (1536, 384, 25003), (1096, 392, 9001), (2056, 504, 5003), (392, 1544, 17003), (504, 1096, 20011), (512, 4608, 3139),
                (640, 136, 5003), (288, 136, 16401), (160, 544, 16403),
-               (264, 136, 65500)]                                      # just outside: the persistent form of the resident kernel
+               (264, 136, 65500)]                                      # just outside, many tokens: the resident kernel
 WIDE_DENSE_SHAPES = [(264, 104, 4099), (1032, 200, 9001), (1536, 384, 25003), (104, 520, 4101), (320, 1032, 9001), (136, 1096, 30011),
                      (1056, 64, 2051), (72, 544, 4100)]
 
