@@ -462,14 +462,39 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
         uint32_t w[M][PW];
         uint32_t bb[M];
         if (j0 < J) {
+            // All permutation entries, then all rows and mask bytes: no condition stands between two loads of a group, before which
+            // the compiler would wait for the earlier ones (4:8 at 1536 x 384 7.4 -> 5.2 us).
+            int64_t src[M];
+            if (perm) {                                  // uniform
 #pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int64_t src = perm ? static_cast<int64_t>(perm[rb + m]) : rb + m;
-                if constexpr (QC == 8) load8<DT>(W + src * ldw, j0, J, vec_in, w[m]);
-                else load_few<DT, QC>(W + src * ldw + j0, vec_in, w[m]);
-                bb[m] = (Bbar_in ? reinterpret_cast<const uint8_t*>(Bbar_in)[(rb + m) * wpr * 4 + (j0 >> 3)]
-                                 : reinterpret_cast<const uint8_t*>(B_bits)[src * wpr * 4 + (j0 >> 3)]) >> sh;
+                for (int m = 0; m < M; ++m) src[m] = perm[rb + m];
+            } else {
+#pragma unroll
+                for (int m = 0; m < M; ++m) src[m] = rb + m;
             }
+            const uint8_t* mask = reinterpret_cast<const uint8_t*>(Bbar_in ? Bbar_in : B_bits) + (j0 >> 3);
+            const int64_t mask_pitch = static_cast<int64_t>(wpr) * 4;
+#pragma unroll
+            for (int m = 0; m < M; ++m) bb[m] = mask[(Bbar_in ? rb + m : src[m]) * mask_pitch];
+            if constexpr (QC == 8) {
+                if (vec_in && j0 + 8 <= J) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) load8<DT>(W + src[m] * ldw, j0, j0 + 8, true, w[m]);
+                } else {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) load8<DT>(W + src[m] * ldw, j0, J, false, w[m]);
+                }
+            } else {
+                if (vec_in) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) load_few<DT, QC>(W + src[m] * ldw + j0, true, w[m]);
+                } else {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) load_few<DT, QC>(W + src[m] * ldw + j0, false, w[m]);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < M; ++m) bb[m] >>= sh;
 #pragma unroll
             for (int q = 0; q < QC; ++q) {
                 uint32_t colbits = 0;                       // mask bits of this column block
