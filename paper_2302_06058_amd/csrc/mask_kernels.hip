@@ -9,10 +9,6 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // native 16-byte register vector
 
-// Compressed operands up to this size are written with ordinary stores so that the GEMM that
-// follows finds them in L2 (4 MB per XCD); larger ones are streamed to memory.
-constexpr size_t kL2Keep = 2u << 20;
-
 // ---------------------------------------------------------------------------------
 // small register helpers
 // ---------------------------------------------------------------------------------
@@ -190,7 +186,7 @@ __device__ __forceinline__ void
 forward24_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t ldw, int N,
                const uint32_t* __restrict__ mask_in, uint32_t* __restrict__ B_bits,
                typename DT::raw* __restrict__ values, uint32_t* __restrict__ index,
-               int wpr, int ks, int64_t row_octets, bool vec_in, bool stream_out, int64_t block) {
+               int wpr, int ks, int64_t row_octets, bool vec_in, int64_t block) {
     using raw = typename DT::raw;
     constexpr int PW = Pack<DT>::kWords;
     constexpr int U = 2;                               // stages per wavefront: 4 loads in flight per lane
@@ -235,8 +231,7 @@ forward24_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int
                     ov[g] = v2;
                 }
                 raw* dst = values + ((((i >> 5) * ks + st) * 4 + (q & 3)) * 64 + (i & 31) + 32 * (q >> 2)) * 8;
-                if (stream_out) __builtin_nontemporal_store(ov, reinterpret_cast<u32x4*>(dst));
-                else *reinterpret_cast<u32x4*>(dst) = ov;
+                *reinterpret_cast<u32x4*>(dst) = ov;
                 // lanes q and q^1 merge their 16 index / mask bits into one word (even lane writes)
                 const uint32_t packed = bits | (nibs << 16);
                 const uint32_t other = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(packed), 0xB1, 0xF, 0xF, true));
@@ -281,11 +276,9 @@ forward24_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int
                 const uint32_t vmask = left >= 4 ? 0xFFFFu : (left <= 0 ? 0u : (1u << (4 * static_cast<int>(left))) - 1u);
                 bits &= vmask;
                 nibs &= vmask;
-                // whole 128-byte lines per 8 lanes; streamed past L2 when the operand is too large to
-                // wait there for the GEMM anyway
+                // whole 128-byte lines per 8 lanes
                 const u32x4 ov = {ow[0], ow[1], ow[2], ow[3]};
-                if (stream_out) __builtin_nontemporal_store(ov, reinterpret_cast<u32x4*>(dst));
-                else *reinterpret_cast<u32x4*>(dst) = ov;
+                *reinterpret_cast<u32x4*>(dst) = ov;
                 done = true;
             }
         }
@@ -339,8 +332,8 @@ __global__ void __launch_bounds__(kThreads)
 k_forward24(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t ldw, int N,
             const uint32_t* __restrict__ mask_in, uint32_t* __restrict__ B_bits,
             typename DT::raw* __restrict__ values, uint32_t* __restrict__ index,
-            int wpr, int ks, int64_t row_octets, bool vec_in, bool stream_out) {
-    forward24_body<DT, M>(W, I, J, ldw, N, mask_in, B_bits, values, index, wpr, ks, row_octets, vec_in, stream_out,
+            int wpr, int ks, int64_t row_octets, bool vec_in) {
+    forward24_body<DT, M>(W, I, J, ldw, N, mask_in, B_bits, values, index, wpr, ks, row_octets, vec_in,
                           static_cast<int64_t>(blockIdx.x));
 }
 
@@ -367,7 +360,7 @@ struct FwdGroupP {
     void* values;
     uint32_t* index;
     int64_t I, J, ldw, row_octets;
-    int wpr, ks, vec_in, stream_out;
+    int wpr, ks, vec_in;
 };
 
 template <typename DT, int M>
@@ -377,7 +370,7 @@ k_forward24_group(const GroupTable<FwdGroupP> g, int N) {
     const int l = group_layer_of(g, blockIdx.x);
     const FwdGroupP& p = g.p[l];
     forward24_body<DT, M>(static_cast<const raw*>(p.W), p.I, p.J, p.ldw, N, nullptr, p.B_bits, static_cast<raw*>(p.values),
-                          p.index, p.wpr, p.ks, p.row_octets, p.vec_in != 0, p.stream_out != 0,
+                          p.index, p.wpr, p.ks, p.row_octets, p.vec_in != 0,
                           static_cast<int64_t>(blockIdx.x - g.first[l]));
 }
 
@@ -702,7 +695,7 @@ template <int NO, bool FAST>
 __device__ __forceinline__ void backward24_tile(
         const uint16_t* __restrict__ W, int64_t I, int64_t J, int64_t ldw, const uint32_t* __restrict__ B_bits,
         const int32_t* __restrict__ perm, uint32_t* __restrict__ Bbar_bits, uint16_t* __restrict__ values,
-        uint32_t* __restrict__ index, int wpr, bool vec_in, bool vec_perm, bool stream_out, bool active,
+        uint32_t* __restrict__ index, int wpr, bool vec_in, bool vec_perm, bool active,
         int64_t r0, int c0, uint4* lds_wave, int lane, int N) {
     const int c = lane & 7, k = lane >> 3;
     const int64_t rb = r0 + 4 * k;
@@ -821,9 +814,8 @@ __device__ __forceinline__ void backward24_tile(
         const u32x4 v = reinterpret_cast<const u32x4*>(lds_wave)[it ^ ((it >> 4) & 7)];
         if (FAST || (active && c0 + 32 * it0 < J)) {
             uint16_t* dst = values + ((((c0 / 32 + it0) * ks + stage) * 4 + s4base + ((it >> 5) & 1)) * 64 + (it & 31) + 32 * lane_half) * 8;
-            // 512-byte runs, whole lines; streamed past L2 for operands too large to stay there
-            if (stream_out) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
-            else *reinterpret_cast<u32x4*>(dst) = v;
+            // 512-byte runs, whole lines (streaming stores measured: no gain on 4096 x 11008, 92.1 us a pass either way)
+            *reinterpret_cast<u32x4*>(dst) = v;
         }
     }
 }
@@ -834,7 +826,7 @@ k_backward24_bf16(const uint16_t* __restrict__ W, int64_t I, int64_t J, int64_t 
                   const uint32_t* __restrict__ B_bits, const int32_t* __restrict__ perm,
                   uint32_t* __restrict__ Bbar_bits, uint16_t* __restrict__ values,
                   uint32_t* __restrict__ index, int wpr, int64_t col_tiles, int64_t units,
-                  bool vec_in, bool vec_perm, bool stream_out, int N) {
+                  bool vec_in, bool vec_perm, int N) {
     constexpr int TC = 64 * NO;
     // per wavefront: 2*NO output row tiles x 2 instruction slots x 32 lanes x 16 bytes
     __shared__ uint4 lds[kThreads / 64][NO * 128];
@@ -848,10 +840,10 @@ k_backward24_bf16(const uint16_t* __restrict__ W, int64_t I, int64_t J, int64_t 
         static_cast<int>(active && vec_in && r0 + 32 <= I && c0 + TC <= J)) != 0;
     if (fast)
         backward24_tile<NO, true>(W, I, J, ldw, B_bits, perm, Bbar_bits, values, index, wpr, vec_in, vec_perm,
-                                  stream_out, active, r0, c0, lds[wave], lane, N);
+                                  active, r0, c0, lds[wave], lane, N);
     else
         backward24_tile<NO, false>(W, I, J, ldw, B_bits, perm, Bbar_bits, values, index, wpr, vec_in, vec_perm,
-                                   stream_out, active, r0, c0, lds[wave], lane, N);
+                                   active, r0, c0, lds[wave], lane, N);
 }
 
 struct BwdGroupP {
@@ -862,7 +854,7 @@ struct BwdGroupP {
     uint16_t* values;
     uint32_t* index;
     int64_t I, J, ldw, col_tiles, units;
-    int wpr, vec_in, vec_perm, stream_out;
+    int wpr, vec_in, vec_perm;
 };
 
 // small bf16 2:4 layers, one wavefront (= one 32 x 64 tile) per workgroup
@@ -881,10 +873,10 @@ k_backward24_bf16_group(const GroupTable<BwdGroupP> g, int N) {
         static_cast<int>(active && p.vec_in != 0 && r0 + 32 <= p.I && c0 + 64 <= p.J)) != 0;
     if (fast)
         backward24_tile<1, true>(p.W, p.I, p.J, p.ldw, p.B_bits, p.perm, p.Bbar_bits, p.values, p.index, p.wpr, p.vec_in != 0,
-                                 p.vec_perm != 0, p.stream_out != 0, active, r0, c0, lds, lane, N);
+                                 p.vec_perm != 0, active, r0, c0, lds, lane, N);
     else
         backward24_tile<1, false>(p.W, p.I, p.J, p.ldw, p.B_bits, p.perm, p.Bbar_bits, p.values, p.index, p.wpr, p.vec_in != 0,
-                                  p.vec_perm != 0, p.stream_out != 0, active, r0, c0, lds, lane, N);
+                                  p.vec_perm != 0, active, r0, c0, lds, lane, N);
 }
 
 template <typename DT, int M>
@@ -901,8 +893,7 @@ int run_forward(const void* W, int64_t I, int64_t J, int64_t ldw, int N, const u
         const int64_t units = row_octets * ((ks + 1) / 2);     // one wavefront each (two stages)
         hipLaunchKernelGGL((k_forward24<DT, M>), dim3(static_cast<unsigned>(ceil_div(units, kThreads / 64))),
                            dim3(kThreads), 0, s, static_cast<const raw*>(W), I, J, ldw, N, mask_in, B_bits,
-                           static_cast<raw*>(values), index, wpr, ks, row_octets, vec_in,
-                           static_cast<size_t>(I) * J * sizeof(raw) / 2 > kL2Keep);
+                           static_cast<raw*>(values), index, wpr, ks, row_octets, vec_in);
         return check_launch();
     }
     // mask only: threads cover the mask words; dense operand: the padded matrix (rows to 32, columns to 128)
@@ -959,17 +950,16 @@ int run_backward(const void* W, int64_t I, int64_t J, int64_t ldw, int N, const 
             const int64_t row_groups = ceil_div(I, 128) * 4;            // 32-row groups of the padded stages
             const uint16_t* Wp = static_cast<const uint16_t*>(W);
             uint16_t* vp = static_cast<uint16_t*>(values);
-            const bool stream_out = static_cast<size_t>(I) * J > kL2Keep;     // operand bytes = I*J*2/2
             // wide tiles when they still give every SIMD of the chip a wavefront
             if (row_groups * ceil_div(J, 128) >= 2048) {
                 const int64_t ct = ceil_div(J, 128), units = row_groups * ct;
                 hipLaunchKernelGGL((k_backward24_bf16<2>), dim3(static_cast<unsigned>(ceil_div(units, 4))), dim3(kThreads),
-                                   0, s, Wp, I, J, ldw, B_bits, perm, Bbar_bits, vp, index, wpr, ct, units, vec_in, vec_perm, stream_out, N);
+                                   0, s, Wp, I, J, ldw, B_bits, perm, Bbar_bits, vp, index, wpr, ct, units, vec_in, vec_perm, N);
             } else {
                 // small matrices: one wavefront per workgroup so that the tiles spread over all CUs
                 const int64_t ct = ceil_div(J, 64), units = row_groups * ct;
                 hipLaunchKernelGGL((k_backward24_bf16<1>), dim3(static_cast<unsigned>(units)), dim3(64),
-                                   0, s, Wp, I, J, ldw, B_bits, perm, Bbar_bits, vp, index, wpr, ct, units, vec_in, vec_perm, stream_out, N);
+                                   0, s, Wp, I, J, ldw, B_bits, perm, Bbar_bits, vp, index, wpr, ct, units, vec_in, vec_perm, N);
             }
             return check_launch();
         }
@@ -1020,7 +1010,6 @@ int run_forward_group(const bimask_group_layer* L, int n, int N, hipStream_t s) 
             p.ks = static_cast<int>(round_up(a.J, 128) / 128);
             p.row_octets = round_up(a.I, 32) / 8;
             p.vec_in = aligned16(a.W) && (a.ldw * sizeof(raw)) % 16 == 0;
-            p.stream_out = static_cast<size_t>(a.I) * a.J * sizeof(raw) / 2 > kL2Keep;
             g.first[l] = blocks;
             blocks += static_cast<unsigned>(ceil_div(p.row_octets * ((p.ks + 1) / 2), kThreads / 64));
         }
@@ -1131,7 +1120,6 @@ int launch_backward_group(const bimask_group_layer* L, int n, int dtype, int N, 
         p.wpr = static_cast<int>(ceil_div(a.J, 32));
         p.vec_in = aligned16(a.W) && (a.ldw * 2) % 16 == 0;
         p.vec_perm = a.best_perm && aligned16(a.best_perm);
-        p.stream_out = static_cast<size_t>(a.I) * a.J > kL2Keep;
         g.first[g.n] = blocks;
         blocks += static_cast<unsigned>(p.units);
         if (++g.n == GroupTable<BwdGroupP>::kCap)
