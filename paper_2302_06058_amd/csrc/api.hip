@@ -29,12 +29,6 @@ int check_matrix(const void* W, int64_t I, int64_t J, int64_t ldw, int dtype, in
 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
-// Two matrices of T rows that share no byte of the ranges they span.
-bool disjoint(const void* a, int64_t T, int64_t lda, int64_t cols_a, const void* b, int64_t ldb, int64_t cols_b, size_t esz) {
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
-    return a0 + ((T - 1) * lda + cols_a) * esz <= b0 || b0 + ((T - 1) * ldb + cols_b) * esz <= a0;
-}
-
 // Operand checks shared by the two GEMM entry points.
 int check_gemm(const void* act, int64_t T, int64_t ldact, int64_t kdim, const void* values, const uint32_t* index,
                int64_t I, int64_t J, int dtype, int N, int M, const void* out, int64_t ldout, int64_t outdim) {

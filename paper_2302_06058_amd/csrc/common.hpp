@@ -142,6 +142,12 @@ inline bool streams_out(const void* C, int64_t Adim, int64_t ldc, bool whole_row
     return (whole_rows && ldc == Adim) || (Adim % 32 == 0 && ldc % 32 == 0 && (reinterpret_cast<uintptr_t>(C) & 63u) == 0);
 }
 
+// Two matrices of T rows that share no byte of the ranges they span.
+inline bool disjoint(const void* a, int64_t T, int64_t lda, int64_t cols_a, const void* b, int64_t ldb, int64_t cols_b, size_t esz) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 + ((T - 1) * lda + cols_a) * esz <= b0 || b0 + ((T - 1) * ldb + cols_b) * esz <= a0;
+}
+
 // launchers implemented in the .hip files -------------------------------------------
 int launch_forward(const void* W, int64_t I, int64_t J, int64_t ldw, int dtype, int N, int M,
                    const uint32_t* mask_in, uint32_t* B_bits, void* values, uint32_t* index,

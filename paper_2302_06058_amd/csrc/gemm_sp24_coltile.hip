@@ -345,14 +345,15 @@ size_t col_lds(int rpt, int64_t K, int64_t width) {
 
 // Row tiles per wavefront, tokens per workgroup and tile.  256 workgroups at most; every one takes the same number of tokens
 // in the fewest tiles.  TM by the estimate below: fitted (within 12 %) to 720 timed launches over 136 .. 2048 columns, 32 .. 2600
-// rows and 16 .. 60000 tokens; over these its choice costs 0.2 % against the best of the three.
-bool col_plan(int64_t Adim, int64_t K, int64_t T, bool dense, ColPlan& best) {
+// rows and 16 .. 60000 tokens; over these its choice costs 0.2 % against the best of the three.  `whole`: all weight rows in one
+// workgroup, which then is the only one to read the token rows that it writes (dX on top of dY).
+bool col_plan(int64_t Adim, int64_t K, int64_t T, bool dense, bool whole, ColPlan& best) {
     double best_us = 0;
     best.tm = 0;
-    for (int tm = 1; tm <= 3; ++tm) {
+    for (int tm = 1; tm <= (whole ? 4 : 3); ++tm) {
         const int64_t pieces = ceil_div(Adim, 128 * tm), width = Adim < 128 * tm ? Adim : 128 * tm, slots = 256 / pieces;
-        if (slots < 1) continue;
-        int cap = 64;
+        if (slots < 1 || (whole && pieces > 1)) continue;
+        int cap = tm == 4 ? 32 : 64;
         while (cap > 0 && (cap * K > 32 * 256 * kColUnits || col_lds(cap, K, width) > kColLds)) cap -= 4;
         if (cap < 4) continue;
         const int64_t chunk = round_up(ceil_div(T, slots), 4), rounds = ceil_div(chunk, cap);
@@ -417,7 +418,8 @@ int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, 
     if (!aligned16(A) || !aligned16(meta) || !aligned16(Bsrc) || !aligned16(C) || ldb % 8 != 0 || ldc % 8 != 0)
         return BIMASK_ERR_UNSUPPORTED;
     ColPlan p;
-    if (!col_plan(Adim, K, T, dense, p) || !col_gains(p, Adim, K, dense)) return BIMASK_ERR_UNSUPPORTED;
+    const bool over = !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2);
+    if (!col_plan(Adim, K, T, dense, over && Adim <= 512, p) || !col_gains(p, Adim, K, dense)) return BIMASK_ERR_UNSUPPORTED;
     const bool few = static_cast<int64_t>(p.rpt) * K <= 32 * 256 * 4;    // pieces per fetching thread
 #define BIMASK_CT(TM_, TN_, D_)                                                                                     \
     return few ? run_coltile<TM_, TN_, D_, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, p, s)                   \
@@ -427,7 +429,10 @@ int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, 
     switch (p.tm) {
         case 1: BIMASK_CT_TOKENS(1)
         case 2: BIMASK_CT_TOKENS(2)
-        default: BIMASK_CT_TOKENS(3)
+        case 3: BIMASK_CT_TOKENS(3)
+        default:                                                         // 385 .. 512 rows in one piece, 32 tokens
+            return dense ? run_coltile<4, 1, true, kColUnits>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, p, s)
+                         : run_coltile<4, 1, false, kColUnits>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, p, s);
     }
 #undef BIMASK_CT_TOKENS
 #undef BIMASK_CT_DENSE

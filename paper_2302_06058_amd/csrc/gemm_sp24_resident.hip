@@ -354,7 +354,8 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
     // Eq. (10)'s gather: a token tile turned column by column, where it gains; 256 -> 64 columns and many tokens are a stream
     // that the wavefront-private kernel carries as whole pieces (200704 tokens 32.8 -> 28.8 us, 50000 11.1 / 10.6)
     const bool stream = K == 256 && Adim == 64 && T >= 32768;
-    if (perm && !stream) {
+    // (not with dX on top of dY: both cut the weight rows over workgroups in more cases than this kernel)
+    if (perm && !stream && disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2)) {
         int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
         rc = launch_gemm_sp24_wide(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);

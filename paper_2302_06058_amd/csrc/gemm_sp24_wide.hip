@@ -305,6 +305,7 @@ int launch_gemm_sp24_wide(const void* A, const uint32_t* meta, int64_t Adim, int
     if (K > 512 || K % 8 != 0 || Adim % 8 != 0 || T > 0x7FFFFFFF) return BIMASK_ERR_UNSUPPORTED;
     if (!aligned16(A) || !aligned16(meta) || !aligned16(Bsrc) || !aligned16(C) || ldb % 8 != 0 || ldc % 8 != 0)
         return BIMASK_ERR_UNSUPPORTED;
+    if (!disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2)) return BIMASK_ERR_UNSUPPORTED;     // pieces of weight rows read the same tokens
     // Where it gains (700 random shapes, us, old -> here).  2-of-4, above one stage of 128 terms and 256 columns: 160 -> 512 at 20591
     // tokens 12.6 -> 9.6, 384 -> 3008 with the gather at 20856 77.6 -> 50.6, 352 -> 1256 at 3617 9.9 -> 8.1; not 128 -> 2944 at 13325
     // 18.5 / 20.9, 480 -> 320 at 34188 21.4 / 23.1 apart, few tokens (184 -> 3936 at 3185 11.1 / 12.1) where the weight stream counts, and

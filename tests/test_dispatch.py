@@ -90,6 +90,12 @@ def test_backward_product_on_top_of_its_input_copies_it_first(rec, C_, T, N, M, 
         assert bwd(rec, C_, C_, T, N, M, dtype, dX=dX)[0].kernel.startswith("k_gather_cols"), dX - A
 
 
+@pytest.mark.parametrize("I,J,T,N,M", [(384, 384, 9001, 2, 4), (384, 384, 9001, 4, 8), (512, 512, 9001, 4, 8), (1032, 456, 5003, 2, 4), (392, 392, 17003, 2, 4)])
+def test_fused_gather_in_place_leaves_each_token_row_to_one_workgroup(rec, I, J, T, N, M):
+    (l,) = bwd(rec, I, J, T, N, M, dX=A)
+    assert l.kernel in ("k_gemm_sp24_coltile", "k_gemm_sp24_resident") and l.grid[1] == 1, l
+
+
 # the tile of the streaming kernel (weight rows, tokens, wavefronts M and N, groups), or another kernel
 @pytest.mark.parametrize("I,J,T,N,M,ld,want", [
     (512, 264, 64, 2, 4, 0, "64, 32, 2, 1, 4"), (512, 384, 1024, 2, 4, 0, "64, 32, 2, 1, 4"), (512, 1152, 2000, 2, 4, 0, "64, 64, 2, 2, 2"),
@@ -120,6 +126,7 @@ def test_exact_products_reach_every_instance_of_the_gemm_kernels(rec):
     for I, J, T, N, M, dtype in exact.exact_products():
         code = bm.F32 if dtype == synth.F32 else bm.BF16
         reached.update(fwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code, perm=None))
+        reached.update(bwd(rec, I, J, T, N, M, code, dX=A))              # these: test_fused_gather_in_place
     names = {f"{l.kernel}<{l.args}>" if l.args else l.kernel for l in reached}
     families = ("k_gemm_sp24", "k_gemm_f32", "k_unpermute_dense", "k_gather_cols_rows")
     missing = {k for k in rec.lib.stub_kernels().decode().splitlines() if k.startswith(families)} - names

@@ -334,3 +334,19 @@ def test_large_shapes_with_padded_leading_dimensions():
     assert torch.equal(Yp[:, :I], Y) and torch.equal(dXp[:, :J], dX)
     assert bool((Yp[:, I:] == fill).all()) and bool((dXp[:, J:] == fill).all())
     assert float(Y.float().abs().max()) > 0 and float(dX.float().abs().max()) > 0
+
+
+# rows of the output on the rows of dY that the same workgroup holds: no other workgroup may read them (weight rows in one piece)
+@pytest.mark.parametrize("I,J,T,N,M", [(384, 384, 9001, 2, 4), (384, 384, 17003, 2, 4), (384, 384, 9001, 4, 8), (264, 264, 5003, 4, 8),
+                                       (512, 512, 9001, 4, 8), (1032, 456, 5003, 2, 4), (520, 392, 9001, 2, 4)])
+def test_fused_gather_in_place(I, J, T, N, M):
+    import torch
+    rng = np.random.default_rng(7665 + I + T)
+    W = to_dev(synth.store(int_weights(I, J, rng), synth.BF16), synth.BF16)
+    dY = to_dev(synth.store(sparse_rows(T, I, rng), synth.BF16), synth.BF16)
+    P = i32_dev(rng.permutation(I).astype(np.int32))
+    _, vb, ib = bm.bimask_backward_mask_compress(W, N, M, bm.bimask_forward_mask(W, N, M), P)
+    want = bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, I, J, N, M)
+    rest = dY[:, J:].clone()
+    bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, I, J, N, M, dX=dY[:, :J])
+    assert torch.equal(dY[:, :J], want) and torch.equal(dY[:, J:], rest)
