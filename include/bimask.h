@@ -188,11 +188,12 @@ BIMASK_API int bimask_sparse_gemm_fwd(const void *X, int64_t T, int64_t ldx, con
 
 /* Backward GEMM, Eq. (10):  dX[t][j] = sum_r dY[t][P[r]] * (Bbar .* W[P,:])[r][j], with the
  * weight operand given in transposed compressed form (transposed = 1); perm = NULL is Eq. (8).
- *   dY  in  T x I (lddy >= I);   dX  out  T x J (lddx >= J).  dX may lie on dY only in calls with a
- *   permutation that ask for a workspace (dY is then copied first).
+ *   dY  in  T x I (lddy >= I);   dX  out  T x J (lddx >= J).  dX may lie on dY in calls with a
+ *   permutation: anywhere where the call asks for a workspace (dY is then copied first), elsewhere
+ *   with the same first element and leading dimension.
  *   workspace: bimask_workspace_bytes(BIMASK_WS_GEMM_BWD, ...) bytes (holds dY[:,P], or for
  *   N > 2 the weights with their columns in natural order, when the gather is not fused into the
- *   GEMM; 0 = none needed; fp32 with a permutation always needs it, small products leave it
+ *   GEMM; 0 = none needed; fp32 with a permutation always needs it; calls may leave it
  *   untouched).  bf16 with N <= 2 fuses it for
  *   I <= 512 and for 512 < I <= 2048 with J <= min(I, 512), I and J multiples of 8; bf16 with
  *   N > 2 for 128 < I <= 2048 with J <= min(I, 512), I and J multiples of 8.  Apart from the

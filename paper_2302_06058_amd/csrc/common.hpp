@@ -142,9 +142,13 @@ inline bool streams_out(const void* C, int64_t Adim, int64_t ldc, bool whole_row
     return (whole_rows && ldc == Adim) || (Adim % 32 == 0 && ldc % 32 == 0 && (reinterpret_cast<uintptr_t>(C) & 63u) == 0);
 }
 
-// Two matrices of T rows that share no byte of the ranges they span.
+// Two matrices of T rows that share no byte: ranges apart, or column ranges apart in the rows of one buffer (equal pitch).
 inline bool disjoint(const void* a, int64_t T, int64_t lda, int64_t cols_a, const void* b, int64_t ldb, int64_t cols_b, size_t esz) {
     const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    if (lda == ldb) {
+        const uintptr_t pitch = lda * esz, d = b0 >= a0 ? (b0 - a0) % pitch : (pitch - (a0 - b0) % pitch) % pitch;
+        if (d >= cols_a * esz && d + cols_b * esz <= pitch) return true;
+    }
     return a0 + ((T - 1) * lda + cols_a) * esz <= b0 || b0 + ((T - 1) * ldb + cols_b) * esz <= a0;
 }
 

@@ -419,7 +419,7 @@ int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, 
         return BIMASK_ERR_UNSUPPORTED;
     ColPlan p;
     const bool over = !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2);
-    if (!col_plan(Adim, K, T, dense, over && Adim <= 512, p) || !col_gains(p, Adim, K, dense)) return BIMASK_ERR_UNSUPPORTED;
+    if (!col_plan(Adim, K, T, dense, over, p) || !col_gains(p, Adim, K, dense)) return BIMASK_ERR_UNSUPPORTED;
     const bool few = static_cast<int64_t>(p.rpt) * K <= 32 * 256 * 4;    // pieces per fetching thread
 #define BIMASK_CT(TM_, TN_, D_)                                                                                     \
     return few ? run_coltile<TM_, TN_, D_, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, p, s)                   \

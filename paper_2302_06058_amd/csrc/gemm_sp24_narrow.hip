@@ -574,6 +574,8 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
     if (K % 8 != 0 ? (ldb != K || perm) : ldb % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
     if (Adim % 8 != 0 ? ldc != Adim : ldc % 8 != 0) return BIMASK_ERR_UNSUPPORTED;
     const int nstg = static_cast<int>(ceil_div(K, 128)), tm = static_cast<int>(ceil_div(Adim, 32));
+    // six row tiles and more go to two wavefronts, which both read the token rows: not with dX on top of dY
+    if (perm && tm > 5 && !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2)) return BIMASK_ERR_UNSUPPORTED;
 #define BIMASK_ROWS(TM_, NP_, W_)                                                                                     \
     return perm ? run_narrow_rows<TM_, NP_, true, W_>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s)                \
                 : run_narrow_rows<TM_, NP_, false, W_>(A, meta, Adim, K, Bsrc, ldb, nullptr, T, C, ldc, s);

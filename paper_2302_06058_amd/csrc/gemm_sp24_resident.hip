@@ -292,7 +292,7 @@ constexpr unsigned kPersistGrid = 768;     // persistent variant: three workgrou
 
 template <int BM, int BN, int WAVES_M, int NSTG, bool PERSIST = false>
 int run_resident(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,
-                 const int32_t* perm, int64_t T, void* C, int64_t ldc, int rpt, hipStream_t s) {
+                 const int32_t* perm, int64_t T, void* C, int64_t ldc, int rpt, bool whole, hipStream_t s) {
     using S = ResSmem<BM, BN, NSTG, PERSIST>;
     auto kern = k_gemm_sp24_resident<BM, BN, WAVES_M, NSTG, PERSIST>;
     if (S::kTotal > 48 * 1024) {
@@ -321,7 +321,8 @@ int run_resident(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, c
     // few token tiles: split the weight tiles over blockIdx.y, as far as one round of 256
     // workgroups goes (the kernel runs one workgroup per CU; a second round costs a full pass)
     const int64_t tiles_all = ceil_div(Adim, BM);
-    int64_t groups = 256 / grid;
+    // (`whole`: dX lies on dY, and a workgroup may write no token row that another one still has to read)
+    int64_t groups = whole ? 1 : 256 / grid;
     if (groups < 1) groups = 1;
     if (groups > tiles_all) groups = tiles_all;
     hipLaunchKernelGGL(kern, dim3(grid, static_cast<unsigned>(groups)), dim3(64 * WAVES_M), S::kTotal, s,
@@ -354,8 +355,9 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
     // Eq. (10)'s gather: a token tile turned column by column, where it gains; 256 -> 64 columns and many tokens are a stream
     // that the wavefront-private kernel carries as whole pieces (200704 tokens 32.8 -> 28.8 us, 50000 11.1 / 10.6)
     const bool stream = K == 256 && Adim == 64 && T >= 32768;
-    // (not with dX on top of dY: both cut the weight rows over workgroups in more cases than this kernel)
-    if (perm && !stream && disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2)) {
+    // dX on top of dY: a kernel takes it only where it keeps all weight rows of a token row in one workgroup
+    const bool over = !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2);
+    if (perm && !stream) {
         int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
         rc = launch_gemm_sp24_wide(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
@@ -370,23 +372,23 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
         // one narrow weight tile: the workgroup is a latency chain (fill, multiply, store), so
         // small token tiles on 4 wavefronts with few registers let three of them share a CU
         const int rpt = pick_rows_per_tile(T, 32, 256);
-        if (nstg == 1) return run_resident<128, 32, 4, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s);
-        return run_resident<128, 32, 4, 2, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s);
+        if (nstg == 1) return run_resident<128, 32, 4, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s);
+        return run_resident<128, 32, 4, 2, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s);
     }
     // few tokens: full 64-row tiles (the weight tiles are split over workgroups instead)
     const int rpt = ceil_div(T, 64) <= 128 ? 64 : pick_rows_per_tile(T, 64, 256);
 #define BIMASK_RES(WAVES) \
     switch (nstg) { \
-        case 1: return run_resident<256, 64, WAVES, 1>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
-        case 2: return run_resident<256, 64, WAVES, 2>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
-        case 3: return run_resident<256, 64, WAVES, 3>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
-        default: return run_resident<256, 64, WAVES, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, s); \
+        case 1: return run_resident<256, 64, WAVES, 1>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s); \
+        case 2: return run_resident<256, 64, WAVES, 2>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s); \
+        case 3: return run_resident<256, 64, WAVES, 3>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s); \
+        default: return run_resident<256, 64, WAVES, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, rpt, over, s); \
     }
     // Many token tiles per CU and one stage: persistent workgroups fetch the next tile's rows during the current one.  With two stages
     // the fetched rows don't fit in registers beside the fragments (74 spilled: 160 -> 552 columns at 168539 tokens 191.9 us against 93.0
     // with a workgroup per tile, 216 -> 216 at 99193 48.0 / 30.6).
     if (nstg == 1 && ceil_div(T, 64) >= 1024)
-        return run_resident<256, 64, 8, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, 64, s);
+        return run_resident<256, 64, 8, 1, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, 64, over, s);
     BIMASK_RES(8)
 #undef BIMASK_RES
 }

@@ -2,7 +2,9 @@
 that records launches instead of making them (tests/dispatch/hip_stub.cpp).  Pointers are never dereferenced."""
 import collections
 import ctypes
+import math
 import os
+import random
 import re
 import shutil
 import subprocess
@@ -66,9 +68,9 @@ def fwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, ld=0, X=A):
     return l
 
 
-def bwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, dY=A, dX=D, ld=0, perm=C):
+def bwd(rec, I, J, T, N=2, M=4, dtype=bm.BF16, dY=A, dX=D, ld=0, perm=C, lddx=0):
     need = bm.workspace_bytes(bm.WS_GEMM_BWD, I, J, T, 0, dtype, N, M)
-    st, l = rec("bimask_sparse_gemm_bwd", dY, T, ld or I, perm, B, C, I, J, dtype, N, M, dX, J, E, need, None)
+    st, l = rec("bimask_sparse_gemm_bwd", dY, T, ld or I, perm, B, C, I, J, dtype, N, M, dX, lddx or J, E, need, None)
     assert st == 0
     return l
 
@@ -94,6 +96,41 @@ def test_backward_product_on_top_of_its_input_copies_it_first(rec, C_, T, N, M, 
 def test_fused_gather_in_place_leaves_each_token_row_to_one_workgroup(rec, I, J, T, N, M):
     (l,) = bwd(rec, I, J, T, N, M, dX=A)
     assert l.kernel in ("k_gemm_sp24_coltile", "k_gemm_sp24_resident") and l.grid[1] == 1, l
+
+
+def pieces_of_weight_rows(l, J):
+    """Workgroups that read the same token rows, each for some of the J weight rows."""
+    if l.kernel.startswith("k_gemm_sp24_narrow"):        # 32 weight rows per row tile; the pieces follow each other in blockIdx.x
+        return -(-J // (32 * int(l.args.split(",")[0])))
+    assert l.kernel in ("k_gemm_sp24_coltile", "k_gemm_sp24_resident"), l
+    return l.grid[1]
+
+
+@pytest.mark.parametrize("I,J,T,N,M", exact.IN_PLACE_SHAPES)
+def test_dX_on_dY_without_a_workspace_leaves_each_token_row_to_one_workgroup(rec, I, J, T, N, M):
+    ld = max(I, J)
+    (l,) = bwd(rec, I, J, T, N, M, dX=A, ld=ld, lddx=ld)
+    assert pieces_of_weight_rows(l, J) == 1, l
+
+
+def test_dX_on_dY_without_a_workspace_over_all_forms(rec):
+    rng = random.Random(31)
+    for _ in range(3000):
+        N, M = rng.choice(((2, 4), (1, 4), (2, 8), (4, 8)))
+        I, J = (M * round(math.exp(rng.uniform(0, math.log(c / M)))) for c in (2048, 4608))
+        T, ld = round(math.exp(rng.uniform(0, 12))), (max(I, J) + rng.choice((0, 0, 2, 8)) + 1) // 2 * 2
+        if bm.workspace_bytes(bm.WS_GEMM_BWD, I, J, T, 0, bm.BF16, N, M) or (I > 512 or N > 2) and ld % 8:
+            continue
+        (l,) = bwd(rec, I, J, T, N, M, dX=A, ld=ld, lddx=ld)
+        assert pieces_of_weight_rows(l, J) == 1, (I, J, T, N, M, ld, l)
+
+
+@pytest.mark.parametrize("I,J,T,N,M", [(384, 384, 25216, 2, 4), (256, 64, 40000, 2, 4), (1152, 384, 25216, 2, 4), (384, 1536, 9000, 4, 8), (128, 256, 3000, 2, 4)])
+def test_dX_beside_dY_in_one_buffer_takes_the_way_of_separate_buffers(rec, I, J, T, N, M):
+    ld = I + J
+    apart = bwd(rec, I, J, T, N, M, ld=ld, lddx=ld)
+    assert bwd(rec, I, J, T, N, M, dX=A + 2 * I, ld=ld, lddx=ld) == apart and bwd(rec, I, J, T, N, M, dX=A - 2 * J, ld=ld, lddx=ld) == apart
+    assert bwd(rec, I, J, T, N, M, dX=A + 2 * ld * (T // 2) + 2 * I, ld=ld, lddx=ld) == apart
 
 
 # the tile of the streaming kernel (weight rows, tokens, wavefronts M and N, groups), or another kernel

@@ -336,9 +336,14 @@ def test_large_shapes_with_padded_leading_dimensions():
     assert float(Y.float().abs().max()) > 0 and float(dX.float().abs().max()) > 0
 
 
-# rows of the output on the rows of dY that the same workgroup holds: no other workgroup may read them (weight rows in one piece)
-@pytest.mark.parametrize("I,J,T,N,M", [(384, 384, 9001, 2, 4), (384, 384, 17003, 2, 4), (384, 384, 9001, 4, 8), (264, 264, 5003, 4, 8),
-                                       (512, 512, 9001, 4, 8), (1032, 456, 5003, 2, 4), (520, 392, 9001, 2, 4)])
+# dX on dY, same first element and pitch, in calls that need no workspace: no workgroup may write a token row that another one still
+# has to read (few tokens, where the weight rows are cut over the grid otherwise; wavefront-private tiles; more columns than dY has)
+IN_PLACE_SHAPES = [(384, 384, 9001, 2, 4), (384, 384, 17003, 2, 4), (384, 384, 9001, 4, 8), (264, 264, 5003, 4, 8), (512, 512, 9001, 4, 8),
+                   (1032, 456, 5003, 2, 4), (520, 392, 9001, 2, 4), (384, 384, 5000, 2, 4), (512, 512, 8192, 2, 4), (264, 264, 8000, 2, 4),
+                   (64, 256, 3000, 2, 4), (128, 176, 777, 2, 4), (256, 64, 40000, 2, 4), (260, 388, 1000, 2, 4), (512, 2304, 100, 2, 4)]
+
+
+@pytest.mark.parametrize("I,J,T,N,M", IN_PLACE_SHAPES)
 def test_fused_gather_in_place(I, J, T, N, M):
     import torch
     rng = np.random.default_rng(7665 + I + T)
@@ -347,6 +352,7 @@ def test_fused_gather_in_place(I, J, T, N, M):
     P = i32_dev(rng.permutation(I).astype(np.int32))
     _, vb, ib = bm.bimask_backward_mask_compress(W, N, M, bm.bimask_forward_mask(W, N, M), P)
     want = bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, I, J, N, M)
-    rest = dY[:, J:].clone()
-    bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, I, J, N, M, dX=dY[:, :J])
-    assert torch.equal(dY[:, :J], want) and torch.equal(dY[:, J:], rest)
+    buf = torch.full((T, max(I, J)), 3.0, dtype=torch.bfloat16, device=W.device)
+    buf[:, :I] = dY
+    bm.bimask_sparse_gemm_bwd(buf[:, :I], P, vb, ib, I, J, N, M, dX=buf[:, :J])
+    assert torch.equal(buf[:, :J], want) and torch.equal(buf[:, J:], dY[:, J:])
