@@ -224,3 +224,22 @@ def test_search_falls_back_where_the_lds_limit_cannot_be_raised(rec):
     finally:
         rec.lib.stub_refuse_lds(0)
     assert search(rec, 3072, 1504, 2, 4, 100) == "k_perm_score_lds"
+
+
+def test_no_kernel_keeps_registers_in_scratch(rec, tmp_path):
+    """A spilled register is reloaded through the vector-memory path, in order behind every load and store in flight."""
+    from paper_2302_06058_amd import build as b
+    llvm = "/opt/rocm/llvm/bin/"
+    if not os.path.exists(llvm + "llvm-readelf") or not os.path.isdir(b.OBJ):
+        pytest.skip("no LLVM tools or no library objects")
+    kernels = 0
+    for s in b.SOURCES:
+        obj, fat, co = os.path.join(b.OBJ, s[:-4] + ".o"), str(tmp_path / "fat"), str(tmp_path / "co")
+        if not os.path.exists(obj) or subprocess.run([llvm + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, obj, os.devnull], stderr=subprocess.DEVNULL).returncode:
+            continue                                     # (no kernels in this file)
+        subprocess.run([llvm + "clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat, "--output=" + co], check=True)
+        notes = subprocess.run([llvm + "llvm-readelf", "--notes", co], check=True, capture_output=True, text=True).stdout
+        scratch = dict(re.findall(r"\.name: +(_Z\S+)\n +\.private_segment_fixed_size: (\d+)", notes))
+        assert not any(map(int, scratch.values())), {k: v for k, v in scratch.items() if v != "0"}
+        kernels += len(scratch)
+    assert kernels >= len(rec.lib.stub_kernels().decode().splitlines())
