@@ -220,9 +220,12 @@ int launch_gemm_sp24_big(const void* A, const uint32_t* meta, int64_t Adim, int6
 int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
                               int64_t ldb, const int32_t* perm, int64_t T, void* C, int64_t ldc,
                               hipStream_t s);
-// wavefront-private variant for narrow weights (Adim <= 256 with K <= 128, Adim <= 64 with K <= 256); BIMASK_ERR_UNSUPPORTED otherwise
+// wavefront-private variant for narrow weights (Adim <= 256 with K <= 128, Adim <= 64 with K <= 512 and, with many tokens, Adim <= 128
+// with K <= 256; with a permutation K <= 128 and what the next function names); BIMASK_ERR_UNSUPPORTED otherwise
 int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
                             int64_t ldb, const int32_t* perm, int64_t T, void* C, int64_t ldc, hipStream_t s);
+// Longer contractions that it takes with a permutation before the column-tile kernel.
+bool gemm_sp24_narrow_streams(int64_t Adim, int64_t K, int64_t T);
 // backward GEMM on token tiles turned column by column in LDS (128 < K <= 2048), gather fused; BIMASK_ERR_UNSUPPORTED outside what it
 // takes and where another kernel is the faster (dense: the weight operand is the dense masked matrix of a ratio with N > 2, meta unused)
 int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc, int64_t ldb,

@@ -344,7 +344,8 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
     int64_t tile = wave_id;
     if (tile >= ntiles) return;
     // (The walks start from copies the optimiser cannot see through: hoisted out of the tile loop, the addresses of all pieces
-    // would occupy a few dozen registers for the whole kernel.)
+    // would occupy a few dozen registers for the whole kernel.  Whole pieces need fewer, and have them but in the largest instance.)
+    constexpr bool HIDE = !WHOLE || TM * NP >= 40;
 
     u32x4 v[NP];
     auto load = [&](int64_t tl) {
@@ -352,7 +353,7 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
         const int last = static_cast<int>(T - t0 < 32 ? T - t0 : 32) - 1;
         const uint8_t* base = reinterpret_cast<const uint8_t*>(Bsrc + t0 * ldb);
         int r = rB, g = gB;
-        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));       // see above
+        if constexpr (HIDE) asm volatile("" : "+v"(r), "+v"(g));       // see above
 #pragma unroll
         for (int it = 0; it < NP; ++it) {
             v[it] = *reinterpret_cast<const u32x4*>(base + static_cast<uint32_t>((r < last ? r : last) * (2 * ldb) + 16 * g));
@@ -384,7 +385,7 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
     auto put = [&]() {                                       // registers -> LDS rows
         wave_lds_fence();                                    // the previous tile's output rows have been read
         int r = rB, g = gB;
-        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+        if constexpr (HIDE) asm volatile("" : "+v"(r), "+v"(g));
 #pragma unroll
         for (int it = 0; it < NP; ++it) {
             uint8_t* row = area + (WHOLE || r < 32 ? r : 32) * pitchB;
@@ -463,7 +464,7 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
         uint8_t* base = reinterpret_cast<uint8_t*>(C + t0 * ldc);
         u32x4 o[NOUT];
         int r = rC, g = gC;
-        if constexpr (!WHOLE) asm volatile("" : "+v"(r), "+v"(g));
+        if constexpr (HIDE) asm volatile("" : "+v"(r), "+v"(g));
 #pragma unroll
         for (int it = 0; it < NOUT; ++it) {
             const bool in = WHOLE || r < 32;
@@ -475,7 +476,7 @@ k_gemm_sp24_narrow_rows(const uint16_t* __restrict__ A_all, const uint32_t* __re
         }
         auto emit = [&](bool stream) {
             int re = rC, ge = gC;
-            if constexpr (!WHOLE) asm volatile("" : "+v"(re), "+v"(ge));
+            if constexpr (HIDE) asm volatile("" : "+v"(re), "+v"(ge));
 #pragma unroll
             for (int it = 0; it < NOUT; ++it) {
                 const bool in = WHOLE || re < 32;
@@ -564,6 +565,12 @@ int run_narrow_rows(const void* A, const uint32_t* meta, int64_t Adim, int64_t K
 
 }  // namespace
 
+// Whole pieces and whole row tiles (us, column tiles -> here: 256 -> 32 columns at 5212 tokens 4.1 -> 3.7, at 122211 17.7 -> 15.8; 256
+// -> 64 at 20709 6.3 -> 5.4, at 200704 32.8 -> 28.8, from 96 tiles on: at 1509 3.7 / 3.8; ragged, 256 -> 56 at 20000 5.8 / 6.6).
+bool gemm_sp24_narrow_streams(int64_t Adim, int64_t K, int64_t T) {
+    return K == 256 && (Adim == 32 || (Adim == 64 && T >= 3072));
+}
+
 // Returns BIMASK_ERR_UNSUPPORTED when the shape, the alignment or the leading dimensions are
 // outside what this kernel handles (the caller then takes the workgroup-tiled kernels).
 int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
@@ -576,42 +583,36 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
     const int nstg = static_cast<int>(ceil_div(K, 128)), tm = static_cast<int>(ceil_div(Adim, 32));
     // six row tiles and more go to two wavefronts, which both read the token rows: not with dX on top of dY
     if (perm && tm > 5 && !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2)) return BIMASK_ERR_UNSUPPORTED;
-#define BIMASK_ROWS(TM_, NP_, W_)                                                                                     \
-    return perm ? run_narrow_rows<TM_, NP_, true, W_>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s)                \
-                : run_narrow_rows<TM_, NP_, false, W_>(A, meta, Adim, K, Bsrc, ldb, nullptr, T, C, ldc, s);
+// WHOLE where the pieces fill an instance (K = 16 NP) and the weight rows its row tiles: every walk over pieces has constant steps
+    // (K = 64 and 128 on 32 .. 256 columns, us, ragged form -> whole: 96 <- 128 at 7003 tokens 3.95 -> 3.0, 128 -> 32 with the gather at
+    // 121643 9.03 -> 7.4, 160 <- 64 at 31836 5.63 -> 4.8, from 0.70 of the ragged time at 4000 tokens to 0.97 at 400000).
+#define BIMASK_ROWS_FORM(TM_, NP_, P_, PERM_)                                                                         \
+    return K == 16 * NP_ && Adim % (32 * TM_) == 0 ? run_narrow_rows<TM_, NP_, P_, true>(A, meta, Adim, K, Bsrc, ldb, PERM_, T, C, ldc, s)  \
+                                                   : run_narrow_rows<TM_, NP_, P_, false>(A, meta, Adim, K, Bsrc, ldb, PERM_, T, C, ldc, s);
+#define BIMASK_ROWS(TM_, NP_) { if (perm) BIMASK_ROWS_FORM(TM_, NP_, true, perm) BIMASK_ROWS_FORM(TM_, NP_, false, nullptr) }
 #define BIMASK_ROWS_PLAIN(TM_, NP_) return run_narrow_rows<TM_, NP_, false, false>(A, meta, Adim, K, Bsrc, ldb, nullptr, T, C, ldc, s);
     if (K % 8 == 0 && Adim % 8 == 0) {
-        if (K == 64) {                                       // the first ResNet stage: pieces and row tiles all whole
-            if (Adim == 64) BIMASK_ROWS(2, 4, true)
-            if (Adim == 128 || Adim == 256) BIMASK_ROWS(4, 4, true)
-        } else if (K == 128) {
-            if (Adim == 64) BIMASK_ROWS(2, 8, true)
-            if (Adim == 128 || Adim == 256) BIMASK_ROWS(4, 8, true)
-        } else if (K == 256 && Adim == 64) BIMASK_ROWS(2, 16, true)
-        if (K <= 64) {
-            switch (tm) {
-                case 1: BIMASK_ROWS(1, 4, false)
-                case 2: BIMASK_ROWS(2, 4, false)
-                case 3: case 6: BIMASK_ROWS(3, 4, false)     // six to eight row tiles: two wavefronts per token tile
-                case 4: case 7: case 8: BIMASK_ROWS(4, 4, false)
-                case 5: BIMASK_ROWS(5, 4, false)
-                default: break;
+        if (nstg == 1) {
+#define BIMASK_ROWS_TILES(NP_)                                                                                        \
+            switch (tm) {                                                                                             \
+                case 1: BIMASK_ROWS(1, NP_)                                                                           \
+                case 2: BIMASK_ROWS(2, NP_)                                                                           \
+                case 3: case 6: BIMASK_ROWS(3, NP_)          /* six to eight row tiles: two wavefronts per token tile */ \
+                case 4: case 7: case 8: BIMASK_ROWS(4, NP_)                                                           \
+                case 5: BIMASK_ROWS(5, NP_)                                                                           \
+                default: break;                                                                                       \
             }
-        } else if (nstg == 1) {
-            switch (tm) {
-                case 1: BIMASK_ROWS(1, 8, false)
-                case 2: BIMASK_ROWS(2, 8, false)
-                case 3: case 6: BIMASK_ROWS(3, 8, false)
-                case 4: case 7: case 8: BIMASK_ROWS(4, 8, false)
-                case 5: BIMASK_ROWS(5, 8, false)
-                default: break;
-            }
-        } else if (!perm && (tm <= 2 || (tm <= 4 && nstg == 2 && T >= 16384))) {
-            // longer contractions: at most 64 weight rows, all their fragments in registers (with a permutation: column tiles).
-            // Up to 128 rows on two wavefronts per token tile gain with two stages and many tokens (256 -> 128 columns at 200704
-            // tokens 36.2 -> 32.0 us, 224 -> 88 at 30096 10.1 -> 7.6; 256 -> 104 at 15659 5.2, two wavefronts 5.9).
+            if (K <= 64) BIMASK_ROWS_TILES(4) else BIMASK_ROWS_TILES(8)
+#undef BIMASK_ROWS_TILES
+        } else if (perm) {                                   // longer contractions with the gather: column tiles, but for these
+            if (!gemm_sp24_narrow_streams(Adim, K, T)) return BIMASK_ERR_UNSUPPORTED;
+            if (tm == 1) return run_narrow_rows<1, 16, true, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
+            return run_narrow_rows<2, 16, true, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
+        } else if (tm <= 2 || (tm <= 4 && nstg == 2 && T >= 16384)) {
+            // Longer contractions: at most 64 weight rows, all their fragments in registers.  Up to 128 rows on two wavefronts per token
+            // tile gain with two stages and many tokens (256 -> 128 columns at 180062 tokens 25.0 -> 22.8 us, 224 -> 88 at 30096 10.1 -> 7.6).
             switch (nstg) {
-                case 2: if (tm == 1) BIMASK_ROWS_PLAIN(1, 16) else BIMASK_ROWS_PLAIN(2, 16)
+                case 2: if (tm == 1) BIMASK_ROWS_FORM(1, 16, false, nullptr) else BIMASK_ROWS_FORM(2, 16, false, nullptr)
                 case 3: if (tm == 1) BIMASK_ROWS_PLAIN(1, 24) else BIMASK_ROWS_PLAIN(2, 24)
                 case 4: if (tm == 1) BIMASK_ROWS_PLAIN(1, 32) else BIMASK_ROWS_PLAIN(2, 32)
                 default: break;
@@ -621,6 +622,7 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
     }
 #undef BIMASK_ROWS_PLAIN
 #undef BIMASK_ROWS
+#undef BIMASK_ROWS_FORM
 #define BIMASK_NARROW(TM_, NSTG_) return run_narrow<TM_, NSTG_>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
     if (nstg == 1) {
         switch (tm) {

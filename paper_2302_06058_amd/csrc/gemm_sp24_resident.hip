@@ -352,12 +352,10 @@ int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim,
                               hipStream_t s) {
     if (K > 512) return BIMASK_ERR_UNSUPPORTED;
     if (!aligned16(A) || !aligned16(meta)) return BIMASK_ERR_ALIGN;
-    // Eq. (10)'s gather: a token tile turned column by column, where it gains; 256 -> 64 columns and many tokens are a stream
-    // that the wavefront-private kernel carries as whole pieces (200704 tokens 32.8 -> 28.8 us, 50000 11.1 / 10.6)
-    const bool stream = K == 256 && Adim == 64 && T >= 32768;
     // dX on top of dY: a kernel takes it only where it keeps all weight rows of a token row in one workgroup
     const bool over = !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2);
-    if (perm && !stream) {
+    // Eq. (10)'s gather: a token tile turned column by column or resident for eight wavefronts, where they gain
+    if (perm && !gemm_sp24_narrow_streams(Adim, K, T)) {
         int rc = launch_gemm_sp24_coltile(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);
         if (rc != BIMASK_ERR_UNSUPPORTED) return rc;
         rc = launch_gemm_sp24_wide(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s, false);

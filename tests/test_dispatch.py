@@ -147,6 +147,24 @@ def test_split_contractions_are_taken_where_they_gain(rec, I, J, T, N, M, ld, wa
     assert (l.args.startswith(want + ", ") if l.kernel == "k_gemm_sp24" else l.kernel == want), l
 
 
+# forward products (K terms to A columns) on the wavefront-private kernel: whole pieces and row tiles whatever their number
+@pytest.mark.parametrize("K", [64, 128])
+@pytest.mark.parametrize("A_", [32, 64, 96, 128, 160, 192, 256])
+def test_whole_pieces_and_row_tiles_take_the_instance_for_them(rec, K, A_):
+    for T in (100, 70000):
+        for l in (*fwd(rec, A_, K, T), *bwd(rec, K, A_, T)):
+            assert l.kernel == "k_gemm_sp24_narrow_rows" and l.args.endswith("true"), l
+    for l in (*fwd(rec, A_, K - 8, 100), *fwd(rec, A_ - 8, K, 100), *bwd(rec, K - 8, A_, 100)):
+        assert l.kernel == "k_gemm_sp24_narrow_rows" and l.args.endswith("false"), l
+
+
+@pytest.mark.parametrize("I,J,T,want", [
+    (256, 32, 100, "narrow_rows"), (256, 64, 4000, "narrow_rows"), (256, 64, 40000, "narrow_rows"), (256, 64, 2000, "coltile"), (256, 56, 40000, "coltile"), (248, 64, 40000, "coltile"),
+    (144, 32, 48000, "coltile"), (168, 32, 200000, "coltile"), (144, 40, 200000, "coltile")])
+def test_narrow_gathers_of_two_stages(rec, I, J, T, want):
+    assert bwd(rec, I, J, T)[0].kernel == "k_gemm_sp24_" + want
+
+
 def test_dense_backward_puts_the_weights_in_natural_order(rec):
     for (I, J, N, M, T), rows in small.NATURAL_ORDER.items():
         l = bwd(rec, I, J, T, N, M)

@@ -173,13 +173,16 @@ def test_column_tiles_are_exact(I, J, T, N, M):
 
 
 # Wavefront-private tiles: rows in 16-byte pieces, 1 to 5 row tiles (6 to 8 on two wavefronts), 1 to 4 stages, every piece and row tile
-# whole or ragged; rows that are no multiple of 16 bytes; three token rows in the last tile; more tiles than wavefronts on the chip
+# whole or ragged (whole ones with constant steps over the pieces: 64, 128, 256 terms on multiples of 32 columns); rows that are no multiple of 16 bytes; three token rows in the last tile; more tiles than wavefronts on the chip
 NARROW_SHAPES = [(24, 56, 67), (56, 24, 67), (64, 88, 131), (88, 64, 131), (48, 120, 99), (120, 48, 99), (56, 152, 163), (152, 56, 163),
                  (24, 120, 99), (120, 24, 99), (88, 120, 131), (120, 88, 131), (152, 120, 163), (120, 152, 163), (176, 56, 195), (56, 248, 259),
                  (24, 248, 259), (24, 376, 387), (56, 376, 387), (24, 504, 515), (56, 504, 515), (104, 200, 16403),
                  (64, 64, 99), (128, 64, 131), (64, 128, 131), (128, 128, 131), (64, 256, 259), (256, 64, 32771),
                  (28, 64, 99), (28, 256, 259), (28, 384, 387), (28, 512, 515), (60, 256, 259), (60, 384, 387), (60, 512, 515), (92, 128, 131), (156, 128, 163),
-                 (60, 64, 99), (56, 24, 140003), (88, 120, 140003), (64, 64, 140003)]
+                 (60, 64, 99), (56, 24, 140003), (88, 120, 140003), (64, 64, 140003),
+                 (32, 64, 99), (64, 32, 99), (96, 64, 131), (64, 96, 131), (64, 160, 163), (160, 64, 163), (64, 192, 195), (96, 128, 131), (128, 96, 131),
+                 (160, 128, 163), (128, 160, 163), (128, 192, 195), (32, 128, 99), (128, 32, 99), (32, 256, 259), (256, 32, 3103), (64, 256, 3075), (256, 64, 3075),
+                 (128, 256, 16387)]
 
 
 @pytest.mark.parametrize("I,J,T", NARROW_SHAPES)
