@@ -567,8 +567,12 @@ int run_narrow_rows(const void* A, const uint32_t* meta, int64_t Adim, int64_t K
 
 // Whole pieces and whole row tiles (us, column tiles -> here: 256 -> 32 columns at 5212 tokens 4.1 -> 3.7, at 122211 17.7 -> 15.8; 256
 // -> 64 at 20709 6.3 -> 5.4, at 200704 32.8 -> 28.8, from 96 tiles on: at 1509 3.7 / 3.8; ragged, 256 -> 56 at 20000 5.8 / 6.6).
+// A second stage that is nearly all padding, one row tile and many tokens, where column tiles of 64 tokens are many short rounds
+// (144 -> 32 at 246298 29.7 -> 24.0, 136 -> 16 at 333432 36.6 -> 26.7, 160 -> 32 at 164190 21.2 -> 19.4; at 53342, 160 -> 8, 9.0 / 8.2
+// in cache and 9.4 / 9.5 from memory, 192 -> 32 at 197689 24.1 / 24.9).
 bool gemm_sp24_narrow_streams(int64_t Adim, int64_t K, int64_t T) {
-    return K == 256 && (Adim == 32 || (Adim == 64 && T >= 3072));
+    if (K == 256) return Adim == 32 || (Adim == 64 && T >= 3072);
+    return K > 128 && K <= 160 && Adim <= 32 && T >= 49152;
 }
 
 // Returns BIMASK_ERR_UNSUPPORTED when the shape, the alignment or the leading dimensions are
@@ -606,11 +610,14 @@ int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, i
 #undef BIMASK_ROWS_TILES
         } else if (perm) {                                   // longer contractions with the gather: column tiles, but for these
             if (!gemm_sp24_narrow_streams(Adim, K, T)) return BIMASK_ERR_UNSUPPORTED;
+            if (K < 256) return run_narrow<1, 2>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
             if (tm == 1) return run_narrow_rows<1, 16, true, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
             return run_narrow_rows<2, 16, true, true>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, s);
-        } else if (tm <= 2 || (tm <= 4 && nstg == 2 && T >= 16384)) {
+        } else if (tm <= 2 || (tm <= 4 && nstg == 2 && T >= (K < 256 || Adim == 128 ? 16384 : 98304))) {
             // Longer contractions: at most 64 weight rows, all their fragments in registers.  Up to 128 rows on two wavefronts per token
-            // tile gain with two stages and many tokens (256 -> 128 columns at 180062 tokens 25.0 -> 22.8 us, 224 -> 88 at 30096 10.1 -> 7.6).
+            // tile gain with two stages and many tokens: below 256 terms against the resident kernel (224 -> 88 columns at 30096
+            // tokens 10.1 -> 7.6 us), at 256 against the streaming one, with whole row tiles (256 -> 128 at 18762 5.3 -> 4.9, at 73446
+            // 12.6 -> 9.9, at 180062 25.0 -> 22.8) sooner than with ragged ones (256 -> 104 at 44161 7.5 / 10.0, at 106868 17.5 / 17.5).
             switch (nstg) {
                 case 2: if (tm == 1) BIMASK_ROWS_FORM(1, 16, false, nullptr) else BIMASK_ROWS_FORM(2, 16, false, nullptr)
                 case 3: if (tm == 1) BIMASK_ROWS_PLAIN(1, 24) else BIMASK_ROWS_PLAIN(2, 24)

@@ -160,9 +160,16 @@ def test_whole_pieces_and_row_tiles_take_the_instance_for_them(rec, K, A_):
 
 @pytest.mark.parametrize("I,J,T,want", [
     (256, 32, 100, "narrow_rows"), (256, 64, 4000, "narrow_rows"), (256, 64, 40000, "narrow_rows"), (256, 64, 2000, "coltile"), (256, 56, 40000, "coltile"), (248, 64, 40000, "coltile"),
-    (144, 32, 48000, "coltile"), (168, 32, 200000, "coltile"), (144, 40, 200000, "coltile")])
+    (144, 32, 70000, "narrow"), (160, 8, 70000, "narrow"), (144, 32, 48000, "coltile"), (168, 32, 200000, "coltile"), (144, 40, 200000, "coltile")])
 def test_narrow_gathers_of_two_stages(rec, I, J, T, want):
     assert bwd(rec, I, J, T)[0].kernel == "k_gemm_sp24_" + want
+
+
+@pytest.mark.parametrize("I,J,T,want", [
+    (104, 256, 60000, "k_gemm_sp24"), (104, 256, 100000, "k_gemm_sp24_narrow_rows"), (128, 256, 20000, "k_gemm_sp24_narrow_rows"), (128, 256, 16000, "k_gemm_sp24"),
+    (104, 248, 20000, "k_gemm_sp24_narrow_rows"), (64, 256, 100, "k_gemm_sp24_narrow_rows")])
+def test_narrow_products_of_two_stages(rec, I, J, T, want):
+    assert fwd(rec, I, J, T)[0].kernel == want
 
 
 def test_dense_backward_puts_the_weights_in_natural_order(rec):

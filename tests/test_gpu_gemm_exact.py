@@ -182,7 +182,7 @@ NARROW_SHAPES = [(24, 56, 67), (56, 24, 67), (64, 88, 131), (88, 64, 131), (48, 
                  (60, 64, 99), (56, 24, 140003), (88, 120, 140003), (64, 64, 140003),
                  (32, 64, 99), (64, 32, 99), (96, 64, 131), (64, 96, 131), (64, 160, 163), (160, 64, 163), (64, 192, 195), (96, 128, 131), (128, 96, 131),
                  (160, 128, 163), (128, 160, 163), (128, 192, 195), (32, 128, 99), (128, 32, 99), (32, 256, 259), (256, 32, 3103), (64, 256, 3075), (256, 64, 3075),
-                 (128, 256, 16387)]
+                 (160, 32, 65539), (136, 8, 65539), (128, 256, 16387), (96, 256, 98307)]
 
 
 @pytest.mark.parametrize("I,J,T", NARROW_SHAPES)
