@@ -380,8 +380,15 @@ bool col_plan(int64_t Adim, int64_t K, int64_t T, bool dense, bool whole, ColPla
 //   piece; 320 x 1088 at 27946 33.8 / 39.5, 384 x 1056 at 16356 20.3 / 24.8.
 //   dense (else weights put in natural order): one tile (1376 x 2880 at 2880, two, 56.7 -> 41.9, but 1728 x 896 at 6467 35.9 /
 //   43.5), 16 pieces (960 x 2880 at 145, 23 of them, 9.1 / 10.8) and 256 terms.
-bool col_gains(const ColPlan& p, int64_t Adim, int64_t K, bool dense) {
+//   Long contractions in 13 pieces and more, all of which read the tokens: a gathered copy is little next to the weights, and the
+//   streaming kernel splits the contraction where its tiles are few.  4:8 from 1320 terms, in pieces of 128 rows from 2.4 million weights and
+//   with 29 to 199 tokens (1792 x 1952 at 68 10.4 / 12.8; at 254 1792 x 1712 12.8 / 13.0, at 19 1568 x 1920 10.0 -> 8.9, 1376 x 1600 at 121
+//   9.9 -> 8.9), in 14 pieces of 256 up to 512 (1752 x 4056 at 470 21.0 / 24.1, 1632 x 3776 at 527 24.0 -> 21.2); 2:4 from 1920 terms in 14 pieces
+//   of 256 (2048 x 3680 at 915 25.6 / 31.8, 1984 x 3808 at 242 14 % faster there; 2016 x 3752 at 515 22.9 -> 19.1).
+bool col_gains(const ColPlan& p, int64_t Adim, int64_t K, int64_t T, bool dense) {
     if (Adim <= 512 && Adim <= K) return true;
+    if (p.tm == 1 && dense && p.pieces > 12 && K >= 1320 && Adim * K >= 2400000 && T > 28 && T < 200) return false;
+    if (p.tm == 2 && p.pieces > 13 && K >= (dense ? 1320 : 1920) && (T <= 512 || (!dense && T > 768))) return false;
     if (dense) return K >= 256 && p.rounds == 1 && p.pieces <= 16;
     return (p.rounds <= 2 && p.pieces <= 16) || p.pieces <= (K > 512 ? 3u : 1u);
 }
@@ -419,7 +426,7 @@ int launch_gemm_sp24_coltile(const void* A, const uint32_t* meta, int64_t Adim, 
         return BIMASK_ERR_UNSUPPORTED;
     ColPlan p;
     const bool over = !disjoint(Bsrc, T, ldb, K, C, ldc, Adim, 2);
-    if (!col_plan(Adim, K, T, dense, over, p) || !col_gains(p, Adim, K, dense)) return BIMASK_ERR_UNSUPPORTED;
+    if (!col_plan(Adim, K, T, dense, over, p) || !col_gains(p, Adim, K, T, dense)) return BIMASK_ERR_UNSUPPORTED;
     const bool few = static_cast<int64_t>(p.rpt) * K <= 32 * 256 * 4;    // pieces per fetching thread
 #define BIMASK_CT(TM_, TN_, D_)                                                                                     \
     return few ? run_coltile<TM_, TN_, D_, 4>(A, meta, Adim, K, Bsrc, ldb, perm, T, C, ldc, p, s)                   \

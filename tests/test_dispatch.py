@@ -172,6 +172,15 @@ def test_narrow_products_of_two_stages(rec, I, J, T, want):
     assert fwd(rec, I, J, T)[0].kernel == want
 
 
+@pytest.mark.parametrize("I,J,T,N,M,fused", [
+    (1792, 1952, 68, 4, 8, False), (1792, 1952, 28, 4, 8, True), (1792, 1952, 250, 4, 8, True), (1376, 1600, 121, 4, 8, True), (1752, 4056, 470, 4, 8, False),
+    (1632, 3776, 527, 4, 8, True), (1216, 3776, 300, 4, 8, True), (2048, 3680, 915, 2, 4, False), (1984, 3808, 242, 2, 4, False), (2016, 3752, 515, 2, 4, True),
+    (1792, 3808, 242, 2, 4, True)])
+def test_few_tokens_on_large_weights_gather_first(rec, I, J, T, N, M, fused):
+    kernels = [l.kernel for l in bwd(rec, I, J, T, N, M)]
+    assert kernels == ["k_gemm_sp24_coltile"] if fused else kernels[0].startswith("k_gather_cols") and len(kernels) == 2, kernels
+
+
 def test_dense_backward_puts_the_weights_in_natural_order(rec):
     for (I, J, N, M, T), rows in small.NATURAL_ORDER.items():
         l = bwd(rec, I, J, T, N, M)
