@@ -220,6 +220,7 @@ int launch_gemm_sp24_big(const void* A, const uint32_t* meta, int64_t Adim, int6
 int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,
                               int64_t ldb, const int32_t* perm, int64_t T, void* C, int64_t ldc,
                               hipStream_t s);
+double gemm_sp24_resident_fill(int64_t Adim, int64_t T);
 // wavefront-private variant for narrow weights (Adim <= 256 with K <= 128, Adim <= 64 with K <= 512 and, with many tokens, Adim <= 128
 // with K <= 256; with a permutation K <= 128 and what the next function names); BIMASK_ERR_UNSUPPORTED otherwise
 int launch_gemm_sp24_narrow(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,

@@ -345,6 +345,13 @@ static int pick_rows_per_tile(int64_t T, int bn, int cus) {
     return static_cast<int>(rpt);
 }
 
+// Share of the 256-row x 64-token slots of its rounds of 256 workgroups that the one-tile-per-workgroup form fills (up to two stages).
+double gemm_sp24_resident_fill(int64_t Adim, int64_t T) {
+    const int64_t grid = ceil_div(T, ceil_div(T, 64) <= 128 ? 64 : pick_rows_per_tile(T, 64, 256)), tiles = ceil_div(Adim, 256);
+    const int64_t groups = grid >= 256 ? 1 : 256 / grid < tiles ? 256 / grid : tiles;
+    return static_cast<double>(T * Adim) / static_cast<double>(ceil_div(grid * groups, 256) * 256 * 64 * ceil_div(tiles, groups) * 256);
+}
+
 // Short-contraction 2:4 GEMM with the token tile resident in LDS and an optional fused
 // column gather.  Returns BIMASK_ERR_UNSUPPORTED when K is too long for this kernel.
 int launch_gemm_sp24_resident(const void* A, const uint32_t* meta, int64_t Adim, int64_t K, const void* Bsrc,

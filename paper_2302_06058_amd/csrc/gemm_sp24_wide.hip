@@ -323,6 +323,18 @@ int launch_gemm_sp24_wide(const void* A, const uint32_t* meta, int64_t Adim, int
         : K > 128 && sectors &&
           ((Adim > 512 && T >= 5000) || (Adim > 256 && T >= 16384) || (Adim > 1024 && K > 256 && T >= 3072));
     if (!gains) return BIMASK_ERR_UNSUPPORTED;
+    // Two stages, against the resident kernel where that fills one or two rounds of workgroups: it writes rows in pieces of 256
+    // columns, this one in pieces of 64, both ends of which lie inside a 128-byte line where the columns are an odd multiple of 32.
+    // 1504 shapes and 191 more; resident -> here with the resident kernel's slots more than 70 % (one round) or 80 % full: 8 % slower in
+    // the mean (192 -> 3040 with the gather at 32475 tokens 49.8 / 60.4, 160 -> 3232 at 6665 15.3 / 18.6, 224 -> 3680 without at 16316
+    // 31.4 / 37.0); with 43 to 62 % 14 % faster, from 33000 tokens 3 %, at 5000 10 %, columns that are multiples of 64 12 %.
+    if (!dense && K <= 256 && Adim % 64 != 0 && Adim > (perm ? 768 : 1024) && T > 5400 && T <= 32768 &&
+        gemm_sp24_resident_fill(Adim, T) > (T <= 16384 ? 0.7 : 0.8))
+        return BIMASK_ERR_UNSUPPORTED;
+    // Four stages, where only tiles of 64 tokens fit: not with a second round just begun (448 -> 384 at 16681 tokens 11.7 / 12.9, 480 -> 640
+    // at 18165 18.1 / 19.5, 512 -> 576 at 20953 17.6 / 19.2, but 416 -> 544 at 21834 24.0 -> 19.2; 448 -> 480 at 16421, where the streaming
+    // kernel's 256-row tiles are not full, 16.9 -> 14.2; 416 -> 1056 at 19755 32.0 -> 25.7; with the gather always).
+    if (!dense && !perm && K > 384 && Adim <= 768 && (Adim <= 384 || Adim > 512) && T > 16384 && T < 21760) return BIMASK_ERR_UNSUPPORTED;
     WidePlan p2, p4;
     const double us2 = wide_plan(2, Adim, K, T, perm != nullptr, dense, p2), us4 = wide_plan(4, Adim, K, T, perm != nullptr, dense, p4);
     if (us2 == 0) return BIMASK_ERR_UNSUPPORTED;

@@ -172,6 +172,17 @@ def test_narrow_products_of_two_stages(rec, I, J, T, want):
     assert fwd(rec, I, J, T)[0].kernel == want
 
 
+# columns that end inside a 128-byte line against the resident kernel with full rounds; four stages and a second round just begun
+@pytest.mark.parametrize("d,K,A_,T,want", [
+    ("p", 192, 3040, 32475, "resident"), ("p", 160, 3232, 6665, "resident"), ("f", 224, 3680, 16316, "resident"), ("p", 192, 3072, 32475, "wide"),
+    ("p", 192, 3040, 34000, "wide"), ("p", 192, 736, 32475, "wide"), ("p", 288, 3040, 32475, "wide"), ("f", 224, 992, 16316, "wide"), ("p", 192, 3040, 18000, "wide"),
+    ("f", 448, 384, 16681, ""), ("f", 480, 640, 18165, ""), ("f", 512, 576, 20953, ""), ("f", 448, 480, 18000, "wide"), ("f", 416, 1056, 19755, "wide"),
+    ("f", 416, 544, 21834, "wide"), ("f", 384, 384, 18000, "wide"), ("p", 448, 576, 18000, "wide")])
+def test_wide_products_and_their_neighbours(rec, d, K, A_, T, want):
+    (l,) = fwd(rec, A_, K, T) if d == "f" else bwd(rec, K, A_, T)
+    assert l.kernel == "k_gemm_sp24" + ("_" + want if want else ""), l
+
+
 @pytest.mark.parametrize("I,J,T,N,M,fused", [
     (1792, 1952, 68, 4, 8, False), (1792, 1952, 28, 4, 8, True), (1792, 1952, 250, 4, 8, True), (1376, 1600, 121, 4, 8, True), (1752, 4056, 470, 4, 8, False),
     (1632, 3776, 527, 4, 8, True), (1216, 3776, 300, 4, 8, True), (2048, 3680, 915, 2, 4, False), (1984, 3808, 242, 2, 4, False), (2016, 3752, 515, 2, 4, True),
