@@ -414,7 +414,9 @@ __device__ __forceinline__ void load_few(const typename DT::raw* p, bool vec, ui
     }
 }
 
-template <typename DT, int M, int TC, int QC>
+// LEAN: at most 128 registers (four workgroups per CU) with M = 16 and 8 columns per thread: the rows' mask bytes are put together
+// after the columns, and a row that is no 16-byte pieces is whole before the next one is loaded.
+template <typename DT, int M, int TC, int QC, bool LEAN = false>
 __device__ __forceinline__ void
 backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t ldw, int N,
               const uint32_t* __restrict__ B_bits, const uint32_t* __restrict__ Bbar_in,
@@ -452,6 +454,7 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
         uint32_t ob[M];
 #pragma unroll
         for (int m = 0; m < M; ++m) ob[m] = 0;           // pad bits of the last mask word stay zero
+        uint32_t kept[LEAN ? QC : 1] = {};
         uint32_t w[M][PW];
         uint32_t bb[M];
         if (j0 < J) {
@@ -475,7 +478,12 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
                     for (int m = 0; m < M; ++m) load8<DT>(W + src[m] * ldw, j0, j0 + 8, true, w[m]);
                 } else {
 #pragma unroll
-                    for (int m = 0; m < M; ++m) load8<DT>(W + src[m] * ldw, j0, J, false, w[m]);
+                    for (int m = 0; m < M; ++m) {
+                        load8<DT>(W + src[m] * ldw, j0, J, false, w[m]);
+                        if constexpr (LEAN)
+#pragma unroll
+                            for (int x = 0; x < PW; ++x) asm volatile("" : "+v"(w[m][x]));
+                    }
                 }
             } else {
                 if (vec_in) {
@@ -503,8 +511,10 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
                     sel = select_top_n<M>(key, N);
                 }
                 const uint32_t keep = Bbar_in ? colbits : (sel & colbits);
+                if constexpr (LEAN) kept[q] = keep;
+                else
 #pragma unroll
-                for (int m = 0; m < M; ++m) ob[m] |= ((keep >> m) & 1u) << q;
+                    for (int m = 0; m < M; ++m) ob[m] |= ((keep >> m) & 1u) << q;
                 const int col = ch * QC + q;
                 if (c0 + col >= J) continue;                 // ragged last chunk: not a row of the operand
                 if (mode == 1) {
@@ -544,6 +554,11 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
                 }
             }
         }
+        if constexpr (LEAN)
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int q = 0; q < QC; ++q) ob[m] |= ((kept[q] >> m) & 1u) << q;
         if constexpr (QC < 8) {                          // 8 / QC neighbouring lanes share a mask byte (same kb, all here)
 #pragma unroll
             for (int m = 0; m < M; ++m) {
@@ -600,14 +615,14 @@ backward_body(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int6
     }
 }
 
-template <typename DT, int M, int TC>
+template <typename DT, int M, int TC, bool LEAN>
 __global__ void __launch_bounds__(kThreads)
 k_backward(const typename DT::raw* __restrict__ W, int64_t I, int64_t J, int64_t ldw, int N,
            const uint32_t* __restrict__ B_bits, const uint32_t* __restrict__ Bbar_in,
            const int32_t* __restrict__ perm, uint32_t* __restrict__ Bbar_bits,
            typename DT::raw* __restrict__ values, uint32_t* __restrict__ index, int mode,
            int wpr, bool vec_in, bool vec_out) {
-#define BIMASK_BODY(QC) backward_body<DT, M, TC, QC>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, wpr, \
+#define BIMASK_BODY(QC) backward_body<DT, M, TC, QC, LEAN>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, wpr, \
                                                      vec_in, vec_out, blockIdx.x, blockIdx.y)
     if constexpr (TC != 32) BIMASK_BODY(8);
     else if constexpr (M != 4) BIMASK_BODY(2);
@@ -910,7 +925,7 @@ int run_forward(const void* W, int64_t I, int64_t J, int64_t ldw, int N, const u
     return check_launch();
 }
 
-template <typename DT, int M, int TC>
+template <typename DT, int M, int TC, bool LEAN = false>
 int run_backward_t(const void* W, int64_t I, int64_t J, int64_t ldw, int N, const uint32_t* B_bits,
                    const uint32_t* Bbar_in, const int32_t* perm, uint32_t* Bbar_bits, void* values,
                    uint32_t* index, int mode, hipStream_t s) {
@@ -926,7 +941,7 @@ int run_backward_t(const void* W, int64_t I, int64_t J, int64_t ldw, int N, cons
         if (!aligned16(values)) return BIMASK_ERR_ALIGN;
         lds = static_cast<size_t>(TC) * lds_stride_m2<DT>() * sizeof(raw);
     }
-    auto kern = k_backward<DT, M, TC>;
+    auto kern = k_backward<DT, M, TC, LEAN>;
     if (lds > 48 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(lds)) != hipSuccess) return BIMASK_ERR_HIP;
@@ -965,8 +980,15 @@ int run_backward(const void* W, int64_t I, int64_t J, int64_t ldw, int N, const 
         }
     }
     // small matrices: narrow tiles so that the grid still covers the chip
-    if (ceil_div(J, 128) * ceil_div(I, kTR) < 256)
+    const int64_t tiles = ceil_div(J, 128) * ceil_div(I, kTR);
+    if (tiles < 256)
         return run_backward_t<DT, M, 32>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, s);
+    // Blocks of 16 in bf16 take 156 registers, three workgroups per CU; with more than 768 tiles four of them on fewer registers are the
+    // shorter way (1:16 3520 x 4224 56.5 -> 40.8 us, 8:16 6400 x 2752 54.5 -> 50.1, 3632 x 8384 80.3 -> 72.4; 2112 x 5312, 714 tiles, 31.7 /
+    // 33.5), the mask alone but for two rounds either way (4:16 5088 x 4016 45.2 / 49.1; 1:16 3520 x 4224 38.6 -> 28.8, 3632 x 8384 64.2 -> 58.3).
+    if constexpr (std::is_same<DT, BF16>::value && M == 16)
+        if (tiles > 768 && (mode != 0 || tiles <= 1024 || tiles > 1536))
+            return run_backward_t<DT, M, 128, true>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, s);
     return run_backward_t<DT, M, 128>(W, I, J, ldw, N, B_bits, Bbar_in, perm, Bbar_bits, values, index, mode, s);
 }
 

@@ -215,6 +215,17 @@ def test_exact_products_reach_every_instance_of_the_gemm_kernels(rec):
     assert not missing, sorted(missing)
 
 
+@pytest.mark.parametrize("I,J,N,M,dtype,want", [
+    (3536, 3472, 1, 16, bm.BF16, "16, 128, true"), (3536, 3472, 8, 16, bm.BF16, "16, 128, true"), (3072, 4096, 8, 16, bm.BF16, "16, 128, false"),
+    (3536, 3472, 8, 16, bm.F32, "16, 128, false"), (3536, 3472, 4, 8, bm.BF16, "8, 128, false"), (1024, 1024, 1, 16, bm.BF16, "16, 32, false")])
+def test_backward_masks_of_16_on_fewer_registers(rec, I, J, N, M, dtype, want):
+    st, (l,) = rec("bimask_backward_mask_compress", A, I, J, J, dtype, N, M, B, C, D, E, A, None)
+    assert st == 0 and l.kernel == "k_backward" and l.args.endswith(want), l
+    for I, J, lean in ((3536, 3472, "true"), (5088, 4016, "false"), (3632, 8384, "true")):           # the mask alone: 784, 1280 and 1914 tiles
+        st, (l,) = rec("bimask_backward_mask", A, I, J, J, bm.BF16, 4, 16, B, C, D, None)
+        assert st == 0 and l.args.endswith("16, 128, " + lean), l
+
+
 def search(rec, I, J, N, M, K):
     need = bm.workspace_bytes(bm.WS_PERM_SEARCH, I, J, 0, K, bm.BF16, N, M)
     st, l = rec("bimask_perm_search", A, I, J, N, M, B, K, C, C, D, E, need, None)

@@ -170,6 +170,20 @@ def test_backward_column_pairs(dtype, N, M):
             assert (x is None and y is None) or torch.equal(x, y), (N, M, I, J)
 
 
+# more than 768 tiles of 128 x 128 (the instance on fewer registers), ragged in both directions; ties; rows that are no 16-byte pieces
+@pytest.mark.parametrize("N", [1, 8])
+def test_blocks_of_16_on_many_tiles(N):
+    import torch
+    I, J = 3536, 3472
+    check_layer(I, J, N, 16, synth.BF16, 2, 5100 + N, "integers")
+    W = to_dev(make_w(I, J, synth.BF16, 5200 + N), synth.BF16)
+    wide = torch.zeros((I, J + 3), dtype=W.dtype, device=W.device)
+    wide[:, :J] = W
+    P, B = i32_dev(perms_of(I, 1, 5300)[0]), bm.bimask_forward_mask(W, N, 16)
+    for want, got in zip(bm.bimask_backward_mask_compress(W, N, 16, B, P), bm.bimask_backward_mask_compress(wide[:, :J], N, 16, B, P)):
+        assert want is got is None or torch.equal(want, got)
+
+
 @pytest.mark.parametrize("I,J,N,M", [(136, 128, 4, 8), (520, 8, 4, 8), (264, 136, 3, 8), (392, 264, 4, 8), (640, 384, 4, 8), (1000, 392, 4, 8),
                                      (520, 32, 2, 4), (520, 128, 2, 4), (776, 136, 2, 4)])
 def test_row_resident_backward_row_tiles(I, J, N, M):
