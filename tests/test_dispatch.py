@@ -203,12 +203,31 @@ def test_dense_backward_puts_the_weights_in_natural_order(rec):
         assert (bwd(rec, I, J, T, 4, 8)[0].kernel == "k_unpermute_dense") == natural, (I, J, T)
 
 
+def label(l):
+    """A kernel as the table of test_gpu_gemm_exact.py names it."""
+    a = l.args.split(", ")
+    if l.kernel == "k_gemm_sp24":
+        return f"{'split ' if int(a[4]) > 1 else ''}{a[0]} x {a[1]}"
+    if l.kernel == "k_gemm_sp24_resident":
+        return f"resident {a[0]} x {a[1]}{' persistent' if a[0] == '256' and a[4] == 'true' else ''}"
+    return "gather" if l.kernel.startswith("k_gather_cols") else l.kernel.replace("k_gemm_sp24_", "")
+
+
+def test_exact_products_run_on_the_kernels_that_their_table_names(rec):
+    for (I, J, T), want in exact.SP24_SHAPES.items():
+        assert (", ".join(map(label, fwd(rec, I, J, T))), ", ".join(map(label, bwd(rec, I, J, T)))) == want, (I, J, T)
+
+
 def test_exact_products_reach_every_instance_of_the_gemm_kernels(rec):
     reached = set()
-    for I, J, T, N, M, dtype in exact.exact_products():
+    for I, J, T, N, M, dtype, perms in exact.exact_products():
         code = bm.F32 if dtype == synth.F32 else bm.BF16
-        reached.update(fwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code) + bwd(rec, I, J, T, N, M, code, perm=None))
-        reached.update(bwd(rec, I, J, T, N, M, code, dX=A))              # these: test_fused_gather_in_place
+        reached.update(fwd(rec, I, J, T, N, M, code))
+        for perm in perms:
+            reached.update(bwd(rec, I, J, T, N, M, code, perm=C if perm else None))
+    for I, J, T, N, M in exact.IN_PLACE_SHAPES:
+        ld = max(I, J)
+        reached.update(bwd(rec, I, J, T, N, M) + bwd(rec, I, J, T, N, M, dX=A, ld=ld, lddx=ld))
     names = {f"{l.kernel}<{l.args}>" if l.args else l.kernel for l in reached}
     families = ("k_gemm_sp24", "k_gemm_f32", "k_unpermute_dense", "k_gather_cols_rows")
     missing = {k for k in rec.lib.stub_kernels().decode().splitlines() if k.startswith(families)} - names

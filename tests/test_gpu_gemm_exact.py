@@ -68,67 +68,70 @@ def exact_layer(I, J, T, N, M, dtype, seed, perm=True):
     assert bad_x.shape[0] == 0, f"backward: {bad_x.shape[0]} wrong outputs, first at (t, j) = {bad_x[0].tolist()}"
 
 
-# (I, J, T): forward kernel / backward kernel with a permutation.  "split 64 x 32": the streaming kernel with the contraction split over
-# groups of wavefronts; "ragged": the contraction ends inside a 128-deep stage, "4-byte rows": it is no multiple of 8
-SP24_SHAPES = [
-    (64, 148, 300),      # wavefront-private, 296-byte rows / wavefront-private, 5 row tiles, 296-byte output rows
-    (256, 64, 300),      # wavefront-private, two sibling wavefronts / wavefront-private 2 x 2 stages
-    (224, 64, 150),      # wavefront-private, 7 row tiles over 2 x 4 / wavefront-private 2 x 2 stages
-    (64, 512, 600),      # wavefront-private, 4 stages / resident-token 256 x 64
-    (160, 128, 200),     # wavefront-private, 5 row tiles / resident-token 128 x 32, two stages
-    (128, 256, 700),     # streaming 128 x 64 / wavefront-private, two sibling wavefronts, with the fused gather
-    (64, 128, 200),      # wavefront-private, two row tiles / wavefront-private, sibling wavefronts
-    (32, 128, 200),      # wavefront-private, one row tile, 1 stage / wavefront-private
-    (32, 256, 200),      # ... 2 stages / wavefront-private
-    (32, 384, 200),      # ... 3 stages / resident-token
-    (32, 512, 200),      # ... 4 stages / resident-token
-    (96, 128, 200),      # wavefront-private, 3 row tiles / wavefront-private
-    (512, 128, 300),     # resident-token 256 x 64, one stage / resident-token 256 x 64, 4 stages
-    (1024, 192, 300),    # split 64 x 32, ragged / column tile
-    (256, 124, 300),     # wavefront-private / resident-token 128 x 32, two stages
-    (124, 128, 300),     # wavefront-private / resident-token 128 x 32, one stage, contraction 124
-    (512, 128, 16400),   # resident-token / column tile
-    (512, 256, 16400),   # streaming 256 x 128 / column tile
-    (384, 384, 16400),   # streaming 128 x 64 / column tile
-    (512, 512, 16400),   # streaming 256 x 128 / column tile
-    (1536, 384, 400),    # split 64 x 64 / column tile, 12 stages
-    (2048, 512, 600),    # streaming 128 x 64 / column tile, 16 stages
-    (64, 576, 500),      # split 64 x 32, ragged / resident-token 256 x 64
-    (64, 576, 66000),    # streaming 64 x 64, ragged / resident-token 256 x 64, persistent
-    (64, 640, 9000),     # streaming 64 x 64, whole stages / resident-token
-    (64, 644, 9000),     # streaming 64 x 64, 4-byte rows / resident-token
-    (256, 576, 66000),   # streaming 256 x 128, ragged / resident-token 256 x 64 persistent, two stages
-    (256, 2304, 2400),   # split 64 x 64 / resident-token, two stages
-    (384, 640, 700),     # split 64 x 32 / resident-token, three stages
-    (384, 640, 2800),    # streaming 128 x 64 (384 rows = 1.5 tiles of 256), whole stages / resident-token
-    (384, 648, 2800),    # ... ragged
-    (384, 644, 2800),    # ... 4-byte rows
-    (256, 640, 12500),   # streaming 256 x 64, whole stages / resident-token
-    (256, 648, 12500),   # ... ragged
-    (256, 644, 12500),   # ... 4-byte rows
-    (512, 644, 12200),   # streaming 256 x 128, 4-byte rows / resident-token
-    (2100, 64, 600),     # resident-token, ragged rows / separate gather, then split 64 x 32 with 4-byte rows, 17 stages
-    (1024, 1028, 300),   # split 64 x 32, 4-byte rows / separate gather, then split 64 x 32
-    (2560, 1024, 2600),  # streaming 256 x 128 / separate gather, then streaming 256 x 64
-    (4096, 2048, 8200),  # forward: 512 x 128 tiles (8 x 65 tiles, the last token tile ragged) / separate gather, streaming 256 x 128
-    (3200, 1152, 22037), # 512 x 128 tiles both ways (the backward one behind the separate gather): 6.25 and 2.25 weight tiles, ragged last token tile
-    (1024, 1152, 65600), # 512 x 128 tiles: two / three weight tiles, 513 token tiles (65 per XCD, the last XCD's run shorter)
-    (4352, 256, 2051),   # resident-token / separate gather with four token rows interleaved per tile (8.5 KB rows), ragged last tile, split 64 x 64
-    (8704, 128, 2305),   # resident-token / separate gather with two token rows interleaved per tile (17 KB rows), one row in the last tile, split 64 x 32
-    (4224, 1024, 11200), # 512 x 128 tiles: nine weight tiles (the last with 128 rows) x 88 token tiles, 99 tiles per XCD on 32 workgroups (3 or 4 each)
-]
+# (I, J, T): forward kernel, backward kernel with a permutation (checked without a GPU in test_dispatch.py).  "a x b": the streaming kernel
+# with tiles of a weight rows x b tokens, "split": its contraction split over groups of wavefronts
+SP24_SHAPES = {
+    (64, 148, 300): ("narrow", "narrow"),                                           # 296-byte rows both ways
+    (256, 64, 300): ("narrow_rows", "coltile"),                                     # two sibling wavefronts forward
+    (224, 64, 150): ("narrow_rows", "coltile"),                                     # 7 row tiles over 2 x 4
+    (64, 512, 600): ("narrow_rows", "resident 256 x 64"),
+    (160, 128, 200): ("narrow_rows", "coltile"),                                    # 5 row tiles
+    (128, 256, 700): ("128 x 64", "narrow_rows"),                                   # two sibling wavefronts with the fused gather
+    (64, 128, 200): ("narrow_rows", "narrow_rows"),
+    (32, 128, 200): ("narrow_rows", "narrow_rows"),
+    (32, 256, 200): ("narrow_rows", "narrow_rows"),
+    (32, 384, 200): ("narrow_rows", "resident 256 x 64"),                           # 3 stages
+    (32, 512, 200): ("narrow_rows", "resident 256 x 64"),                           # 4 stages
+    (96, 128, 200): ("narrow_rows", "narrow_rows"),
+    (512, 128, 300): ("resident 256 x 64", "coltile"),                              # one stage / 4 stages
+    (1024, 192, 300): ("split 64 x 32", "coltile"),                                 # contraction ends inside a stage
+    (256, 124, 300): ("narrow", "resident 128 x 32"),                               # 124 columns
+    (124, 128, 300): ("narrow", "resident 128 x 32"),                               # contraction 124
+    (512, 128, 16400): ("resident 256 x 64", "coltile"),
+    (512, 256, 16400): ("wide", "coltile"),
+    (384, 384, 16400): ("wide", "coltile"),
+    (512, 512, 16400): ("wide", "coltile"),
+    (1536, 384, 400): ("split 64 x 64", "coltile"),                                 # 12 stages
+    (2048, 512, 600): ("128 x 64", "coltile"),                                      # 16 stages
+    (64, 576, 500): ("split 64 x 32", "resident 256 x 64"),                         # contraction ends inside a stage
+    (64, 576, 66000): ("64 x 64", "resident 256 x 64 persistent"),                  # contraction ends inside a stage
+    (64, 640, 9000): ("64 x 64", "resident 256 x 64"),
+    (64, 644, 9000): ("64 x 64", "resident 256 x 64"),                              # 4-byte rows
+    (256, 576, 66000): ("256 x 128", "wide"),                                       # contraction ends inside a stage
+    (256, 2304, 2400): ("split 64 x 64", "coltile"),
+    (384, 640, 700): ("split 64 x 32", "coltile"),
+    (384, 640, 2800): ("128 x 64", "coltile"),                                      # 384 rows = 1.5 tiles of 256
+    (384, 648, 2800): ("128 x 64", "coltile"),                                      # ... contraction ends inside a stage
+    (384, 644, 2800): ("128 x 64", "resident 256 x 64"),                            # ... 4-byte rows
+    (256, 640, 12500): ("256 x 64", "coltile"),
+    (256, 648, 12500): ("256 x 64", "coltile"),                                     # contraction ends inside a stage
+    (256, 644, 12500): ("256 x 64", "resident 256 x 64"),                           # 4-byte rows
+    (512, 644, 12200): ("256 x 128", "resident 256 x 64"),                          # 4-byte rows
+    (2100, 64, 600): ("resident 256 x 64", "gather, split 64 x 32"),                # 4-byte rows, 17 stages
+    (1024, 1028, 300): ("split 64 x 32", "gather, split 64 x 32"),                  # 4-byte rows
+    (2560, 1024, 2600): ("256 x 128", "gather, 256 x 64"),
+    (4096, 2048, 8200): ("big", "gather, 256 x 128"),                               # 8 x 65 tiles, the last token tile ragged
+    (3200, 1152, 22037): ("big", "gather, big"),                                    # 6.25 and 2.25 weight tiles, ragged last token tile
+    (1024, 1152, 65600): ("big", "coltile"),                                        # two weight tiles, 513 token tiles (65 per XCD, the last run shorter)
+    (4352, 256, 2051): ("resident 256 x 64", "gather, split 64 x 64"),              # four token rows interleaved per gather tile (8.5 KB rows), ragged last tile
+    (8704, 128, 2305): ("resident 256 x 64", "gather, split 64 x 32"),              # two token rows per gather tile (17 KB rows), one row in the last tile
+    (4224, 1024, 11200): ("big", "gather, 256 x 128"),                              # nine weight tiles (the last with 128 rows) x 88 token tiles, 99 per XCD on 32 workgroups
+}
 
 
-@pytest.mark.parametrize("I,J,T", SP24_SHAPES)
+@pytest.mark.parametrize("I,J,T", list(SP24_SHAPES))
 @pytest.mark.parametrize("perm", [True, False], ids=["perm", "identity"])
 def test_sparse_core_gemms_are_exact_on_integer_operands(I, J, T, perm):
     exact_layer(I, J, T, 2, 4, synth.BF16, 7000 + I + J + T, perm=perm)
 
 
-@pytest.mark.parametrize("N,M", [(1, 4), (2, 8), (1, 16)])
+OTHER_RATIOS, OTHER_RATIO_SHAPES = [(1, 4), (2, 8), (1, 16)], [(256, 384, 500), (64, 128, 200)]
+
+
+@pytest.mark.parametrize("N,M", OTHER_RATIOS)
 def test_other_ratios_on_the_sparse_cores_are_exact(N, M):
-    exact_layer(256, 384, 500, N, M, synth.BF16, 7100 + M + N)
-    exact_layer(64, 128, 200, N, M, synth.BF16, 7200 + M + N)
+    for q, (I, J, T) in enumerate(OTHER_RATIO_SHAPES):
+        exact_layer(I, J, T, N, M, synth.BF16, 7100 + 100 * q + M + N)
 
 
 # dense operand: streaming tiles 64 x 64, 128 x 64 and 256 x 128 with whole and ragged stages (the split tiles are below); column tiles
@@ -195,7 +198,7 @@ def test_wavefront_private_tiles_are_exact(I, J, T, perm):
 # stages), row tiles and wavefront tiles that are not full, a last token tile of a few rows, fewer wavefront tiles than wavefronts
 WIDE_SHAPES = [(1032, 264, 4099), (1536, 384, 25003), (1096, 392, 9001), (2056, 504, 5003), (392, 1544, 17003), (504, 1096, 20011), (512, 4608, 3139),
                (640, 136, 5003), (288, 136, 16401), (160, 544, 16403),
-               (264, 136, 65500)]                                      # just outside, many tokens: the resident kernel
+               (264, 136, 65500), (192, 992, 16200), (384, 448, 16700)]     # just outside: resident (many tokens; rows that end inside a line), streaming
 WIDE_DENSE_SHAPES = [(264, 104, 4099), (1032, 200, 9001), (1536, 384, 25003), (104, 520, 4101), (320, 1032, 9001), (136, 1096, 30011),
                      (1056, 64, 2051), (72, 544, 4100)]
 
@@ -231,15 +234,19 @@ def test_fp32_tiles_and_contraction_splits_are_exact(I, J, T, N, M, perm):
     exact_layer(I, J, T, N, M, synth.F32, 7600 + I + J, perm=perm)
 
 
+BOTH = (True, False)                                     # with a permutation, with the identity
+
+
 def exact_products():
-    """(I, J, T, N, M, dtype) of every layer above; each with and without a permutation."""
-    for shape in SP24_SHAPES + SPLIT_SHAPES + COLTILE_SHAPES + NARROW_SHAPES + WIDE_SHAPES:
-        yield *shape, 2, 4, synth.BF16
-    for shape in DENSE_SHAPES + COLTILE_SHAPES + WIDE_DENSE_SHAPES + [s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0]:
-        yield *shape, 4, 8, synth.BF16
-    for shape in F32_SMALL + F32_SHAPES:
-        yield *shape, 2, 4, synth.F32
-        yield *shape, 4, 8, synth.F32
+    """(I, J, T, N, M, dtype, permutations) of every layer above: one forward product, a backward product for each entry of the last."""
+    for shapes, ratios, dtype, perms in (
+            (SP24_SHAPES, [(2, 4)], synth.BF16, BOTH), (OTHER_RATIO_SHAPES, OTHER_RATIOS, synth.BF16, BOTH[:1]), (DENSE_SHAPES, [(4, 8)], synth.BF16, BOTH),
+            (SPLIT_SHAPES, [(2, 4)], synth.BF16, BOTH), ([s for s in SPLIT_SHAPES if s[0] % 8 == 0 and s[1] % 8 == 0], [(4, 8)], synth.BF16, BOTH),
+            (COLTILE_SHAPES, [(2, 4), (4, 8)], synth.BF16, BOTH[:1]), (NARROW_SHAPES, [(2, 4)], synth.BF16, BOTH), (WIDE_SHAPES, [(2, 4)], synth.BF16, BOTH[:1]),
+            (WIDE_DENSE_SHAPES, [(4, 8)], synth.BF16, BOTH[:1]), (F32_SMALL, [(2, 4), (4, 8)], synth.F32, BOTH[:1]), (F32_SHAPES, [(2, 4), (4, 8)], synth.F32, BOTH)):
+        for shape in shapes:
+            for ratio in ratios:
+                yield *shape, *ratio, dtype, perms
 
 
 @pytest.mark.parametrize("I,J,T", [(40, 72, 37), (72, 40, 50), (264, 136, 300), (136, 72, 33000)])

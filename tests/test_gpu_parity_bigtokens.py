@@ -93,21 +93,21 @@ def test_config3_layers_with_many_tokens_at_full_token_count(idx):
 @pytest.mark.parametrize("I,J,T,perm,ld_extra", [
     # wavefront-private kernel, several tiles per wavefront (one-tile-ahead prefetch, LDS area reused):
     (64, 148, 140017, True, 0),      # forward 2 row tiles x 2 stages, rows of 296 bytes; backward 5 row tiles, 296-byte output rows
-    (256, 64, 140017, True, 0),      # forward: 8 row tiles over two sibling wavefronts; backward 2 x 2
+    (256, 64, 140017, True, 0),      # forward: 8 row tiles over two sibling wavefronts; backward two stages, whole pieces, fused gather
     (64, 256, 140017, True, 0),      # backward: two sibling wavefronts with the fused gather
-    (224, 64, 140017, True, 0),      # forward: 7 row tiles over two wavefronts of 4 (the last one re-reads tile 6)
-    (160, 128, 70001, False, 0),     # 5 row tiles in one wavefront, identity permutation
-    # resident-token kernel, persistent 256 x 64 variant (at least 1024 tiles of 64 tokens):
-    (64, 576, 70019, True, 0),       # backward: one stage, fused gather
-    (256, 576, 70019, True, 0),      # backward: two stages (more in-features than out-features: more tiles and pieces than the column-tile kernel takes)
-    (512, 128, 70019, False, 0),     # forward: one stage, no permutation; backward identity: streaming tiles
-    (1024, 192, 66000, True, 0),     # forward: two stages; backward: column tiles, K = 1024
+    (224, 64, 140017, True, 0),      # forward: 7 row tiles over two wavefronts of 4 (the last one re-reads tile 6); backward: column tiles
+    (160, 128, 70001, False, 0),     # 5 row tiles in one wavefront; backward, identity: two stages on two sibling wavefronts
+    # resident-token kernel, persistent 256 x 64 variant (one stage, at least 1024 tiles of 64 tokens), and wide outputs:
+    (64, 576, 70019, True, 0),       # backward: fused gather
+    (256, 576, 70019, True, 0),      # backward: two stages, wide kernel with the fused gather
+    (512, 128, 70019, False, 0),     # forward: no permutation; backward identity: streaming tiles
+    (1024, 192, 66000, True, 0),     # forward: two stages, wide kernel; backward: column tiles, K = 1024
     # resident-token kernel, persistent 128 x 32 variant with more than 768 tiles:
     (256, 124, 30011, True, 0),      # backward: 124 in-features (no multiple of 8), two stages
     (124, 128, 30011, True, 0),      # backward: contraction 124 with a permutation, one stage
-    (128, 96, 30011, False, 8),      # leading dimensions that are no multiple of 8... + 8 keeps 16-byte rows; identity
+    (128, 96, 30011, False, 8),      # leading dimensions 8 longer (rows of 16-byte pieces), identity: wavefront-private both ways
     (96, 200, 30011, True, 4),       # rows not 16-byte aligned: the guarded paths of the workgroup kernels at many tokens
-    # column-tile backward kernel at many tokens, and the streaming tiles chosen for them:
+    # column-tile and wide backward kernels at many tokens:
     (512, 128, 50176 + 13, True, 0), (256, 512, 50176 + 13, True, 0), (1536, 384, 66000, True, 0),
 ])
 def test_token_counts_that_select_the_persistent_variants(I, J, T, perm, ld_extra):
