@@ -12,10 +12,10 @@
 // tile is as tall as LDS takes (64 tokens up to 1150 columns, 52 of 1536, 36 of 2048) and ONE workgroup owns the CU: wavefronts
 // 0-3 multiply, each TM row tiles (32 rows) against all tokens, weights straight from L2 into registers that are re-loaded as
 // soon as they are used; wavefronts 4-7 hold the next tile's rows in registers meanwhile.  With 32-row tiles, two workgroups
-// per CU and 2-byte stores (before -> now, backward, us): 1152 x 384 at 25216 tokens 46.1 -> 33.0, 4:8 1536 x 384 66.3 -> 49.5,
-// 1024 x 256 at 12544 17.3 -> 13.8, 2048 x 512 at 3136 19.1 -> 12.4; 1504 x 192 at 1100 16.0 -> 7.3; where dY was gathered by
-// a pass of its own: 768 x 768 at 8192 23.1 -> 13.4, 2048 x 768 at 3000 30.0 -> 17.3.
-// Of the 33 us (timestamps inside the kernel): rows of the first tile 7.5, written 1.5, products while the second tile's rows
+// per CU and 2-byte stores (before -> now, backward, us; means over four cards, buffers in turn): 1152 x 384 at 25216 tokens 45.6 ->
+// 31.2, 4:8 1536 x 384 69.3 -> 48.4, 1024 x 256 at 12544 17.7 -> 14.0, 2048 x 512 at 3136 19.4 -> 12.6; 1504 x 192 at 1100 15.7 -> 7.5;
+// where dY was gathered by a pass of its own: 768 x 768 at 8192 23.7 -> 12.8, 2048 x 768 at 3000 30.4 -> 19.2.
+// 1152 x 384 took 33 us with plain stores of its output, of which (timestamps inside the kernel): rows of the first tile 7.5, written 1.5, products while the second tile's rows
 // arrive 10.5 (6.2 without), output and writing 3, products 6.2, output 1.  Tried without gain: a shorter first tile (33.7),
 // the stages in another order per workgroup, the rows pulled into L2 by scalar loads first (46-58).
 #include "common.hpp"

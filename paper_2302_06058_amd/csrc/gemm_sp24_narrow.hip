@@ -310,14 +310,14 @@ k_gemm_sp24_narrow(const uint16_t* __restrict__ A_all, const uint32_t* __restric
 #undef BIMASK_NARROW_SHAPE
 }
 
-// Rows that are no multiple of 16 bytes stay with the kernel above.
+// Rows that are no multiple of 16 bytes stay with the kernel above, and a few gathers (gemm_sp24_narrow_streams).
 // Token rows and output rows in 16-byte pieces (K and Adim multiples of 8): every load and every store of a tile is unconditional,
 // which is what keeps the next tile's rows in flight.  Where a piece is loaded under a condition the compiler cannot count what is
 // outstanding and waits for the previous load -- and for the previous tile's stores -- before each one.  Pieces and rows that do
 // not exist repeat one that does (loads), go to a spare row (LDS) or store the last piece once more; all tiles but the last one of
 // the matrix are full, and only that one's stores are conditional.  Bound by memory; the kernel above, with conditions -> this
-// one, us: 64 -> 256 columns at 200704 tokens 34.1 -> 28.9 (4.5 TB/s), with the gather 38.6 -> 29.2, 128 -> 256 with the gather
-// 43.1 -> 33.7, 512 -> 64 at 100000 38.4 -> 29.7, 64 -> 128 at 3000 5.1 -> 3.2.
+// one, us (means over four cards, buffers in turn): 64 -> 256 columns at 200704 tokens 34.5 -> 23.3 (5.5 TB/s), with the gather
+// 36.9 -> 23.8, 128 -> 256 with the gather 41.0 -> 28.4, 512 -> 64 at 100000 38.2 -> 28.1, 64 -> 128 at 3000 5.0 -> 3.0.
 // NP: pieces per lane and tile (K <= 16 NP); WHOLE: K = 16 NP and Adim a multiple of 32 TM, known at compile time.
 template <int TM, int NP, bool PERM, bool WHOLE>
 __global__ void __launch_bounds__(64, narrow_waves_per_simd(TM, (NP + 7) / 8))

@@ -5,12 +5,12 @@
 // is a 2-byte scatter on the way in) and its eight wavefronts then work on their own: each takes pairs of weight-row tiles (64
 // rows) in turn against ALL tokens of the tile, weights from L2 into registers that are re-loaded as soon as they are used, and
 // writes its 64 columns through an LDS strip of its own as whole 128-byte lines.  No barrier after the fill, so one wavefront's
-// output overlaps the other's products.  The weight-row-tile loop of the resident kernel (32 rows per wavefront, a barrier per
+// output overlaps another's products (not its own: its next tile waits for weights requested before its stores).  The weight-row-tile loop of the resident kernel (32 rows per wavefront, a barrier per
 // 256) reads every token fragment from LDS for one matrix instruction; here it serves two, and with 128 tokens a weight fragment
 // serves four: half the LDS reads and half the weight bytes through the CU.
-// Measured, us (resident or streaming -> here): 384 -> 1536 columns with the gather at 25216 tokens 45.2 -> 36, without 33 -> 24,
-// 4:8 47 -> 39.  What bounds it now (timestamps, 384 -> 1536): 8 us until the rows are in LDS, then 5.7 per 64 x 100 tile of a
-// wavefront, half of it its output (4 TB/s over the chip).
+// Measured, us (resident or streaming -> here; means over four cards, buffers in turn): 384 -> 1536 columns with the gather at 25216
+// tokens 45.2 -> 33.1, without 38.4 -> 30.0, 4:8 47.4 -> 37.5; 384 -> 1152 29.3 -> 21.7.  What bounds it (timestamps, 384 -> 1536): 8 us
+// until the rows are in LDS, then 5.7 per 64 x 100 tile of a wavefront, half of it its output (4 TB/s over the chip).
 #include "common.hpp"
 
 namespace bimask {
