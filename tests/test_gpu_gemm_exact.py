@@ -366,3 +366,19 @@ def test_fused_gather_in_place(I, J, T, N, M):
     buf[:, :I] = dY
     bm.bimask_sparse_gemm_bwd(buf[:, :I], P, vb, ib, I, J, N, M, dX=buf[:, :J])
     assert torch.equal(buf[:, :J], want) and torch.equal(buf[:, J:], dY[:, J:])
+
+
+# dX beside dY in the rows of one buffer: no byte in common, so the way of separate buffers
+@pytest.mark.parametrize("I,J,T,N,M", [(384, 384, 17003, 2, 4), (256, 64, 40000, 2, 4), (1152, 384, 5003, 2, 4), (384, 1536, 5003, 4, 8), (128, 256, 3000, 2, 4)])
+def test_backward_product_beside_its_input(I, J, T, N, M):
+    import torch
+    rng = np.random.default_rng(7680 + I + T)
+    W = to_dev(synth.store(int_weights(I, J, rng), synth.BF16), synth.BF16)
+    dY = to_dev(synth.store(sparse_rows(T, I, rng), synth.BF16), synth.BF16)
+    P = i32_dev(rng.permutation(I).astype(np.int32))
+    _, vb, ib = bm.bimask_backward_mask_compress(W, N, M, bm.bimask_forward_mask(W, N, M), P)
+    want = bm.bimask_sparse_gemm_bwd(dY, P, vb, ib, I, J, N, M)
+    buf = torch.full((T, I + J), float("nan"), dtype=torch.bfloat16, device=W.device)
+    buf[:, :I] = dY
+    bm.bimask_sparse_gemm_bwd(buf[:, :I], P, vb, ib, I, J, N, M, dX=buf[:, I:])
+    assert torch.equal(buf[:, I:], want) and torch.equal(buf[:, :I], dY)
